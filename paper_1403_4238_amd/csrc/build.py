@@ -19,7 +19,9 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libinpaint.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["fill.hip", "search.hip", "search_mfma.hip", "static_query.hip", "runtime.cpp"]
+# (source, definitions): fill.hip is compiled in parts
+SOURCES = [("fill.hip", "INPAINT_FILL_PART=%d" % p) for p in (0, 3, 2, 1)] + [
+    ("search.hip", None), ("search_mfma.hip", None), ("static_query.hip", None), ("runtime.cpp", None)]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = [
@@ -34,11 +36,12 @@ DEVICE = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
+def _compile(source: tuple) -> str:
+    src, define = source
+    obj = os.path.join(BUILD_DIR, os.path.basename(src) + (define or "").replace("=", "") + ".o")
     path = os.path.join(HERE, src)
     if src.endswith(".hip"):
-        cmd = [HIPCC, "-x", "hip", *DEVICE, *COMMON, "-c", path, "-o", obj]
+        cmd = [HIPCC, "-x", "hip", *DEVICE, *COMMON, *(["-D" + define] if define else []), "-c", path, "-o", obj]
     else:
         cmd = [HIPCC, *COMMON, "-D__HIP_PLATFORM_AMD__", "-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -17,6 +17,13 @@
 
 #include "search_mfma_tile.h"
 
+// This file is compiled once per part so that the parts build in parallel:
+// 0 holds the initialisation, commit, query and persistent SIMT kernels and
+// every launcher, 1 to 3 one family of persistent MFMA kernels each.
+#ifndef INPAINT_FILL_PART
+#error "INPAINT_FILL_PART (0 .. 3) selects what this compilation holds"
+#endif
+
 namespace inpaint {
 
 namespace {
@@ -917,6 +924,7 @@ __device__ __forceinline__ int stage_target_lds(const LdsStage<R> &L, int px, in
 
 // ----------------------------------------------------------------- kernels
 
+#if INPAINT_FILL_PART == 0
 __global__ void k_init_info(InitInfo *info, uint32_t nonce) {
     info->hole_count = 0;
     info->bad = 0;
@@ -1107,6 +1115,7 @@ __global__ __launch_bounds__(256) void k_count_valid(JobDev d) {
     if (threadIdx.x == 0 && s_cnt)
         atomicAdd((unsigned long long *)&d.info->valid_count, (unsigned long long)s_cnt);
 }
+#endif  // INPAINT_FILL_PART 0
 
 // Priority terms and block maxima of every block of the priority range; one
 // wave per 8x8 block.
@@ -1533,7 +1542,7 @@ __device__ void commit_finish(const JobDev &d, Scratch &s, LdsStage<R> &L, const
                 *pix = L.img[i] & 0x00ffffffu;
                 return true;
             });
-        } else if (far && far->idx == idx) {
+        } else if (PRE && far->idx == idx) {
             kk = stage_slots_lean(R, tx, ty, d.tgt, s, recs, rec_tag(v.iter + 1), [&](int t, uint32_t *pix) {
                 *pix = far->pix[t];
                 return far->known[t] != 0;
@@ -1549,7 +1558,7 @@ __device__ void commit_finish(const JobDev &d, Scratch &s, LdsStage<R> &L, const
         }
     } else if (adx <= 2 * R + 2 && ady <= 2 * R + 2) {
         kk = stage_target_lds<R>(L, px, py, tx, ty, d.tgt, s, recs);
-    } else if (far && far->idx == idx) {
+    } else if (PRE && far->idx == idx) {
         // the best pixel of the untouched blocks, copied before this
         // iteration's search ended: its patch is at least 2r + 2 pixels from
         // the filled one, so the copy did not change it
@@ -1883,6 +1892,7 @@ __device__ void fill_search_mfma(const JobDev &d, uint32_t epoch, SearchLdsMfma<
     const int t = (int)blockIdx.x - 1;
     int tx0, ty0;
     mtile::tile_origin<R>(d.rx0, d.ry0, d.ntx, t, &tx0, &ty0);
+    mtile::clear_tables<R>(&S.ft);
     const uint32_t vmask = mtile::stage_tile<R>(d, tx0, ty0, d.rx0, d.rx1, d.ry1, S.tile);
     const bool anyv = __syncthreads_or(vmask != 0);
     FillSync *sy = d.sync;
@@ -1918,12 +1928,9 @@ __device__ void fill_search_mfma(const JobDev &d, uint32_t epoch, SearchLdsMfma<
         if (S.flag == 0) break;
         uint64_t best = ~0ull;
         if (anyv) {
-            // the target from the record words into the patch tables, then
-            // the shifted tables
-            mtile::build_patch<R>(
-                &S.ft, [&](int) { return w & 0x00ffffffu; }, [&](int) { return w >> 31; });
-            __syncthreads();
-            mtile::build_tables<R>(&S.ft);
+            // the target from the record words into the tables
+            mtile::build_tables<R>(
+                &S.ft, [&](int, int) { return w; }, [&](int, int) { return w >> 31; });
             __syncthreads();
             best = tile::wave_min_u64(mtile::score_tile_rows<R>(d, &S.ft, tx0, ty0, vmask, S.tile));
             if ((threadIdx.x & 63) == 0) S.red[threadIdx.x >> 6] = best;
@@ -2047,10 +2054,8 @@ __device__ __forceinline__ void multi_serve_mfma(const JobDev &d, int t, uint32_
             if (__syncthreads_and((int)threadIdx.x >= N || ((w >> 24) & 0x7fu) == tag)) break;
             if (spin >= kSpinLimit) return;
         }
-        mtile::build_patch<R>(
-            &S.ft, [&](int) { return w & 0x00ffffffu; }, [&](int) { return w >> 31; });
-        __syncthreads();
-        mtile::build_tables<R>(&S.ft);
+        mtile::build_tables<R>(
+            &S.ft, [&](int, int) { return w; }, [&](int, int) { return w >> 31; });
         __syncthreads();
         best = tile::wave_min_u64(mtile::score_tile_rows<R>(d, &S.ft, tx0, ty0, vmask, S.tile));
         if ((threadIdx.x & 63) == 0) S.red[threadIdx.x >> 6] = best;
@@ -2143,6 +2148,7 @@ __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(
                                                                              lds.c);
         return;
     }
+    mtile::clear_tables<R>(&lds.s.ft);   // (published by the first poll's barrier)
     multi_search(m, (int)blockIdx.x - m.n_commit, epoch, &pk,
                  [&](const JobDev &d, int t, uint32_t k, uint32_t tag, bool restage, uint32_t &vmask, bool &anyv)
                      __attribute__((always_inline)) { multi_serve_mfma<R>(d, t, k, tag, restage, lds.s, vmask, anyv); });
@@ -2188,11 +2194,13 @@ __device__ __forceinline__ void mixed_role(const MultiPlan &m, int n_iters, uint
                                                                              lds.c);
         return;
     }
+    mtile::clear_tables<R>(&lds.s.ft);   // (published by the first poll's barrier)
     multi_search(m, (int)blockIdx.x - m.n_commit, epoch, pk,
                  [&](const JobDev &d, int t, uint32_t k, uint32_t tag, bool restage, uint32_t &vmask, bool &anyv)
                      __attribute__((always_inline)) { multi_serve_mfma<R>(d, t, k, tag, restage, lds.s, vmask, anyv); });
 }
 
+#if INPAINT_FILL_PART == 3
 __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_fill_multi_mfma_mixed(
     MultiPlan m, int n_iters, uint32_t epoch) {
     __shared__ MixLdsMfma lds;
@@ -2215,6 +2223,7 @@ __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(
         default: break;   // no items; the host plan holds only radii 1 .. 5
     }
 }
+#endif
 
 template <int R, bool ISECT>
 __global__ __launch_bounds__(kCommitThreads) void k_commit(JobDev d) {
@@ -2243,6 +2252,7 @@ __global__ __launch_bounds__(kCommitThreads) void k_commit_batched(const JobDev 
     commit_body<R>(d, s, L);
 }
 
+#if INPAINT_FILL_PART == 0
 __global__ __launch_bounds__(kCommitThreads) void k_stage_query(JobDev d, int tx, int ty, int r) {
     __shared__ Scratch s;
     stage_target(d, tx, ty, r, d.qtgt, s);
@@ -2276,8 +2286,11 @@ __global__ void k_count_active(const JobDev *slots, int nslots, int64_t *out, in
     __syncthreads();
     if (threadIdx.x == 0) *out = cnt;
 }
+#endif  // INPAINT_FILL_PART 0
 
 // ---------------------------------------------------------------- launchers
+
+#if INPAINT_FILL_PART == 0
 
 static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
@@ -2371,18 +2384,24 @@ hipError_t launch_commit_batched(const JobDev *slots, const int32_t *ids, const 
     return hipGetLastError();
 }
 
-static const void *fill_kernel(int r, bool mfma) {
-    if (mfma) {
-        switch (r) {
-            case 1: return (const void *)k_fill_mfma<1>;
-            case 2: return (const void *)k_fill_mfma<2>;
-            case 3: return (const void *)k_fill_mfma<3>;
-            case 4: return (const void *)k_fill_mfma<4>;
-            case 5: return (const void *)k_fill_mfma<5>;
-            case 6: return (const void *)k_fill_mfma<6>;
-            default: return nullptr;
-        }
+#endif  // INPAINT_FILL_PART 0
+
+// Kernels by radius, nullptr where there is none.
+#if INPAINT_FILL_PART == 1
+const void *fill_mfma_kernel(int r) {
+    switch (r) {
+        case 1: return (const void *)k_fill_mfma<1>;
+        case 2: return (const void *)k_fill_mfma<2>;
+        case 3: return (const void *)k_fill_mfma<3>;
+        case 4: return (const void *)k_fill_mfma<4>;
+        case 5: return (const void *)k_fill_mfma<5>;
+        case 6: return (const void *)k_fill_mfma<6>;
+        default: return nullptr;
     }
+}
+#endif
+#if INPAINT_FILL_PART == 0
+const void *fill_simt_kernel(int r) {
     switch (r) {
         case 1: return (const void *)k_fill<1>;
         case 2: return (const void *)k_fill<2>;
@@ -2395,6 +2414,41 @@ static const void *fill_kernel(int r, bool mfma) {
         default: return nullptr;
     }
 }
+#endif
+#if INPAINT_FILL_PART == 2
+const void *multi_mfma_kernel(int r) {
+    switch (r) {
+        case 1: return (const void *)k_fill_multi_mfma<1>;
+        case 2: return (const void *)k_fill_multi_mfma<2>;
+        case 3: return (const void *)k_fill_multi_mfma<3>;
+        case 4: return (const void *)k_fill_multi_mfma<4>;
+        case 5: return (const void *)k_fill_multi_mfma<5>;
+        case 6: return (const void *)k_fill_multi_mfma<6>;
+        default: return nullptr;
+    }
+}
+#endif
+#if INPAINT_FILL_PART == 0
+const void *multi_simt_kernel(int r) {
+    switch (r) {
+        case 1: return (const void *)k_fill_multi<1>;
+        case 2: return (const void *)k_fill_multi<2>;
+        case 3: return (const void *)k_fill_multi<3>;
+        case 4: return (const void *)k_fill_multi<4>;
+        case 5: return (const void *)k_fill_multi<5>;
+        case 6: return (const void *)k_fill_multi<6>;
+        case 7: return (const void *)k_fill_multi<7>;
+        case 8: return (const void *)k_fill_multi<8>;
+        default: return nullptr;
+    }
+}
+#endif
+#if INPAINT_FILL_PART == 3
+const void *multi_mixed_kernel() { return (const void *)k_fill_multi_mfma_mixed; }
+#endif
+
+#if INPAINT_FILL_PART == 0
+static const void *fill_kernel(int r, bool mfma) { return mfma ? fill_mfma_kernel(r) : fill_simt_kernel(r); }
 
 hipError_t fill_blocks_per_cu(int r, bool mfma, int *blocks) {
     const void *f = fill_kernel(r, mfma);
@@ -2413,29 +2467,8 @@ hipError_t launch_fill(const JobDev &d, int ntiles, int n_iters, uint32_t epoch,
 }
 
 static const void *fill_multi_kernel(bool mfma, int r) {
-    if (mfma) {
-        switch (r) {
-            case kMultiMixed: return (const void *)k_fill_multi_mfma_mixed;
-            case 1: return (const void *)k_fill_multi_mfma<1>;
-            case 2: return (const void *)k_fill_multi_mfma<2>;
-            case 3: return (const void *)k_fill_multi_mfma<3>;
-            case 4: return (const void *)k_fill_multi_mfma<4>;
-            case 5: return (const void *)k_fill_multi_mfma<5>;
-            case 6: return (const void *)k_fill_multi_mfma<6>;
-            default: return nullptr;
-        }
-    }
-    switch (r) {
-        case 1: return (const void *)k_fill_multi<1>;
-        case 2: return (const void *)k_fill_multi<2>;
-        case 3: return (const void *)k_fill_multi<3>;
-        case 4: return (const void *)k_fill_multi<4>;
-        case 5: return (const void *)k_fill_multi<5>;
-        case 6: return (const void *)k_fill_multi<6>;
-        case 7: return (const void *)k_fill_multi<7>;
-        case 8: return (const void *)k_fill_multi<8>;
-        default: return nullptr;
-    }
+    if (!mfma) return multi_simt_kernel(r);
+    return r == kMultiMixed ? multi_mixed_kernel() : multi_mfma_kernel(r);
 }
 
 hipError_t multi_blocks_per_cu(bool mfma, int r, int *blocks) {
@@ -2468,5 +2501,6 @@ hipError_t launch_count_active(const JobDev *slots, int nslots, int64_t *out, in
     hipLaunchKernelGGL(k_count_active, dim3(1), dim3(256), 0, s, slots, nslots, out, status);
     return hipGetLastError();
 }
+#endif  // INPAINT_FILL_PART 0
 
 }  // namespace inpaint

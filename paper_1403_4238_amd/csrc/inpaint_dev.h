@@ -21,7 +21,7 @@ constexpr int kMfmaMaxRadius = 6;     // int8-MFMA search: patches up to 13x13
 constexpr int kMfmaTileRows = 16;     // MFMA search tile: 64 x 64 candidates
 constexpr int kFillTileRows = 8;      // persistent fill: candidate rows per search thread
 
-// Padding of the static search planes (srcp, vradp, srcw, srcq) around the
+// Padding of the static search planes (srcp, vradp) around the
 // image, in pixels: every staged search window -- a tile of up to 64 x 64
 // candidates, its halo of up to kMaxRadius and the alignment of its start --
 // lies inside the padded plane, so the search loads need no bounds checks.
@@ -135,8 +135,6 @@ struct JobDev {
     uint64_t *partials;  // one (ssd << 32 | index) per search tile
     TargetStage *tgt;    // staged target of the fill loop
     TargetStage *qtgt;   // staged target of inpaint_find_exemplar
-    uint32_t *srcw;      // MFMA: original RGBX ^ 0x80808080, padded plane (static)
-    uint16_t *srcq;      // MFMA: (|s'|^2 low byte - 128, high byte - 128), padded plane (static)
     uint32_t *srcp;      // source RGBX in the padded plane, zero outside the image and in the hole;
                          // with INTERSECT scoring the 4th byte is 1 on source pixels.  Static,
                          // except under the CURRENT source policy (filled pixels are added)
@@ -216,7 +214,6 @@ bool mfma_supported(int r);
 // int8-MFMA form of the search; same tiling as launch_search with tile_rows 16.
 hipError_t launch_search_mfma(const JobDev &d, bool query, int r, int rx0, int ry0, int rx1, int ry1, int ntx, int nty,
                               hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-hipError_t launch_mfma_planes(const JobDev &d, hipStream_t s);
 // The batch's search over a static (slot, tile) list on the matrix cores;
 // each slot carries the MFMA tiling.
 hipError_t launch_search_batched_mfma(const JobDev *slots, const WorkItem *items, const int32_t *nitems, int r,
@@ -228,6 +225,12 @@ hipError_t launch_commit_batched(const JobDev *slots, const int32_t *ids, const 
 hipError_t launch_count_active(const JobDev *slots, int nslots, int64_t *out, int32_t *status, hipStream_t s);
 hipError_t launch_search_batched(const JobDev *slots, const WorkItem *items, const int32_t *nitems,
                                  int r, int tile_rows, int grid, hipStream_t s);
+// Persistent kernels by radius (nullptr where there is none).
+const void *fill_mfma_kernel(int r);
+const void *fill_simt_kernel(int r);
+const void *multi_mfma_kernel(int r);
+const void *multi_simt_kernel(int r);
+const void *multi_mixed_kernel();
 // Persistent fill: runs up to n_iters iterations of the job in
 // one dispatch; needs fill_grid(ntiles) co-resident work-groups.
 hipError_t fill_blocks_per_cu(int r, bool mfma, int *blocks);

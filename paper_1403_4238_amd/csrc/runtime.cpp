@@ -121,7 +121,7 @@ static MaskStats mask_stats(const uint8_t *m, int stride, int W, int H) {
 }
 
 struct Layout {
-    uint64_t img, gray, hole, hole0, vrad, conf, pcd, blk, partials, tgt, qtgt, srcw, srcq, srcp, vradp, hdist, st,
+    uint64_t img, gray, hole, hole0, vrad, conf, pcd, blk, partials, tgt, qtgt, srcp, vradp, hdist, st,
         sync, fslot, info, key, mplan, log, total;
     int64_t log_cap;
     int max_tiles;
@@ -156,10 +156,7 @@ Layout make_layout(int W, int H, const inpaint_params &p) {
     L.partials = take(8ull * L.max_tiles);
     L.tgt = take(sizeof(TargetStage));
     L.qtgt = take(sizeof(TargetStage));
-    const bool mfma = p.path == INPAINT_PATH_MFMA;
     const uint64_t np = (uint64_t)padded_pitch(W) * padded_rows(H);
-    L.srcw = mfma ? take(4 * np) : 0;
-    L.srcq = mfma ? take(2 * np) : 0;
     L.srcp = take(4 * np);
     L.vradp = take(np);
     // the CURRENT source policy with WHOLE scoring keeps its row distances
@@ -570,8 +567,6 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     d.tgt = (TargetStage *)(ws + L.tgt);
     d.qtgt = (TargetStage *)(ws + L.qtgt);
     d.mfma = p->path == INPAINT_PATH_MFMA ? 1 : 0;
-    d.srcw = d.mfma ? (uint32_t *)(ws + L.srcw) : nullptr;
-    d.srcq = d.mfma ? (uint16_t *)(ws + L.srcq) : nullptr;
     d.srcp = (uint32_t *)(ws + L.srcp);
     d.vradp = ws + L.vradp;
     d.hdist = L.hdist ? ws + L.hdist : nullptr;
@@ -602,7 +597,6 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     if (e == hipSuccess) e = upload_rows(stage_mask, W, mask, mask_stride, H, s);
     const uint32_t nonce = next_nonce();
     if (e == hipSuccess) e = launch_init(d, stage_rgb, ch, stage_mask, hdist, nonce, s);
-    if (e == hipSuccess && d.mfma) e = launch_mfma_planes(d, s);
     if (e == hipSuccess) e = launch_seal(d, nonce, s);
     if (e == hipSuccess) e = hipMemcpyAsync(c->h_key, d.info, sizeof(InitInfo), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -9,21 +9,21 @@
 // with T2' = sum_o m(o) |t'(o)|^2 a per-target constant.  All operands are
 // int8 and all sums fit in int32, so the result is exact.
 //
-// A wave owns 16x16 candidate tiles.  For each patch row dy, the cross term of
-// a tile is a 16 x 96 by 96 x 16 product: the A rows are the 16 candidate rows
-// shifted by dy, each holding 24 consecutive source pixels (RGBX bytes); B is
-// the banded Toeplitz matrix of the target's row dy, B[(x, ch)][n] =
-// m t'(x - n - r, dy, ch) for 0 <= x - n <= 2r.  That is two
-// v_mfma_i32_16x16x64_i8 per dy.  The square term uses the same banded mask
-// against per-pixel planes of the low and high byte of |s'|^2 (two more
-// MFMAs).  The B operands depend only on the target: each work-group builds
-// them as shifted tables in LDS from the 1.3 KB staged target (words and
-// known mask) and every wave reads one patch row's operands at a time; the
-// A fragments are 16-byte LDS reads from the staged tile.
+// A wave owns 16 candidate columns and 64 candidate rows.  For patch row dy,
+// the cross term of 16 candidate rows and columns is a 16 x 96 by 96 x 16
+// product: the A rows are the candidate rows shifted by dy, each holding 24
+// consecutive source pixels of four bytes; B is the banded Toeplitz matrix of
+// the target's row dy, B[(x, ch)][n] = m t'(x - n - r, dy, ch) for 0 <= x - n
+// <= 2r.  The square term is the banded mask against the two bytes of |s'|^2:
+// the high one rides as the fourth byte of each pixel against -128, the low
+// one has a plane and MFMAs of its own.  Which rows share an operand and how
+// the products are packed into v_mfma_i32_16x16x64_i8: search_mfma_tile.h.
+// The B operands depend only on the target: each work-group keeps the target
+// (1.3 KB staged words and known mask) as shifted tables in LDS.
 //
-// The planes are static (candidate windows lie in the original known
+// The source plane is static (candidate windows lie in the original known
 // region, which never changes) and zero-padded, and the tiling starts on a
-// column that puts every staged window on an 8-pixel boundary: a tile is
+// column that puts every staged window on a 16-byte boundary: a tile is
 // staged with unconditional 16-byte loads, issued together with the
 // candidates' validity radii and the staged target before the first wait.
 #include <hip/hip_ext.h>
@@ -43,38 +43,32 @@ struct MfmaLds {
     uint64_t red[kSearchWaves];
 };
 
-// Pass 1 of the B-operand tables from a staged target (words and known mask
-// in column-major slot order); the caller's barrier publishes it.
+// The B-operand tables from a staged target (words and known mask in
+// column-major slot order); the caller's barrier publishes them.
 template <int R>
-__device__ __forceinline__ void build_patch_from(const TargetStage *tg, FragTables<R> *ft) {
-    build_patch<R>(
-        ft, [&](int sl) { return tg->tpix[sl]; }, [&](int sl) { return (tg->mbits[sl >> 5] >> (sl & 31)) & 1u; });
+__device__ __forceinline__ void build_tables_from(const TargetStage *tg, FragTables<R> *ft) {
+    build_tables<R>(
+        ft, [&](int sl, int) { return tg->tpix[sl]; },
+        [&](int sl, int) { return (tg->mbits[sl >> 5] >> (sl & 31)) & 1u; });
 }
 
 // Stages and scores tile t against the target whose B-operand tables are
 // built here from its 1.3 KB stage (build = true) or are already in L.ft
-// (the previous tile of this work-group had the same target).
+// (the previous tile of this work-group had the same target).  L.ft must
+// have been cleared.
 template <int R>
 __device__ __forceinline__ void search_tile_mfma(const JobDev &d, const TargetStage *tg, bool build, bool live,
                                                  int rx0, int ry0, int rx1, int ry1, int ntx, int t, uint64_t *out,
                                                  MfmaLds<R> &L) {
     int tx0, ty0;
     tile_origin<R>(rx0, ry0, ntx, t, &tx0, &ty0);
-    if (build) build_patch_from<R>(tg, &L.ft);   // its loads in flight with the tile's
+    if (build) build_tables_from<R>(tg, &L.ft);   // its loads in flight with the tile's
     const uint32_t vmask = stage_tile<R>(d, tx0, ty0, rx0, rx1, ry1, L.tile);
-    // one barrier publishes the tile (and pass 1) and tells whether any
+    // one barrier publishes the tile and the tables and tells whether any
     // candidate is valid
     if (!__syncthreads_or(live && vmask != 0)) {
-        if (build) {
-            build_tables<R>(&L.ft);   // (every thread reaches this branch: keeps the tables whole)
-            __syncthreads();
-        }
         if (threadIdx.x == 0 && live) out[t] = ~0ull;
         return;
-    }
-    if (build) {
-        build_tables<R>(&L.ft);
-        __syncthreads();
     }
     const uint64_t best = tile::wave_min_u64(score_tile_rows<R>(d, &L.ft, tx0, ty0, vmask, L.tile));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -99,6 +93,8 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search_mfma(JobDev d, int
     __shared__ MfmaLds<R> L;
     const int tile = xcd_band_tile((int)blockIdx.x, (int)gridDim.x);
     if (tile >= ntiles) return;
+    clear_tables<R>(&L.ft);
+    __syncthreads();
     // read now, tested after the tile loads are issued
     bool live = true;
     if (!query) {
@@ -116,6 +112,8 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search_batched_mfma(const
                                                                            const WorkItem *items,
                                                                            const int32_t *nitems) {
     __shared__ MfmaLds<R> L;
+    clear_tables<R>(&L.ft);
+    __syncthreads();
     const int n = *nitems;
     // each work-group takes a contiguous run of the (slot-ordered) items, so
     // consecutive tiles mostly share a target and its B tables are built
@@ -152,34 +150,7 @@ hipError_t launch_mfma_t(const JobDev &d, bool query, int rx0, int ry0, int rx1,
     return hipGetLastError();
 }
 
-// Static source planes of the MFMA search in the padded layout, from the
-// original image: offset RGBX words and the |s'|^2 byte pair (zero outside
-// the image).  Only original known pixels are ever read by a valid
-// candidate, and those never change.
-__global__ __launch_bounds__(256) void k_mfma_planes(JobDev d) {
-    const int pitch = d.pitch;
-    const int64_t n = (int64_t)pitch * padded_rows(d.H);
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int x = (int)(i % pitch) - kPadL, y = (int)(i / pitch) - kPadT;
-    uint32_t w = 0;
-    uint16_t q = 0;
-    if (x >= 0 && x < d.W && y >= 0 && y < d.H) {
-        const uint32_t v = d.img[(int64_t)y * d.W + x];
-        w = v ^ 0x80808080u;
-        q = sq_bytes(v);
-    }
-    d.srcw[i] = w;
-    d.srcq[i] = q;
-}
-
 }  // namespace
-
-hipError_t launch_mfma_planes(const JobDev &d, hipStream_t s) {
-    const int64_t n = (int64_t)d.pitch * padded_rows(d.H);
-    hipLaunchKernelGGL(k_mfma_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d);
-    return hipGetLastError();
-}
 
 bool mfma_supported(int r) { return r >= 1 && r <= kMfmaMaxRadius; }
 

@@ -10,111 +10,99 @@ namespace inpaint {
 namespace mtile {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef v4i v4i_dw __attribute__((aligned(4)));   // at any dword of LDS
 
-constexpr int kMfmaTilesPerWave = 4;                       // 16-row tiles stacked per wave
-constexpr int kMfmaTileH = 16 * kMfmaTilesPerWave;          // 64 rows
-constexpr int kMfmaStrideA = 100;                           // words per staged row (100 % 32 == 4)
-constexpr int kMfmaStrideQ = 272;                           // bytes per |s'|^2 row (68 words, 68 % 32 == 4)
+constexpr int kMfmaTileH = 64;   // candidate rows of a tile
 
+// The staged window of a 64 x 64 tile.  A wave scores 16 candidate columns as
+// four MFMA accumulators s = 0 .. 3 of the candidate rows 4 m + s (m = 0 ..
+// 15): accumulator s then needs, for patch row dy, the window rows 4 m + s +
+// dy, so one A operand (rows 4 m + v) serves every (s, dy) with s + dy = v.
+// P + 3 operands replace the 4 P that four blocks of 16 consecutive rows
+// need; the LDS reads of the operands are what bounds the scoring otherwise.
+// The rows are stored by residue mod 4 so that the 16 lanes of an operand
+// read rows a fixed stride apart: strides of 4 (mod 8) words touch every
+// bank once per 8 lanes.
 template <int R>
 struct MfmaGeom {
     static constexpr int P = 2 * R + 1;
     static constexpr int ROWS = kMfmaTileH + 2 * R;
+    static constexpr int RP = (ROWS + 3) / 4;                   // stored rows per residue
     static constexpr int COLS = kTileW + 2 * R;                 // staged columns that meet nonzero B entries
-    static constexpr int QA = (COLS + 3) / 4;                   // 16-byte quads per row: RGBX words
-    static constexpr int QQ = (2 * COLS + 15) / 16;             // 16-byte quads per row: |s'|^2 byte pairs
-    static constexpr int NA = ROWS * QA, NQ = ROWS * QQ;
+    static constexpr int QA = (COLS + 3) / 4;                   // 16-byte quads per row
+    // Patches up to 9 pixels wide meet 24 window pixels per row of a block of
+    // 16 columns: 16 pixels of one row fill one MFMA, and the other 8 pixels
+    // of two rows share one.  Wider ones take two MFMAs per row.
+    static constexpr bool PAIR = R <= 4;
+    static constexpr int SA = PAIR ? 76 : 84;                   // words per stored row
+    static constexpr int SL = 80;                               // bytes per stored row of |s'|^2 low bytes
+    static constexpr int NA = ROWS * QA;
     static constexpr int AIT = (NA + kSearchWaves * 64 - 1) / (kSearchWaves * 64);
-    static constexpr int QIT = (NQ + kSearchWaves * 64 - 1) / (kSearchWaves * 64);
+    // Stored row of window row y, relative to the operand's lane row (m = 0).
+    static constexpr int slot(int y) { return (y & 3) * RP + (y >> 2); }
 };
 
-// |s'|^2 of an RGBX word, split into (low byte - 128, high byte - 128) int8s
-// packed as a 16-bit value (low byte first).
-__device__ __forceinline__ uint16_t sq_bytes(uint32_t w) {
-    const int r = (int)(w & 255) - 128, g = (int)((w >> 8) & 255) - 128, b = (int)((w >> 16) & 255) - 128;
-    const int q = r * r + g * g + b * b;              // 0 .. 49152
-    const int lo = (q & 255) - 128, hi = (q >> 8) - 128;
-    return (uint16_t)((uint8_t)lo | ((uint32_t)(uint8_t)hi << 8));
-}
-
+// Byte 3 of a staged word and the byte of the low plane are the two bytes of
+// q = |s'|^2 (0 .. 49152), each minus 128 as int8.
 template <int R>
 struct MfmaTile {
-    alignas(16) uint32_t a[MfmaGeom<R>::ROWS * kMfmaStrideA];      // RGBX ^ 0x80808080
-    alignas(16) uint8_t q[MfmaGeom<R>::ROWS * kMfmaStrideQ + 32];  // (lo', hi') per pixel
+    alignas(16) uint32_t a[4 * MfmaGeom<R>::RP * MfmaGeom<R>::SA];   // (R', G', B', q high)
+    alignas(16) uint8_t lo[4 * MfmaGeom<R>::RP * MfmaGeom<R>::SL];   // q low
 };
 
-// Per-target tables a work-group builds in LDS, from which every wave reads
-// its B operands with a few aligned LDS loads.  With T(dy, x) the target
-// word (RGB ^ 0x808080) at patch column x of row dy where known, 0 elsewhere
-// (also outside 0 <= x < P), and M(dy, x) its 0/1 known flag:
-// tc[s][dy][i] = T(dy, i - 16 - s), so the four words lane (n, g) needs,
-// T(dy, 16 h + 4 g - n + j), start 16-byte aligned in copy s = n mod 4;
-// lw[dy][i] = M(dy, i - 16) | M(dy, i - 15) << 16.  Built in two passes:
-// the patch itself into tm / km (one slot per thread, with the per-wave
-// partial sums of T2', k and the row mask), then the shifted tables.
+// The target as every wave reads its B operands from.  With T(dy, x) the
+// target word at patch column x of row dy -- (R', G', B', -128) where known, 0
+// elsewhere, also outside 0 <= x < P and for dy = P -- and M(dy, x) its 0/1
+// known flag: t[s][dy][i] = T(dy, i - 16 - s) and m[s][dy][i] = M(dy, i - 16 -
+// s), so that what lane (n, g) needs, four words or sixteen bytes starting at
+// x = const - n, starts at a multiple of four in copy s = n mod 4.  Only the
+// entries of 0 <= x < P are ever written after clear_tables().
 template <int R>
 struct FragTables {
     static constexpr int P = 2 * R + 1;
-    alignas(16) uint32_t tc[4][P][48];
-    uint32_t lw[P][48];
-    uint32_t tm[P][P];   // T(dy, x)
-    uint8_t km[P][P];    // M(dy, x)
+    alignas(16) uint32_t t[4][P + 1][48];
+    alignas(16) uint8_t m[4][P + 1][48];
     int t2p[kSearchWaves], k[kSearchWaves];
-    uint32_t rowmask[kSearchWaves];
 };
 
-// Pass 1, from the staged words (column-major slots x * P + dy) and the
-// known mask; `word(slot)` and `known(slot)` read them wherever they are.
+// Zeroes the tables (whole work-group, once before the first build; the
+// caller's barrier publishes it).
+template <int R>
+__device__ __forceinline__ void clear_tables(FragTables<R> *ft) {
+    uint32_t *w = &ft->t[0][0][0];
+    for (int i = threadIdx.x; i < (int)(sizeof(ft->t) / 4); i += kSearchWaves * 64) w[i] = 0;
+    uint32_t *b = (uint32_t *)&ft->m[0][0][0];
+    for (int i = threadIdx.x; i < (int)(sizeof(ft->m) / 4); i += kSearchWaves * 64) b[i] = 0;
+}
+
+// Writes the target's entries from its words (column-major slots x * P + dy)
+// and known flags -- `word(slot, round)` and `known(slot, round)` read them
+// wherever they are, round r covering slots r * 256 .. -- with the per-wave
+// partial sums of T2' and k.  The caller's barrier publishes the tables.
 template <int R, class Word, class Known>
-__device__ __forceinline__ void build_patch(FragTables<R> *ft, Word word, Known known) {
-    constexpr int P = 2 * R + 1;
+__device__ __forceinline__ void build_tables(FragTables<R> *ft, Word word, Known known) {
+    constexpr int P = 2 * R + 1, N = P * P, T = kSearchWaves * 64;
     int t2 = 0, kk = 0;
-    uint32_t rows = 0;
-    for (int sl = threadIdx.x; sl < P * P; sl += blockDim.x) {
-        const int x = sl / P, dy = sl - x * P;
-        const bool kn = known(sl);
-        const uint32_t w = kn ? word(sl) : 0u;
-        ft->tm[dy][x] = kn ? (w ^ 0x00808080u) : 0u;
-        ft->km[dy][x] = kn ? 1 : 0;
-        if (kn) {
-            const int a = (int)(w & 255) - 128, b = (int)((w >> 8) & 255) - 128, c = (int)((w >> 16) & 255) - 128;
-            t2 += a * a + b * b + c * c;
-            kk += 1;
-            rows |= 1u << dy;
+#pragma unroll
+    for (int r = 0; r < (N + T - 1) / T; ++r) {
+        const int sl = threadIdx.x + r * T;
+        const bool in = sl < N, kn = in && known(in ? sl : 0, r);
+        const uint32_t w = kn ? (word(sl, r) & 0x00ffffffu) ^ 0x00808080u : 0u;
+        t2 = __builtin_amdgcn_sdot4((int)w, (int)w, t2, false);
+        kk += __popcll(__ballot(kn));
+        if (in) {
+            const int x = sl / P, dy = sl - x * P;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                ft->t[s][dy][x + 16 + s] = kn ? w | 0x80000000u : 0u;
+                ft->m[s][dy][x + 16 + s] = kn ? 1 : 0;
+            }
         }
     }
-    t2 = (int)dpp::sum_u32((uint32_t)t2);   // exact: 32-bit wrap-around sums
-    kk = (int)dpp::sum_u32((uint32_t)kk);
-    rows = dpp::or_u32(rows);
+    t2 = (int)dpp::sum_u32((uint32_t)t2);
     if ((threadIdx.x & 63) == 0) {
         ft->t2p[threadIdx.x >> 6] = t2;
         ft->k[threadIdx.x >> 6] = kk;
-        ft->rowmask[threadIdx.x >> 6] = rows;
-    }
-}
-
-// Pass 2, after a barrier that publishes pass 1.
-template <int R>
-__device__ __forceinline__ void build_tables(FragTables<R> *ft) {
-    constexpr int P = 2 * R + 1, NT = 4 * P * 48, NL = P * 48, T = kSearchWaves * 64;
-#pragma unroll
-    for (int it = 0; it < (NT + T - 1) / T; ++it) {
-        const int e = threadIdx.x + it * T;
-        if (e < NT) {
-            const int s = e / (P * 48), r = e - s * (P * 48), dy = r / 48, i = r - dy * 48;
-            const int x = i - 16 - s;
-            ft->tc[s][dy][i] = (x >= 0 && x < P) ? ft->tm[dy][x] : 0u;
-        }
-    }
-#pragma unroll
-    for (int it = 0; it < (NL + T - 1) / T; ++it) {
-        const int e = threadIdx.x + it * T;
-        if (e < NL) {
-            const int dy = e / 48, i = e - dy * 48, x = i - 16;
-            const uint32_t m0 = (x >= 0 && x < P) ? ft->km[dy][x] : 0u;
-            const uint32_t m1 = (x + 1 >= 0 && x + 1 < P) ? ft->km[dy][x + 1] : 0u;
-            ft->lw[dy][i] = m0 | (m1 << 16);
-        }
     }
 }
 
@@ -126,10 +114,14 @@ __device__ __forceinline__ void tile_origin(int rx0, int ry0, int ntx, int tile,
 }
 
 // Issues every load of the tile at (tx0, ty0) -- staged window (padded rows
-// ty0 - R + kPadT .., columns tx0 - R + kPadL .., a multiple of 8) and the
-// validity radii of this lane's candidates (rows 16 t + 4 g + i of the tile,
-// column tx0 + 16 wave + n) -- then writes the window to LDS.  Returns the
-// lane's validity bits (bit 4 t + i); the caller publishes with a barrier.
+// ty0 - R + kPadT .., columns tx0 - R + kPadL .., a multiple of 4) and the
+// validity radii of this lane's candidates (rows 16 g + j of the tile, column
+// tx0 + 16 wave + n) -- then writes the window to LDS in the offset domain
+// with the bytes of |s'|^2.  They are formed here, from the source plane the
+// SIMT search reads too, rather than kept as planes of their own: a third
+// less to load per tile (4 instead of 6 bytes a pixel) for four dot products
+// and a few byte moves per 16-byte load.  Returns the lane's validity bits
+// (bit j); the caller publishes with a barrier.
 template <int R>
 __device__ __forceinline__ uint32_t stage_tile(const JobDev &d, int tx0, int ty0, int rx0, int rx1, int ry1,
                                                MfmaTile<R> &L) {
@@ -138,63 +130,59 @@ __device__ __forceinline__ uint32_t stage_tile(const JobDev &d, int tx0, int ty0
     const int n = lane & 15, g = lane >> 4;
     const int pitch = d.pitch;
     const int cx = tx0 + 16 * wave + n;
-    const int64_t org = (int64_t)(ty0 - R + kPadT) * pitch + (tx0 - R + kPadL);
-    const uint4 *wa = (const uint4 *)(d.srcw + org);
-    const uint4 *wq = (const uint4 *)(d.srcq + org);
-    uint4 va[G::AIT], vq[G::QIT];
+    const uint4 *src = (const uint4 *)(d.srcp + (int64_t)(ty0 - R + kPadT) * pitch + (tx0 - R + kPadL));
+    uint4 va[G::AIT];
 #pragma unroll
     for (int k = 0; k < G::AIT; ++k) {
         const int i = min(tid + k * kSearchWaves * 64, G::NA - 1);
         const int ly = i / G::QA, lq = i - ly * G::QA;
-        va[k] = wa[ly * (pitch >> 2) + lq];
+        va[k] = src[ly * (pitch >> 2) + lq];
     }
+    const uint8_t *vr = d.vradp + (int64_t)(ty0 + 16 * g + kPadT) * pitch + (cx + kPadL);
+    uint32_t vv[16];
 #pragma unroll
-    for (int k = 0; k < G::QIT; ++k) {
-        const int i = min(tid + k * kSearchWaves * 64, G::NQ - 1);
-        const int ly = i / G::QQ, lq = i - ly * G::QQ;
-        vq[k] = wq[ly * (pitch >> 3) + lq];
-    }
-    const uint8_t *vr = d.vradp + (int64_t)(ty0 + 4 * g + kPadT) * pitch + (cx + kPadL);
-    uint32_t vv[kMfmaTilesPerWave * 4];
-#pragma unroll
-    for (int t = 0; t < kMfmaTilesPerWave; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) vv[4 * t + i] = vr[(16 * t + i) * pitch];
+    for (int j = 0; j < 16; ++j) vv[j] = vr[j * pitch];
 
 #pragma unroll
     for (int k = 0; k < G::AIT; ++k) {
         const int i = min(tid + k * kSearchWaves * 64, G::NA - 1);
         const int ly = i / G::QA, lq = i - ly * G::QA;
-        *(uint4 *)&L.a[ly * kMfmaStrideA + 4 * lq] = va[k];
-    }
+        const int row = (ly & 3) * G::RP + (ly >> 2);
+        const uint32_t in[4] = {va[k].x, va[k].y, va[k].z, va[k].w};
+        uint32_t w[4], q[4];
 #pragma unroll
-    for (int k = 0; k < G::QIT; ++k) {
-        const int i = min(tid + k * kSearchWaves * 64, G::NQ - 1);
-        const int ly = i / G::QQ, lq = i - ly * G::QQ;
-        *(uint4 *)&L.q[ly * kMfmaStrideQ + 16 * lq] = vq[k];
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t v = (in[j] & 0x00ffffffu) ^ 0x00808080u;
+            q[j] = (uint32_t)__builtin_amdgcn_sdot4((int)v, (int)v, 0, false);
+            w[j] = v | (((q[j] << 16) & 0xff000000u) ^ 0x80000000u);
+        }
+        *(uint4 *)&L.a[row * G::SA + 4 * lq] = make_uint4(w[0], w[1], w[2], w[3]);
+        const uint32_t l01 = (q[0] & 255u) | (q[1] & 255u) << 8, l23 = (q[2] & 255u) | (q[3] & 255u) << 8;
+        *(uint32_t *)&L.lo[row * G::SL + 4 * lq] = (l01 | l23 << 16) ^ 0x80808080u;
     }
     uint32_t vmask = 0;
     const bool colok = cx >= rx0 && cx < rx1;
 #pragma unroll
-    for (int t = 0; t < kMfmaTilesPerWave; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int y = ty0 + 16 * t + 4 * g + i;
-            if (colok && y < ry1 && vv[4 * t + i] >= (uint32_t)R) vmask |= 1u << (4 * t + i);
-        }
+    for (int j = 0; j < 16; ++j)
+        if (colok && ty0 + 16 * g + j < ry1 && vv[j] >= (uint32_t)R) vmask |= 1u << j;
     return vmask;
 }
 
 // Scores this lane's candidates of a staged tile and returns their minimum
-// key (~0 if none is valid).  The B operands are read from the per-target
-// tables in LDS one patch row at a time (rows outer, the four 16-row blocks
-// inner): only one row's B operands and the 16 accumulators are live, so
-// the register budget does not grow with the patch size, and the 16
-// independent accumulation chains keep the matrix cores busy.
+// key (~0 if none is valid).  Accumulator s, element i of lane (n, g) is the
+// candidate at tile row 16 g + 4 i + s, column 16 wave + n.
+//
+// Per 16 candidate rows and columns, patches up to 9 pixels wide take P + R + 1
+// MFMAs for the cross term and the high byte of |s'|^2 (which rides in the
+// words' fourth byte against a B byte of -128: -2 acc then carries 256 q_hi)
+// and R + 1 for the low byte (32 bytes of two rows each): 19 at 9x9, where
+// operands of four full rows and separate byte planes took 36.  LDS reads per
+// wave fall from 108 + 54 to 36 + 19 at 9x9.
 template <int R>
 __device__ __forceinline__ uint64_t score_tile_rows(const JobDev &d, const FragTables<R> *ft, int tx0, int ty0,
                                                     uint32_t vmask, const MfmaTile<R> &L) {
-    constexpr int P = 2 * R + 1;
+    using G = MfmaGeom<R>;
+    constexpr int P = G::P, V = P + 3;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, g = lane >> 4, s4 = n & 3;
     const int W = d.W, cx = tx0 + 16 * wave + n;
@@ -206,49 +194,57 @@ __device__ __forceinline__ uint64_t score_tile_rows(const JobDev &d, const FragT
     }
     t2 = __builtin_amdgcn_readfirstlane(t2);
     kk = __builtin_amdgcn_readfirstlane(kk);
-    v4i c0[kMfmaTilesPerWave], c1[kMfmaTilesPerWave], cl[kMfmaTilesPerWave], ch[kMfmaTilesPerWave];
+    v4i acc[4], al[4];
 #pragma unroll
-    for (int t = 0; t < kMfmaTilesPerWave; ++t) {
-        c0[t] = v4i{0, 0, 0, 0};
-        c1[t] = v4i{0, 0, 0, 0};
-        cl[t] = v4i{0, 0, 0, 0};
-        ch[t] = v4i{0, 0, 0, 0};
+    for (int s = 0; s < 4; ++s) {
+        acc[s] = v4i{0, 0, 0, 0};
+        al[s] = v4i{0, 0, 0, 0};
     }
-    const int base = n * kMfmaStrideA + 16 * wave + 4 * g;
-    const int qbase = n * kMfmaStrideQ + 32 * wave + 16 * g;
+    // Operands over two rows: lanes g >= 2 read the next row, which is RP
+    // stored rows on, or (after residue 3) back to residue 0.
+    const int g1 = g & 1, gh = g >> 1;
+    const uint32_t *ax = &L.a[n * G::SA + 16 * wave + 4 * g];
+    const uint32_t *ay = &L.a[n * G::SA + 16 * wave + 16 + 4 * g1];
+    const uint8_t *lb = &L.lo[n * G::SL + 16 * wave + 16 * g1];
+    const int step = gh * G::RP, wrap = gh * (1 - 3 * G::RP);
+    const uint32_t *bx = &ft->t[s4][0][16 + 4 * g - 4 * (n >> 2)];
+    const uint32_t *by = &ft->t[s4][gh][32 + 4 * g1 - 4 * (n >> 2)];
+    const uint8_t *bm = &ft->m[s4][gh][16 + 16 * g1 - 4 * (n >> 2)];
+    v4i b0[P], b1[P], bp[R + 1], bl[R + 1];
 #pragma unroll
-    for (int dy = 0; dy < P; ++dy) {
-        const v4i b0 = *(const v4i *)&ft->tc[s4][dy][4 * g + 16 - 4 * (n >> 2)];
-        const v4i b1 = *(const v4i *)&ft->tc[s4][dy][16 + 4 * g + 16 - 4 * (n >> 2)];
-        v4i bl, bh;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t w = ft->lw[dy][8 * g + 2 * j - n + 16];
-            bl[j] = (int)w;
-            bh[j] = (int)(w << 8);
+    for (int v = 0; v < V; ++v) {
+        const int row = G::slot(v), next = (v & 3) == 3 ? wrap : step;
+        const v4i a0 = *(const v4i *)&ax[row * G::SA];
+        const v4i a1 = G::PAIR ? *(const v4i *)&ay[(row + next) * G::SA] : *(const v4i *)&ax[row * G::SA + 16];
+        const v4i a2 = *(const v4i *)&lb[(row + next) * G::SL];
+        if (v < P) {
+            b0[v] = *(const v4i *)&bx[v * 48];
+            if (!G::PAIR) b1[v] = *(const v4i *)&bx[v * 48 + 16];
+            if ((v & 1) == 0) {
+                if (G::PAIR) bp[v >> 1] = *(const v4i *)&by[v * 48];
+                bl[v >> 1] = *(const v4i_dw *)&bm[v * 48];
+            }
         }
 #pragma unroll
-        for (int t = 0; t < kMfmaTilesPerWave; ++t) {
-            const int row = (16 * t + dy);
-            const v4i a0 = *(const v4i *)&L.a[base + row * kMfmaStrideA];
-            const v4i a1 = *(const v4i *)&L.a[base + row * kMfmaStrideA + 16];
-            const v4i aq = *(const v4i *)&L.q[qbase + row * kMfmaStrideQ];
-            c0[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, b0, c0[t], 0, 0, 0);
-            c1[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, b1, c1[t], 0, 0, 0);
-            cl[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aq, bl, cl[t], 0, 0, 0);
-            ch[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aq, bh, ch[t], 0, 0, 0);
+        for (int s = 0; s < 4; ++s) {
+            const int dy = v - s;
+            if (dy < 0 || dy >= P) continue;
+            acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, b0[dy], acc[s], 0, 0, 0);
+            if (!G::PAIR) acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, b1[dy], acc[s], 0, 0, 0);
+            if (dy & 1) continue;
+            if (G::PAIR) acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bp[dy >> 1], acc[s], 0, 0, 0);
+            al[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a2, bl[dy >> 1], al[s], 0, 0, 0);
         }
     }
+    const uint32_t base = (uint32_t)(t2 + kk * (256 * 128 + 128));
     uint64_t best = ~0ull;
 #pragma unroll
-    for (int t = 0; t < kMfmaTilesPerWave; ++t) {
-        // C lane (n, g) holds rows 4g + i of column n.
+    for (int s = 0; s < 4; ++s) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (vmask & (1u << (4 * t + i))) {
-                const int s2 = 256 * (ch[t][i] + 128 * kk) + cl[t][i] + 128 * kk;
-                const uint32_t ssd = (uint32_t)(t2 - 2 * (c0[t][i] + c1[t][i]) + s2);
-                const int y = ty0 + 16 * t + 4 * g + i;
+            if (vmask & (1u << (4 * i + s))) {
+                const uint32_t ssd = base + (uint32_t)(al[s][i] - 2 * acc[s][i]);
+                const int y = ty0 + 16 * g + 4 * i + s;
                 const uint64_t key = ((uint64_t)ssd << 32) | (uint32_t)(y * W + cx);
                 best = key < best ? key : best;
             }
