@@ -1,0 +1,644 @@
+// One fill iteration around the exemplar search on gfx950: the LDS copy of
+// the target's neighbourhood, the search-independent half of the commit, the
+// half that needs the source patch, the choice of the next target and the
+// upkeep of the priority maxima.  Shared by the stream-form commit kernels
+// and the persistent committer; one work-group of kCommitThreads per image.
+//
+// A commit is a chain of short steps on at most a few thousand pixels, so
+// what bounds it is the number of instructions on that chain and the number
+// of barriers and memory round trips in it, not bandwidth: four waves issue
+// one vector instruction each per four cycles.  Hence the layout below: no
+// integer division by a run-time value, one 32-bit word per pixel for colour
+// and state, gradients kept in a plane instead of being formed again, and
+// the maxima of untouched priority blocks kept in superblocks.
+//
+// Priorities are binary64 and must match a plain sequential CPU evaluation
+// bit for bit: FP contraction is off and every sum runs in the fixed raster
+// order of the patch offsets.
+#pragma once
+
+#include "search_tile.h"
+
+#pragma clang fp contract(off)
+
+namespace inpaint {
+
+constexpr int kSlots = 2;   // patch slots per thread: 17 x 17 over 256 threads
+
+// Neighbourhood staged around the target: the refresh window reaches 2r+1
+// from it, a priority reads its patch (r) and the gradients there.
+template <int R>
+struct Stage {
+    static constexpr int P = 2 * R + 1;
+    static constexpr int half = 3 * R + 2;
+    static constexpr int side = 2 * half + 1;
+    static constexpr int pitch = side <= 32 ? 32 : side;   // a power of two where it is cheap
+    static constexpr int n = pitch * side;
+    static constexpr int reach = 2 * R + 1;
+    static constexpr int WIN = 2 * reach + 1;              // refresh window side
+    static constexpr int NBA = (WIN + 6) / 8 + 1;          // 8x8 blocks it can touch per axis
+    static constexpr int KP = 8 * NBA;                     // side of the touched blocks' pixels
+    static constexpr int at(int dx, int dy) { return (dy + half) * pitch + (dx + half); }
+};
+
+// Pixel state in the fourth byte of an image word.
+constexpr uint32_t kStateHole = 1u << 24, kStateOut = 2u << 24, kColour = 0x00ffffffu;
+__device__ __forceinline__ uint32_t state_of(uint32_t w) { return w >> 24; }
+
+// Integer BT.601 gray of an RGBX word.
+__device__ __forceinline__ int gray_of(uint32_t w) {
+    return (int)((299 * (w & 255) + 587 * ((w >> 8) & 255) + 114 * ((w >> 16) & 255) + 500) / 1000);
+}
+
+// A gradient as the grad plane and the LDS copy hold it: gx in the low and gy
+// in the high 16 bits, 0 where the pixel or one of its four neighbours is not
+// known (a zero gradient and none give the same isophote).
+__device__ __forceinline__ uint32_t pack_grad(int gx, int gy) { return (uint32_t)(gx & 0xffff) | (uint32_t)gy << 16; }
+typedef short short2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int grad_size(uint32_t g) {
+    const short2_t v = __builtin_bit_cast(short2_t, g);
+    return __builtin_amdgcn_sdot2(v, v, 0, false);
+}
+
+__device__ __forceinline__ bool in_img(const JobDev &d, int x, int y) {
+    return (unsigned)x < (unsigned)d.W && (unsigned)y < (unsigned)d.H;
+}
+
+// Column and row of a raster index (0 <= i < W * H < 2^31) by a reciprocal
+// taken once: m = floor(2^32 / W) gives the row or one less, as i < 2^32.
+struct Raster {
+    uint32_t W, m;
+    __device__ explicit Raster(int w) : W((uint32_t)w), m(0xffffffffu / (uint32_t)w) {}
+    __device__ __forceinline__ void split(uint32_t i, int *x, int *y) const {
+        uint32_t q = __umulhi(i, m), r = i - q * W;
+        while (r >= W) {   // at most twice: m may be one below floor(2^32 / W)
+            r -= W;
+            ++q;
+        }
+        *x = (int)r;
+        *y = (int)q;
+    }
+};
+
+// Barrier over LDS contents alone.  __syncthreads also waits for every global
+// store in flight, half a microsecond when one was just issued; the commit's
+// stores are read back only after the full barrier that ends an iteration.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// ---- (key, index) maxima: the greater key wins, equal keys go to the lower
+// index, a strict total order.  Keys are -1 (none) or the bits of a
+// non-negative double.
+struct Best {
+    int64_t key;
+    uint32_t idx;
+};
+__device__ __forceinline__ Best no_best() { return {-1, 0xffffffffu}; }
+__device__ __forceinline__ bool better(int64_t ka, uint32_t ia, int64_t kb, uint32_t ib) {
+    return ka > kb || (ka == kb && ia < ib);
+}
+__device__ __forceinline__ void take(Best &b, int64_t key, uint32_t idx) {
+    if (better(key, idx, b.key, b.idx)) b = {key, idx};
+}
+__device__ __forceinline__ uint32_t max_u32(uint32_t v) {
+    return dpp::fold_wave(v, [](uint32_t a, uint32_t b) { return b > a ? b : a; });
+}
+// The wave's maximum, in every lane (all lanes active): the key's high word,
+// then its low word and the index among the lanes that still match.  Three
+// one-word folds of single DPP instructions are a third of the instructions of
+// a fold over the pairs.
+__device__ __forceinline__ Best wave_best(Best b) {
+    const uint64_t e = (uint64_t)(b.key + 1);   // 0: none
+    const uint32_t hi = (uint32_t)(e >> 32), lo = (uint32_t)e;
+    const uint32_t mh = max_u32(hi);
+    const uint32_t ml = max_u32(hi == mh ? lo : 0u);
+    const uint32_t mi = max_u32(hi == mh && lo == ml ? ~b.idx : 0u);
+    return {(int64_t)((uint64_t)mh << 32 | ml) - 1, ~mi};
+}
+// The wave's minimum of 64-bit words.
+__device__ __forceinline__ uint64_t wave_min(uint64_t v) {
+    const uint64_t e = ~v;
+    const uint32_t hi = (uint32_t)(e >> 32), lo = (uint32_t)e;
+    const uint32_t mh = max_u32(hi), ml = max_u32(hi == mh ? lo : 0u);
+    return ~((uint64_t)mh << 32 | ml);
+}
+
+// State of the fill loop at the start of an iteration; uniform.
+struct Snap {
+    int64_t iter, limit, remaining;
+    uint32_t p;
+    double C, D, Pr;
+    int32_t done, err, pending;
+};
+
+__device__ __forceinline__ Snap load_snap(const IterState *st) {
+    return {st->iter, st->iter_limit, st->remaining, (uint32_t)st->p_idx, st->C, st->D, st->Pr,
+            st->done, st->error, st->pending};
+}
+
+// Superblocks: 2^sshift x 2^sshift priority blocks of the priority range,
+// d.nsx per row, at most kMaxSuper.
+__device__ __forceinline__ int super_count(const JobDev &d) { return d.nsx * d.nsy; }
+
+template <int R>
+struct CommitLds {
+    using S = Stage<R>;
+    double conf[S::n];            // C of known pixels, +0.0 elsewhere
+    uint32_t img[S::n];           // colour and state
+    uint32_t grad[S::n];          // pack_grad
+    int64_t bkey[S::KP * S::KP];  // priority keys of the touched blocks' pixels
+    double fC[S::WIN * S::WIN];   // confidence term of each listed front pixel
+    int16_t front[S::WIN * S::WIN];   // window index of each front pixel of the refresh window
+    int nfront;
+    uint8_t gray[(S::P + 4) * (S::P + 4)];   // of the patch and two pixels around it
+    // work-group folds, one set of words per use
+    int64_t fk[2][4];
+    uint32_t fi[2][4];
+    double wC[4], wD[4];          // terms of each wave's best new front pixel
+    uint64_t smin[4];
+    int cnt[4], late[4];
+    Best part[4];                 // untouched blocks of each touched superblock
+    int64_t bmk[S::NBA * S::NBA];     // maxima of the touched blocks
+    uint32_t bmi[S::NBA * S::NBA];
+    uint32_t tword[S::P * S::P];  // the staged target words (colour, known in bit 31)
+};
+
+// Geometry of one iteration: the window of pixels whose priority can change
+// (within 2r+1 of the filled target, clipped to the image), the 8x8 blocks
+// it touches and the superblocks they lie in (at most two per axis).
+struct Refresh {
+    int wx0, wx1, wy0, wy1;
+    int abx0, aby0, nabx, naby;
+    int sx0, sy0, sx1, sy1;
+};
+template <int R>
+__device__ __forceinline__ Refresh refresh_geometry(const JobDev &d, int px, int py) {
+    constexpr int reach = Stage<R>::reach;
+    Refresh g;
+    g.wx0 = max(px - reach, 0);
+    g.wx1 = min(px + reach + 1, d.W);
+    g.wy0 = max(py - reach, 0);
+    g.wy1 = min(py + reach + 1, d.H);
+    g.abx0 = g.wx0 >> 3;
+    g.aby0 = g.wy0 >> 3;
+    g.nabx = ((g.wx1 - 1) >> 3) - g.abx0 + 1;
+    g.naby = ((g.wy1 - 1) >> 3) - g.aby0 + 1;
+    // (the window lies in the priority range: the hole's box grown by 2r+1)
+    g.sx0 = (g.abx0 - d.pbx0) >> d.sshift;
+    g.sy0 = (g.aby0 - d.pby0) >> d.sshift;
+    g.sx1 = (g.abx0 + g.nabx - 1 - d.pbx0) >> d.sshift;
+    g.sy1 = (g.aby0 + g.naby - 1 - d.pby0) >> d.sshift;
+    return g;
+}
+
+// Priority key from the cached terms: bits of P = C * D (Eq. 1), -1 off the
+// front.  Non-negative doubles order like their bit patterns.
+__device__ __forceinline__ int64_t key_of(double2 cd) {
+    return cd.x < 0.0 ? -1 : __double_as_longlong(cd.x * cd.y);
+}
+
+// Reads everything of the commit that does not depend on the search: the
+// target's neighbourhood and the touched blocks' keys into LDS, and this
+// thread's share of the maximum over every pixel whose priority stays --
+// superblocks that are not touched (`sup`, in LDS or global memory), the
+// untouched blocks of the touched ones (wave w scans the w-th) and the
+// touched blocks' pixels outside the window.  All loads are issued, from
+// clamped addresses, before any is consumed.
+template <int R>
+__device__ __forceinline__ Best gather(const JobDev &d, int px, int py, const Refresh &g, const BlockBest *sup,
+                                       CommitLds<R> &L) {
+    using S = Stage<R>;
+    constexpr int T = kCommitThreads;
+    constexpr int NIT = (S::n + T - 1) / T, KIT = (S::KP * S::KP + T - 1) / T;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ox = px - S::half, oy = py - S::half;
+    const int W = d.W;
+
+    // the w-th touched superblock, its blocks one per lane and round
+    const int sx = g.sx0 + (wave & 1), sy = g.sy0 + (wave >> 1);
+    const bool has = sx <= g.sx1 && sy <= g.sy1;
+    const int sh = d.sshift;
+    const int bx0 = d.pbx0 + (sx << sh), by0 = d.pby0 + (sy << sh);
+    const int brow = lane >> 3, bcol = lane & 7;   // 8 x 8 blocks per round
+    BlockBest bb = {-1, INT64_MAX};
+    const auto load_block = [&](int bx, int by) {
+        BlockBest v = d.blk[min(by, d.pby1 - 1) * d.nbw + min(bx, d.pbx1 - 1)];
+        const bool touched = (unsigned)(bx - g.abx0) < (unsigned)g.nabx && (unsigned)(by - g.aby0) < (unsigned)g.naby;
+        if (bx >= d.pbx1 || by >= d.pby1 || touched) v.key = -1;
+        return v;
+    };
+    if (has) bb = load_block(bx0 + bcol, by0 + brow);
+
+    uint32_t im[NIT], gr[NIT];
+    double c[NIT];
+#pragma unroll
+    for (int k = 0; k < NIT; ++k) {
+        const int t = tid + k * T;
+        const int x = min(max(ox + t % S::pitch, 0), W - 1), y = min(max(oy + t / S::pitch, 0), d.H - 1);
+        const uint32_t i = (uint32_t)(y * W + x);
+        im[k] = d.img[i];
+        c[k] = d.conf[i];
+        gr[k] = d.grad[i];
+    }
+    double2 cd[KIT];
+    const int kx0 = g.abx0 * 8, ky0 = g.aby0 * 8;
+#pragma unroll
+    for (int k = 0; k < KIT; ++k) {
+        const int t = tid + k * T;
+        const int x = min(kx0 + t % S::KP, W - 1), y = min(ky0 + t / S::KP, d.H - 1);
+        cd[k] = d.pcd[(uint32_t)(y * W + x)];
+    }
+
+    // ---- consume
+    Best best = no_best();
+    const int ns = super_count(d);
+    const int e0 = g.sy0 * d.nsx + g.sx0, e1 = g.sy0 * d.nsx + g.sx1, e2 = g.sy1 * d.nsx + g.sx0,
+              e3 = g.sy1 * d.nsx + g.sx1;
+    for (int e = tid; e < ns; e += T) {
+        const BlockBest v = sup[e];
+        if (e != e0 && e != e1 && e != e2 && e != e3) take(best, v.key, (uint32_t)v.idx);
+    }
+    Best part = {bb.key, (uint32_t)bb.idx};
+    if (has)
+        for (int q = 1; q < 1 << (2 * (sh - 3)); ++q) {   // larger superblocks of very large holes
+            const BlockBest v = load_block(bx0 + bcol + 8 * (q & ((1 << (sh - 3)) - 1)), by0 + brow + 8 * (q >> (sh - 3)));
+            take(part, v.key, (uint32_t)v.idx);
+        }
+    part = wave_best(part);
+    if (lane == 0) L.part[wave] = part;
+    take(best, part.key, part.idx);
+#pragma unroll
+    for (int k = 0; k < NIT; ++k) {
+        const int t = tid + k * T;
+        if ((k + 1) * T <= S::n || t < S::n) {
+            const bool in = in_img(d, ox + t % S::pitch, oy + t / S::pitch);
+            const uint32_t w = in ? im[k] : kStateOut;
+            L.img[t] = w;
+            L.grad[t] = gr[k];
+            L.conf[t] = state_of(w) == 0 ? c[k] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KIT; ++k) {
+        const int t = tid + k * T;
+        if ((k + 1) * T <= S::KP * S::KP || t < S::KP * S::KP) {
+            const int col = t % S::KP, row = t / S::KP, x = kx0 + col, y = ky0 + row;
+            const bool in = x < W && y < d.H && col < 8 * g.nabx && row < 8 * g.naby;
+            const int64_t key = in ? key_of(cd[k]) : -1;
+            L.bkey[t] = key;
+            const bool win = x >= g.wx0 && x < g.wx1 && y >= g.wy0 && y < g.wy1;
+            if (!win) take(best, key, (uint32_t)(y * W + x));
+        }
+    }
+    return best;
+}
+
+// A patch in registers, raster slots tid + 256 j ... (dx = t % P - R): which of
+// them the copy fills.
+struct FillSlots {
+    bool fill[kSlots];
+};
+
+// The target patch's hole pixels take the target's confidence and leave the
+// hole and the front, in device memory and LDS; their colours follow with
+// copy_colours.  keep(t): whether hole slot t is filled (INTERSECT scoring
+// fills only those whose source pixel qualifies).  L.cnt gets each wave's
+// count of filled slots, L.nfront is cleared.
+template <int R, class Keep>
+__device__ __forceinline__ FillSlots mark_filled(const JobDev &d, int px, int py, double C, const Refresh &g,
+                                                 CommitLds<R> &L, Keep keep) {
+    using S = Stage<R>;
+    constexpr int P = S::P;
+    FillSlots f;
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+        f.fill[j] = false;
+        if (j * kCommitThreads >= P * P) continue;
+        const int t = threadIdx.x + j * kCommitThreads;
+        const int dx = t % P - R, dy = t / P - R, li = S::at(dx, dy);
+        if (t < P * P && (L.img[li] & kStateHole) && keep(t)) {
+            f.fill[j] = true;
+            const int x = px + dx, y = py + dy;
+            const uint32_t dst = (uint32_t)(y * d.W + x);
+            d.conf[dst] = C;
+            d.hole[dst] = 0;
+            d.pcd[dst] = make_double2(-1.0, 0.0);
+            L.img[li] = 0;
+            L.conf[li] = C;
+            L.bkey[(y - 8 * g.aby0) * S::KP + (x - 8 * g.abx0)] = -1;
+        }
+        n += __popcll(__ballot(f.fill[j]));
+    }
+    if ((threadIdx.x & 63) == 0) L.cnt[threadIdx.x >> 6] = n;
+    if (threadIdx.x == 0) L.nfront = 0;
+    return f;
+}
+
+__device__ __forceinline__ int filled_count(const int *cnt) { return cnt[0] + cnt[1] + cnt[2] + cnt[3]; }
+
+// Pixels of the refresh window on the front (a hole pixel with a known
+// in-image 4-neighbour) go to a compact list, one atomic per wave.  Pixels
+// off the front already carry C = -1 in global memory and key -1 in LDS: a
+// hole pixel off the front has never been on it (the front only gains hole
+// pixels), a known one was set when it was filled or at initialisation.
+template <int R>
+__device__ __forceinline__ void list_front(CommitLds<R> &L) {
+    using S = Stage<R>;
+    constexpr int N = S::WIN * S::WIN;
+#pragma unroll
+    for (int k = 0; k < (N + kCommitThreads - 1) / kCommitThreads; ++k) {
+        const int t = threadIdx.x + k * kCommitThreads;
+        const int li = S::at(min(t, N - 1) % S::WIN - S::reach, min(t, N - 1) / S::WIN - S::reach);
+        const uint32_t c = L.img[li], e = L.img[li + 1], w = L.img[li - 1], n = L.img[li - S::pitch],
+                       s = L.img[li + S::pitch];
+        const bool on = t < N && state_of(c) == 1 &&
+                        (state_of(e) == 0 || state_of(w) == 0 || state_of(n) == 0 || state_of(s) == 0);
+        const uint64_t b = __ballot(on);
+        if (b == 0) continue;
+        int at = 0;
+        if ((threadIdx.x & 63) == 0) at = atomicAdd(&L.nfront, (int)__popcll(b));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (on) L.front[at + __popcll(b & ((1ull << (threadIdx.x & 63)) - 1))] = (int16_t)t;
+    }
+}
+
+// Confidence term of each listed front pixel (Eq. 2): the sum of C over the
+// known pixels of its patch in raster order of the offsets (unknown ones add
+// +0.0, which leaves the running sum bit-identical), over the constant patch
+// area.  One pixel per lane, rows read one ahead of the adds.
+template <int R>
+__device__ __forceinline__ void confidence_terms(CommitLds<R> &L) {
+    using S = Stage<R>;
+    constexpr int P = S::P;
+    const int nf = L.nfront;
+    for (int f = threadIdx.x; f < nf; f += kCommitThreads) {
+        const int wi = L.front[f];
+        const double *cf = &L.conf[S::at(wi % S::WIN - S::reach - R, wi / S::WIN - S::reach - R)];
+        double c0[P], c1[P];
+#pragma unroll
+        for (int dx = 0; dx < P; ++dx) c0[dx] = cf[dx];
+        double sum = 0.0;
+#pragma unroll 1
+        for (int dy = 0; dy < P; ++dy) {
+            // (the row after the last one is still inside the staged square)
+#pragma unroll
+            for (int dx = 0; dx < P; ++dx) c1[dx] = cf[(dy + 1) * S::pitch + dx];
+#pragma unroll
+            for (int dx = 0; dx < P; ++dx) sum = sum + c0[dx];
+#pragma unroll
+            for (int dx = 0; dx < P; ++dx) c0[dx] = c1[dx];
+        }
+        L.fC[f] = sum / (double)(P * P);
+    }
+}
+
+// Gray values of the patch and two pixels around it, before the copy.
+template <int R>
+__device__ __forceinline__ void stage_gray(CommitLds<R> &L) {
+    using S = Stage<R>;
+    constexpr int G = S::P + 4;
+#pragma unroll
+    for (int k = 0; k < (G * G + kCommitThreads - 1) / kCommitThreads; ++k) {
+        const int t = threadIdx.x + k * kCommitThreads;
+        if (t < G * G) L.gray[t] = (uint8_t)gray_of(L.img[S::at(t % G - R - 2, t / G - R - 2)]);
+    }
+}
+
+// Copies the source patch's colours into the filled slots.
+template <int R>
+__device__ __forceinline__ void copy_colours(const JobDev &d, int px, int py, int qx, int qy, const FillSlots &f,
+                                             CommitLds<R> &L) {
+    using S = Stage<R>;
+    constexpr int P = S::P, G = P + 4;
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+        if (j * kCommitThreads >= P * P) continue;
+        const int t = threadIdx.x + j * kCommitThreads;
+        if (f.fill[j]) {
+            const int dx = t % P - R, dy = t / P - R;
+            const uint32_t pix = d.img[(uint32_t)((qy + dy) * d.W + (qx + dx))];
+            d.img[(uint32_t)((py + dy) * d.W + (px + dx))] = pix;
+            L.img[S::at(dx, dy)] = pix;
+            L.gray[(dy + R + 2) * G + (dx + R + 2)] = (uint8_t)gray_of(pix);
+        }
+    }
+}
+
+// Gradients the copy changed: those within one pixel of the patch.
+template <int R>
+__device__ __forceinline__ void refresh_grads(const JobDev &d, int px, int py, CommitLds<R> &L) {
+    using S = Stage<R>;
+    constexpr int Q = S::P + 2, G = S::P + 4;
+#pragma unroll
+    for (int k = 0; k < (Q * Q + kCommitThreads - 1) / kCommitThreads; ++k) {
+        const int t = threadIdx.x + k * kCommitThreads;
+        if (t < Q * Q) {
+            const int dx = t % Q - R - 1, dy = t / Q - R - 1, li = S::at(dx, dy);
+            const uint8_t *gp = &L.gray[(dy + R + 2) * G + (dx + R + 2)];
+            const uint32_t any = (L.img[li] | L.img[li + 1] | L.img[li - 1] | L.img[li + S::pitch] | L.img[li - S::pitch]) >> 24;
+            const uint32_t v = any == 0 ? pack_grad((int)gp[1] - (int)gp[-1], (int)gp[G] - (int)gp[-G]) : 0u;
+            L.grad[li] = v;
+            if (in_img(d, px + dx, py + dy)) d.grad[(uint32_t)((py + dy) * d.W + (px + dx))] = v;
+        }
+    }
+}
+
+// D of Eq. 2: the isophote (-gy, gx) / 2 at the known pixel of the patch with
+// the largest central-difference gradient, dotted with the unit normal of the
+// front (central differences of the hole indicator, out-of-image pixels
+// counted as hole), absolute value, over 255.
+__device__ __forceinline__ double data_term(uint32_t grad, int nx, int ny, double norm1, double norm2) {
+    const int kn = nx * nx + ny * ny;
+    const int gx = (int)(int16_t)(grad & 0xffff), gy = (int)grad >> 16;
+    int a = gx * ny - gy * nx;
+    if (a < 0) a = -a;
+    return kn == 0 ? 0.0 : (0.5 * (double)a) / (kn == 1 ? norm1 : norm2);
+}
+
+// New terms of the listed front pixels, four lanes per pixel: each lane
+// searches a quarter of the patch rows for the largest gradient, the quarters
+// combine in row order (a later one wins only when strictly larger: first in
+// raster order on ties).  Terms go to global memory and the touched blocks'
+// keys; each wave leaves its best pixel in L.fk[1] / fi[1] / wC / wD.
+template <int R>
+__device__ __forceinline__ void data_terms(const JobDev &d, int px, int py, const Refresh &g, CommitLds<R> &L) {
+    using S = Stage<R>;
+    constexpr int P = S::P;
+    const int part = threadIdx.x & 3, nf = L.nfront;
+    Best best = no_best();
+    double bC = 0.0, bD = 0.0;
+    const int y0 = part * P / 4, y1 = (part + 1) * P / 4;
+    // (every lane of a wave takes every round: the quarters combine across lanes)
+    for (int f0 = (threadIdx.x >> 6) * 16; f0 < nf; f0 += kCommitThreads / 4) {
+        const int f = f0 + ((threadIdx.x & 63) >> 2);
+        const bool on = f < nf;
+        const int wi = on ? L.front[f] : 0;
+        const int wx = wi % S::WIN - S::reach, wy = wi / S::WIN - S::reach;
+        uint32_t bg = 0;
+        int b = -1;
+        const uint32_t *gp = &L.grad[S::at(wx - R, wy - R)];
+#pragma unroll
+        for (int r = 0; r < (P + 3) / 4; ++r) {
+            const int dy = min(y0 + r, P - 1);
+            if (y0 + r >= y1) continue;
+#pragma unroll
+            for (int dx = 0; dx < P; ++dx) {
+                const uint32_t v = gp[dy * S::pitch + dx];
+                const int m = grad_size(v);
+                bg = m > b ? v : bg;
+                b = m > b ? m : b;
+            }
+        }
+        // lanes 4 q + 1, + 2 and + 3 onto lane 4 q (quad permutes)
+        const auto merge = [&](int ob, uint32_t og) {
+            bg = ob > b ? og : bg;
+            b = ob > b ? ob : b;
+        };
+        const int b1 = __builtin_amdgcn_mov_dpp(b, 0x55, 0xf, 0xf, true), b2 = __builtin_amdgcn_mov_dpp(b, 0xaa, 0xf, 0xf, true),
+                  b3 = __builtin_amdgcn_mov_dpp(b, 0xff, 0xf, 0xf, true);
+        const uint32_t g1 = __builtin_amdgcn_mov_dpp((int)bg, 0x55, 0xf, 0xf, true),
+                       g2 = __builtin_amdgcn_mov_dpp((int)bg, 0xaa, 0xf, 0xf, true),
+                       g3 = __builtin_amdgcn_mov_dpp((int)bg, 0xff, 0xf, 0xf, true);
+        merge(b1, g1);
+        merge(b2, g2);
+        merge(b3, g3);
+        if (on && part == 0) {
+            const int li = S::at(wx, wy);
+            const int nx = (state_of(L.img[li + 1]) != 0) - (state_of(L.img[li - 1]) != 0);
+            const int ny = (state_of(L.img[li + S::pitch]) != 0) - (state_of(L.img[li - S::pitch]) != 0);
+            const double C = L.fC[f], D = data_term(bg, nx, ny, d.norm1, d.norm2);
+            const int x = px + wx, y = py + wy;
+            const uint32_t idx = (uint32_t)(y * d.W + x);
+            d.pcd[idx] = make_double2(C, D);
+            const int64_t key = __double_as_longlong(C * D);
+            L.bkey[(y - 8 * g.aby0) * S::KP + (x - 8 * g.abx0)] = key;
+            if (better(key, idx, best.key, best.idx)) {
+                best = {key, idx};
+                bC = C;
+                bD = D;
+            }
+        }
+    }
+    const Best w = wave_best(best);
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        L.fk[1][wave] = w.key;
+        L.fi[1][wave] = w.idx;
+    }
+    if (w.key >= 0 && best.key == w.key && best.idx == w.idx) {   // (an index is one lane's)
+        L.wC[wave] = bC;
+        L.wD[wave] = bD;
+    }
+}
+
+// This thread's share of a work-group maximum, posted; after a barrier
+// posted_best() reads the whole.
+template <int R>
+__device__ __forceinline__ void post_best(CommitLds<R> &L, Best b) {
+    b = wave_best(b);
+    if ((threadIdx.x & 63) == 0) {
+        L.fk[0][threadIdx.x >> 6] = b.key;
+        L.fi[0][threadIdx.x >> 6] = b.idx;
+    }
+}
+template <int R>
+__device__ __forceinline__ Best posted_best(const CommitLds<R> &L, int set, int *wave = nullptr) {
+    Best b = {L.fk[set][0], L.fi[set][0]};
+    int at = 0;
+#pragma unroll
+    for (int q = 1; q < 4; ++q)
+        if (better(L.fk[set][q], L.fi[set][q], b.key, b.idx)) {
+            b = {L.fk[set][q], L.fi[set][q]};
+            at = q;
+        }
+    if (wave) *wave = at;
+    return b;
+}
+
+// Brings the block maxima of the touched blocks and the maxima of their
+// superblocks (d.sup and, when not null, the LDS copy `sup`) up to date from
+// L.bkey, and fills no part of the choice of the next target: the persistent
+// committer runs it while the next search is under way.  16 threads per
+// block, 4 keys each; then wave w folds the w-th touched superblock.
+template <int R>
+__device__ __forceinline__ void update_blocks(const JobDev &d, const Refresh &g, CommitLds<R> &L, BlockBest *sup) {
+    using S = Stage<R>;
+    constexpr int NB = S::NBA * S::NBA;
+    const int sub = threadIdx.x & 15;
+#pragma unroll
+    for (int b0 = 0; b0 < NB; b0 += kCommitThreads >> 4) {
+        const int b = b0 + (threadIdx.x >> 4), bc = b % S::NBA, br = b / S::NBA;
+        const bool live = b < NB && bc < g.nabx && br < g.naby;
+        Best best = no_best();
+        if (live) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int e = sub + 16 * j, col = 8 * bc + (e & 7), row = 8 * br + (e >> 3);
+                take(best, L.bkey[row * S::KP + col], (uint32_t)((8 * g.aby0 + row) * d.W + 8 * g.abx0 + col));
+            }
+        }
+        // the block's 16 threads are one DPP row: lane 15 ends with the maximum
+        const uint64_t e = (uint64_t)(best.key + 1);
+        const auto row_max = [](uint32_t v) {
+            v = dpp::fold_rows(v, [](uint32_t a, uint32_t c) { return c > a ? c : a; });
+            return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x15f, 0xf, 0xf, true);   // lane 15 of the row
+        };
+        const uint32_t hi = (uint32_t)(e >> 32), lo = (uint32_t)e;
+        const uint32_t mh = row_max(hi), ml = row_max(hi == mh ? lo : 0u);
+        const uint32_t mi = row_max(hi == mh && lo == ml ? ~best.idx : 0u);
+        if (live && sub == 15) {
+            const int64_t key = (int64_t)((uint64_t)mh << 32 | ml) - 1;
+            const uint32_t idx = ~mi;
+            d.blk[(g.aby0 + br) * d.nbw + g.abx0 + bc] = BlockBest{key, key < 0 ? INT64_MAX : (int64_t)idx};
+            L.bmk[b] = key;
+            L.bmi[b] = idx;
+        }
+    }
+    lds_barrier();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int sx = g.sx0 + (wave & 1), sy = g.sy0 + (wave >> 1);
+    if (sx > g.sx1 || sy > g.sy1) return;   // (uniform over the wave)
+    Best b = no_best();
+    if (lane < NB) {
+        const int bc = lane % S::NBA, br = lane / S::NBA;
+        if (bc < g.nabx && br < g.naby && ((g.abx0 + bc - d.pbx0) >> d.sshift) == sx &&
+            ((g.aby0 + br - d.pby0) >> d.sshift) == sy)
+            b = {L.bmk[lane], L.bmi[lane]};
+    } else if (lane == 63) {
+        b = L.part[wave];
+    }
+    static_assert(NB <= 63, "one touched block per lane, the last lane holds the rest");
+    b = wave_best(b);
+    if (lane == 0) {
+        const BlockBest v = {b.key, b.key < 0 ? INT64_MAX : (int64_t)b.idx};
+        d.sup[sy * d.nsx + sx] = v;
+        if (sup) sup[sy * d.nsx + sx] = v;
+    }
+}
+
+// The patch at raster index idx, column-major slots tid + 256 j, as words with
+// the state in byte 3 (out-of-image slots kStateOut): load it while other
+// work goes on.
+struct PatchWords {
+    uint32_t w[kSlots];
+};
+template <int R>
+__device__ __forceinline__ PatchWords load_patch(const JobDev &d, int tx, int ty) {
+    constexpr int P = 2 * R + 1;
+    PatchWords f{};
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+        if (j * kCommitThreads >= P * P) continue;
+        const int t = min((int)threadIdx.x + j * kCommitThreads, P * P - 1);
+        const int x = tx + t / P - R, y = ty + t % P - R;
+        const uint32_t w = d.img[(uint32_t)(min(max(y, 0), d.H - 1) * d.W + min(max(x, 0), d.W - 1))];
+        f.w[j] = in_img(d, x, y) ? w : kStateOut;
+    }
+    return f;
+}
+
+}  // namespace inpaint

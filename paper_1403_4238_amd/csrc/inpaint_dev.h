@@ -14,6 +14,9 @@ constexpr int kMaxPatch = 2 * kMaxRadius + 1;          // 17
 constexpr int kMaxOffsets = kMaxPatch * kMaxPatch;     // 289
 constexpr int kMaskWords = (kMaxOffsets + 31) / 32;    // 10
 constexpr int kBlock = 8;                              // priority block side (one wave)
+// Superblocks of the priority range: 8 x 8 blocks each (64 x 64 pixels), or
+// more, so that at most this many cover it.
+constexpr int kMaxSuper = 512;
 constexpr int kTileW = 64;                             // search tile width (one wave)
 constexpr int kSearchWaves = 4;                        // waves per search work-group
 constexpr int kCommitThreads = 256;   // one work-group per image; 512 VGPRs per thread
@@ -84,8 +87,6 @@ struct alignas(256) IterState {
 constexpr int kGoCopies = 16;
 struct alignas(256) FillRec {
     uint64_t go;
-    uint32_t t2, k;
-    uint32_t mbits[kMaskWords], sbits[kMaskWords], ebits[kMaskWords];
     uint32_t tpix[kMaxOffsets];
 };
 struct FillSync {
@@ -124,14 +125,15 @@ struct InitInfo {
 // Everything a kernel needs about one job.  Passed by value to the
 // single-image kernels and stored in the slot table for batched ones.
 struct JobDev {
-    uint32_t *img;       // RGBX, W*H
-    uint8_t *gray;       // W*H
+    uint32_t *img;       // RGB and the pixel state (0 known, 1 hole) in the 4th byte, W*H
+    uint32_t *grad;      // packed gradients of the priority range's pixels, W*H
     uint8_t *hole;       // W*H, 1 = still to fill
     uint8_t *hole0;      // W*H, 1 = in the original hole (fixed at create)
     uint8_t *vrad;       // W*H, largest r <= 8 with a valid patch at the centre
     double *conf;        // W*H
     double2 *pcd;        // W*H (C, D) of front pixels; C = -1 elsewhere
     BlockBest *blk;      // ceil(W/8)*ceil(H/8)
+    BlockBest *sup;      // maxima of superblocks of the priority range, kMaxSuper
     uint64_t *partials;  // one (ssd << 32 | index) per search tile
     TargetStage *tgt;    // staged target of the fill loop
     TargetStage *qtgt;   // staged target of inpaint_find_exemplar
@@ -151,6 +153,7 @@ struct JobDev {
     int32_t rx0, ry0, rx1, ry1;   // search rect of centres (clipped)
     int32_t pbx0, pby0, pbx1, pby1;  // priority block range (block units)
     int32_t nbw;                  // blocks per image row
+    int32_t sshift, nsx, nsy;     // superblocks: 2^sshift blocks a side, nsx x nsy of them
     int32_t tile_rows;            // candidate rows per thread in the search
     int32_t ntx, nty;             // search tiles over the rect
     int32_t mfma;                 // 1: the search runs on the matrix cores

@@ -121,7 +121,7 @@ static MaskStats mask_stats(const uint8_t *m, int stride, int W, int H) {
 }
 
 struct Layout {
-    uint64_t img, gray, hole, hole0, vrad, conf, pcd, blk, partials, tgt, qtgt, srcp, vradp, hdist, st,
+    uint64_t img, grad, hole, hole0, vrad, conf, pcd, blk, sup, partials, tgt, qtgt, srcp, vradp, hdist, st,
         sync, fslot, info, key, mplan, log, total;
     int64_t log_cap;
     int max_tiles;
@@ -143,7 +143,7 @@ Layout make_layout(int W, int H, const inpaint_params &p) {
         return o;
     };
     L.img = take(4 * n);
-    L.gray = take(n);
+    L.grad = take(4 * n);
     L.hole = take(n);
     L.hole0 = take(n);
     L.vrad = take(n);
@@ -151,6 +151,7 @@ Layout make_layout(int W, int H, const inpaint_params &p) {
     L.pcd = take(16 * n);  // also the upload staging area during create (<= 6n bytes)
     const uint64_t nblk = (uint64_t)((W + kBlock - 1) / kBlock) * ((H + kBlock - 1) / kBlock);
     L.blk = take(sizeof(BlockBest) * nblk);
+    L.sup = take(sizeof(BlockBest) * kMaxSuper);
     // (+7: the MFMA tiling may start up to 7 columns left of the rect)
     L.max_tiles = ((W + 7 + kTileW - 1) / kTileW) * ((H + search_tile_h(4) - 1) / search_tile_h(4));
     L.partials = take(8ull * L.max_tiles);
@@ -556,13 +557,14 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     JobDev &d = c->d;
     uint8_t *ws = c->ws;
     d.img = (uint32_t *)(ws + L.img);
-    d.gray = ws + L.gray;
+    d.grad = (uint32_t *)(ws + L.grad);
     d.hole = ws + L.hole;
     d.hole0 = ws + L.hole0;
     d.vrad = ws + L.vrad;
     d.conf = (double *)(ws + L.conf);
     d.pcd = (double2 *)(ws + L.pcd);
     d.blk = (BlockBest *)(ws + L.blk);
+    d.sup = (BlockBest *)(ws + L.sup);
     d.partials = (uint64_t *)(ws + L.partials);
     d.tgt = (TargetStage *)(ws + L.tgt);
     d.qtgt = (TargetStage *)(ws + L.qtgt);
@@ -634,12 +636,17 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     set_tiles(d, c->mfma ? kMfmaTileRows : (p->tile_rows ? p->tile_rows : kDefaultTileRows), c->mfma ? d.r : 0);
 
     // Priority blocks: the hole's bbox grown by 2r+1 (how far a fill can
-    // change a priority), in 32x32 blocks.
+    // change a priority), in 8x8 blocks.
     const int reach = 2 * d.r + 1;
     d.pbx0 = std::max(info.bx0 - reach, 0) / kBlock;
     d.pby0 = std::max(info.by0 - reach, 0) / kBlock;
     d.pbx1 = (std::min(info.bx1 + reach, W) + kBlock - 1) / kBlock;
     d.pby1 = (std::min(info.by1 + reach, H) + kBlock - 1) / kBlock;
+    for (d.sshift = 3;; ++d.sshift) {
+        d.nsx = (d.pbx1 - d.pbx0 + (1 << d.sshift) - 1) >> d.sshift;
+        d.nsy = (d.pby1 - d.pby0 + (1 << d.sshift) - 1) >> d.sshift;
+        if ((int64_t)d.nsx * d.nsy <= kMaxSuper) break;
+    }
 
     const uint32_t nonce2 = next_nonce();
     e = launch_count_valid(d, s);
