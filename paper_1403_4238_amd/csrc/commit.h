@@ -23,6 +23,17 @@
 
 namespace inpaint {
 
+// The functions below take the thread's number.  What they derive from it is
+// the same in every iteration, far more than the registers hold; the loop of
+// the persistent committer hands them a number that the compiler cannot see
+// through, so that it is formed again instead of spilled (1080p 9x9: SIMT form
+// 74.7 -> 56.4 ms a removal, MFMA form level).
+__device__ __forceinline__ int thread_number() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 constexpr int kSlots = 2;   // patch slots per thread: 17 x 17 over 256 threads
 
 // Neighbourhood staged around the target: the refresh window reaches 2r+1
@@ -32,12 +43,14 @@ struct Stage {
     static constexpr int P = 2 * R + 1;
     static constexpr int half = 3 * R + 2;
     static constexpr int side = 2 * half + 1;
-    static constexpr int pitch = side <= 32 ? 32 : side;   // a power of two where it is cheap
-    static constexpr int n = pitch * side;
+    static constexpr int cols = side <= 32 ? 32 : side;    // staged per row: a power of two where it is cheap
+    static constexpr int pitch = cols | 1;                 // odd: a column of pixels spreads over the LDS banks
+    static constexpr int n = cols * side;
     static constexpr int reach = 2 * R + 1;
     static constexpr int WIN = 2 * reach + 1;              // refresh window side
     static constexpr int NBA = (WIN + 6) / 8 + 1;          // 8x8 blocks it can touch per axis
     static constexpr int KP = 8 * NBA;                     // side of the touched blocks' pixels
+    static constexpr int BP = KP % 16 ? KP : KP + 8;       // their pitch in LDS: rows of two blocks on other banks
     static constexpr int at(int dx, int dy) { return (dy + half) * pitch + (dx + half); }
 };
 
@@ -146,10 +159,10 @@ __device__ __forceinline__ int super_count(const JobDev &d) { return d.nsx * d.n
 template <int R>
 struct CommitLds {
     using S = Stage<R>;
-    double conf[S::n];            // C of known pixels, +0.0 elsewhere
-    uint32_t img[S::n];           // colour and state
-    uint32_t grad[S::n];          // pack_grad
-    int64_t bkey[S::KP * S::KP];  // priority keys of the touched blocks' pixels
+    double conf[S::pitch * S::side];   // C of known pixels, +0.0 elsewhere
+    uint32_t img[S::pitch * S::side];  // colour and state
+    uint32_t grad[S::pitch * S::side]; // pack_grad
+    int64_t bkey[S::BP * S::KP];  // priority keys of the touched blocks' pixels
     double fC[S::WIN * S::WIN];   // confidence term of each listed front pixel
     int16_t front[S::WIN * S::WIN];   // window index of each front pixel of the refresh window
     int nfront;
@@ -208,12 +221,12 @@ __device__ __forceinline__ int64_t key_of(double2 cd) {
 // touched blocks' pixels outside the window.  All loads are issued, from
 // clamped addresses, before any is consumed.
 template <int R>
-__device__ __forceinline__ Best gather(const JobDev &d, int px, int py, const Refresh &g, const BlockBest *sup,
+__device__ __forceinline__ Best gather(int tid, const JobDev &d, int px, int py, const Refresh &g, const BlockBest *sup,
                                        CommitLds<R> &L) {
     using S = Stage<R>;
     constexpr int T = kCommitThreads;
     constexpr int NIT = (S::n + T - 1) / T, KIT = (S::KP * S::KP + T - 1) / T;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int ox = px - S::half, oy = py - S::half;
     const int W = d.W;
 
@@ -234,22 +247,46 @@ __device__ __forceinline__ Best gather(const JobDev &d, int px, int py, const Re
 
     uint32_t im[NIT], gr[NIT];
     double c[NIT];
-#pragma unroll
-    for (int k = 0; k < NIT; ++k) {
-        const int t = tid + k * T;
-        const int x = min(max(ox + t % S::pitch, 0), W - 1), y = min(max(oy + t / S::pitch, 0), d.H - 1);
-        const uint32_t i = (uint32_t)(y * W + x);
-        im[k] = d.img[i];
-        c[k] = d.conf[i];
-        gr[k] = d.grad[i];
-    }
     double2 cd[KIT];
     const int kx0 = g.abx0 * 8, ky0 = g.aby0 * 8;
+    // Away from the image border every slot of the thread grid is a pixel:
+    // no clamps, and small byte offsets from uniform bases.
+    constexpr int SR = (NIT * T + S::cols - 1) / S::cols, KR = (KIT * T + S::KP - 1) / S::KP;   // rows of the grids
+    const bool inner = W <= 65536 && ox >= 0 && oy >= 0 && ox + S::cols <= W && oy + SR <= d.H && kx0 + S::KP <= W &&
+                       ky0 + KR <= d.H;
+    if (inner) {
+        const int64_t o = (int64_t)oy * W + ox, ko = (int64_t)ky0 * W + kx0;
+        const uint32_t *pi = d.img + o, *pg = d.grad + o;
+        const double *pc = d.conf + o;
+        const double2 *pk = d.pcd + ko;
 #pragma unroll
-    for (int k = 0; k < KIT; ++k) {
-        const int t = tid + k * T;
-        const int x = min(kx0 + t % S::KP, W - 1), y = min(ky0 + t / S::KP, d.H - 1);
-        cd[k] = d.pcd[(uint32_t)(y * W + x)];
+        for (int k = 0; k < NIT; ++k) {
+            const int t = tid + k * T;
+            const uint32_t i = (uint32_t)(t / S::cols) * (uint32_t)W + (uint32_t)(t % S::cols);
+            im[k] = *(const uint32_t *)((const char *)pi + 4 * i);
+            c[k] = *(const double *)((const char *)pc + 8 * i);
+            gr[k] = *(const uint32_t *)((const char *)pg + 4 * i);
+        }
+#pragma unroll
+        for (int k = 0; k < KIT; ++k) {
+            const int t = tid + k * T;
+            cd[k] = *(const double2 *)((const char *)pk + 16 * ((uint32_t)(t / S::KP) * (uint32_t)W + (uint32_t)(t % S::KP)));
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < NIT; ++k) {
+            const int t = tid + k * T, lx = ox + t % S::cols, ly = oy + t / S::cols;
+            const uint32_t i = (uint32_t)(min(max(ly, 0), d.H - 1) * W + min(max(lx, 0), W - 1));
+            im[k] = in_img(d, lx, ly) ? d.img[i] : kStateOut;
+            c[k] = d.conf[i];
+            gr[k] = d.grad[i];
+        }
+#pragma unroll
+        for (int k = 0; k < KIT; ++k) {
+            const int t = tid + k * T, x = kx0 + t % S::KP, y = ky0 + t / S::KP;
+            cd[k] = d.pcd[(uint32_t)(min(y, d.H - 1) * W + min(x, W - 1))];
+            if (x >= W || y >= d.H) cd[k].x = -1.0;
+        }
     }
 
     // ---- consume
@@ -274,23 +311,25 @@ __device__ __forceinline__ Best gather(const JobDev &d, int px, int py, const Re
     for (int k = 0; k < NIT; ++k) {
         const int t = tid + k * T;
         if ((k + 1) * T <= S::n || t < S::n) {
-            const bool in = in_img(d, ox + t % S::pitch, oy + t / S::pitch);
-            const uint32_t w = in ? im[k] : kStateOut;
-            L.img[t] = w;
-            L.grad[t] = gr[k];
-            L.conf[t] = state_of(w) == 0 ? c[k] : 0.0;
+            const int li = (t / S::cols) * S::pitch + t % S::cols;
+            L.img[li] = im[k];
+            L.grad[li] = gr[k];
+            L.conf[li] = state_of(im[k]) == 0 ? c[k] : 0.0;
         }
     }
+    // pixels outside the window keep their keys (those in it are filled, off
+    // the front or evaluated again)
+    const uint32_t vx0 = g.wx0 - kx0, vy0 = g.wy0 - ky0, vw = g.wx1 - g.wx0, vh = g.wy1 - g.wy0;
 #pragma unroll
     for (int k = 0; k < KIT; ++k) {
         const int t = tid + k * T;
         if ((k + 1) * T <= S::KP * S::KP || t < S::KP * S::KP) {
-            const int col = t % S::KP, row = t / S::KP, x = kx0 + col, y = ky0 + row;
-            const bool in = x < W && y < d.H && col < 8 * g.nabx && row < 8 * g.naby;
+            const int col = t % S::KP, row = t / S::KP;
+            const bool in = col < 8 * g.nabx && row < 8 * g.naby;
             const int64_t key = in ? key_of(cd[k]) : -1;
-            L.bkey[t] = key;
-            const bool win = x >= g.wx0 && x < g.wx1 && y >= g.wy0 && y < g.wy1;
-            if (!win) take(best, key, (uint32_t)(y * W + x));
+            L.bkey[row * S::BP + col] = key;
+            if ((uint32_t)col - vx0 >= vw || (uint32_t)row - vy0 >= vh)
+                take(best, key, (uint32_t)((ky0 + row) * W + kx0 + col));
         }
     }
     return best;
@@ -306,9 +345,9 @@ struct FillSlots {
 // hole and the front, in device memory and LDS; their colours follow with
 // copy_colours.  keep(t): whether hole slot t is filled (INTERSECT scoring
 // fills only those whose source pixel qualifies).  L.cnt gets each wave's
-// count of filled slots, L.nfront is cleared.
+// count of filled slots.
 template <int R, class Keep>
-__device__ __forceinline__ FillSlots mark_filled(const JobDev &d, int px, int py, double C, const Refresh &g,
+__device__ __forceinline__ FillSlots mark_filled(int tid, const JobDev &d, int px, int py, double C, const Refresh &g,
                                                  CommitLds<R> &L, Keep keep) {
     using S = Stage<R>;
     constexpr int P = S::P;
@@ -318,7 +357,7 @@ __device__ __forceinline__ FillSlots mark_filled(const JobDev &d, int px, int py
     for (int j = 0; j < kSlots; ++j) {
         f.fill[j] = false;
         if (j * kCommitThreads >= P * P) continue;
-        const int t = threadIdx.x + j * kCommitThreads;
+        const int t = tid + j * kCommitThreads;
         const int dx = t % P - R, dy = t / P - R, li = S::at(dx, dy);
         if (t < P * P && (L.img[li] & kStateHole) && keep(t)) {
             f.fill[j] = true;
@@ -329,12 +368,11 @@ __device__ __forceinline__ FillSlots mark_filled(const JobDev &d, int px, int py
             d.pcd[dst] = make_double2(-1.0, 0.0);
             L.img[li] = 0;
             L.conf[li] = C;
-            L.bkey[(y - 8 * g.aby0) * S::KP + (x - 8 * g.abx0)] = -1;
+            L.bkey[(y - 8 * g.aby0) * S::BP + (x - 8 * g.abx0)] = -1;
         }
         n += __popcll(__ballot(f.fill[j]));
     }
-    if ((threadIdx.x & 63) == 0) L.cnt[threadIdx.x >> 6] = n;
-    if (threadIdx.x == 0) L.nfront = 0;
+    if ((tid & 63) == 0) L.cnt[tid >> 6] = n;
     return f;
 }
 
@@ -345,79 +383,96 @@ __device__ __forceinline__ int filled_count(const int *cnt) { return cnt[0] + cn
 // off the front already carry C = -1 in global memory and key -1 in LDS: a
 // hole pixel off the front has never been on it (the front only gains hole
 // pixels), a known one was set when it was filled or at initialisation.
-template <int R>
-__device__ __forceinline__ void list_front(CommitLds<R> &L) {
+//
+// PATCH: the target's whole patch counts as known, so the list does not wait
+// for mark_filled, which clears those pixels at the same time.
+template <int R, bool PATCH>
+__device__ __forceinline__ void list_front(int tid, CommitLds<R> &L) {
     using S = Stage<R>;
     constexpr int N = S::WIN * S::WIN;
 #pragma unroll
     for (int k = 0; k < (N + kCommitThreads - 1) / kCommitThreads; ++k) {
-        const int t = threadIdx.x + k * kCommitThreads;
-        const int li = S::at(min(t, N - 1) % S::WIN - S::reach, min(t, N - 1) / S::WIN - S::reach);
+        const int t = tid + k * kCommitThreads;
+        const int dx = min(t, N - 1) % S::WIN - S::reach, dy = min(t, N - 1) / S::WIN - S::reach, li = S::at(dx, dy);
         const uint32_t c = L.img[li], e = L.img[li + 1], w = L.img[li - 1], n = L.img[li - S::pitch],
                        s = L.img[li + S::pitch];
-        const bool on = t < N && state_of(c) == 1 &&
-                        (state_of(e) == 0 || state_of(w) == 0 || state_of(n) == 0 || state_of(s) == 0);
+        bool on = t < N && state_of(c) == 1;
+        if (PATCH) {
+            const uint32_t ux = dx + R, uy = dy + R;   // 0 .. 2R inside the patch
+            const bool cx = ux <= 2 * R, cy = uy <= 2 * R;
+            const auto known = [](uint32_t v, bool in_patch) { return in_patch ? state_of(v) != 2 : state_of(v) == 0; };
+            on = on && !(cx && cy) &&
+                 (known(e, ux + 1 <= 2 * R && cy) || known(w, ux - 1 <= 2 * R && cy) || known(n, cx && uy - 1 <= 2 * R) ||
+                  known(s, cx && uy + 1 <= 2 * R));
+        } else {
+            on = on && (state_of(e) == 0 || state_of(w) == 0 || state_of(n) == 0 || state_of(s) == 0);
+        }
         const uint64_t b = __ballot(on);
         if (b == 0) continue;
         int at = 0;
-        if ((threadIdx.x & 63) == 0) at = atomicAdd(&L.nfront, (int)__popcll(b));
+        if ((tid & 63) == 0) at = atomicAdd(&L.nfront, (int)__popcll(b));
         at = __builtin_amdgcn_readfirstlane(at);
-        if (on) L.front[at + __popcll(b & ((1ull << (threadIdx.x & 63)) - 1))] = (int16_t)t;
+        if (on) L.front[at + __popcll(b & ((1ull << (tid & 63)) - 1))] = (int16_t)t;
     }
 }
 
 // Confidence term of each listed front pixel (Eq. 2): the sum of C over the
 // known pixels of its patch in raster order of the offsets (unknown ones add
 // +0.0, which leaves the running sum bit-identical), over the constant patch
-// area.  One pixel per lane, rows read one ahead of the adds.
+// area.  One pixel per lane.
 template <int R>
-__device__ __forceinline__ void confidence_terms(CommitLds<R> &L) {
+__device__ __forceinline__ void confidence_terms(int tid, CommitLds<R> &L) {
     using S = Stage<R>;
     constexpr int P = S::P;
     const int nf = L.nfront;
-    for (int f = threadIdx.x; f < nf; f += kCommitThreads) {
+    for (int f = tid; f < nf; f += kCommitThreads) {
         const int wi = L.front[f];
         const double *cf = &L.conf[S::at(wi % S::WIN - S::reach - R, wi / S::WIN - S::reach - R)];
-        double c0[P], c1[P];
-#pragma unroll
-        for (int dx = 0; dx < P; ++dx) c0[dx] = cf[dx];
         double sum = 0.0;
+        // (a few rows of loads in flight; P is odd, so the rounds end with single rows)
+        constexpr int RB = P <= 9 ? 3 : 2;
 #pragma unroll 1
-        for (int dy = 0; dy < P; ++dy) {
-            // (the row after the last one is still inside the staged square)
+        for (int dy = 0; dy + RB <= P; dy += RB) {
+            double v[RB][P];
 #pragma unroll
-            for (int dx = 0; dx < P; ++dx) c1[dx] = cf[(dy + 1) * S::pitch + dx];
+            for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int dx = 0; dx < P; ++dx) sum = sum + c0[dx];
+                for (int dx = 0; dx < P; ++dx) v[r][dx] = cf[(dy + r) * S::pitch + dx];
 #pragma unroll
-            for (int dx = 0; dx < P; ++dx) c0[dx] = c1[dx];
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int dx = 0; dx < P; ++dx) sum = sum + v[r][dx];
         }
+#pragma unroll
+        for (int dy = P / RB * RB; dy < P; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < P; ++dx) sum = sum + cf[dy * S::pitch + dx];
         L.fC[f] = sum / (double)(P * P);
     }
 }
 
 // Gray values of the patch and two pixels around it, before the copy.
 template <int R>
-__device__ __forceinline__ void stage_gray(CommitLds<R> &L) {
+__device__ __forceinline__ void stage_gray(int tid, CommitLds<R> &L) {
     using S = Stage<R>;
     constexpr int G = S::P + 4;
 #pragma unroll
     for (int k = 0; k < (G * G + kCommitThreads - 1) / kCommitThreads; ++k) {
-        const int t = threadIdx.x + k * kCommitThreads;
+        const int t = tid + k * kCommitThreads;
         if (t < G * G) L.gray[t] = (uint8_t)gray_of(L.img[S::at(t % G - R - 2, t / G - R - 2)]);
     }
 }
 
 // Copies the source patch's colours into the filled slots.
 template <int R>
-__device__ __forceinline__ void copy_colours(const JobDev &d, int px, int py, int qx, int qy, const FillSlots &f,
+__device__ __forceinline__ void copy_colours(int tid, const JobDev &d, int px, int py, int qx, int qy, const FillSlots &f,
                                              CommitLds<R> &L) {
     using S = Stage<R>;
     constexpr int P = S::P, G = P + 4;
 #pragma unroll
     for (int j = 0; j < kSlots; ++j) {
         if (j * kCommitThreads >= P * P) continue;
-        const int t = threadIdx.x + j * kCommitThreads;
+        const int t = tid + j * kCommitThreads;
         if (f.fill[j]) {
             const int dx = t % P - R, dy = t / P - R;
             const uint32_t pix = d.img[(uint32_t)((qy + dy) * d.W + (qx + dx))];
@@ -430,12 +485,12 @@ __device__ __forceinline__ void copy_colours(const JobDev &d, int px, int py, in
 
 // Gradients the copy changed: those within one pixel of the patch.
 template <int R>
-__device__ __forceinline__ void refresh_grads(const JobDev &d, int px, int py, CommitLds<R> &L) {
+__device__ __forceinline__ void refresh_grads(int tid, const JobDev &d, int px, int py, CommitLds<R> &L) {
     using S = Stage<R>;
     constexpr int Q = S::P + 2, G = S::P + 4;
 #pragma unroll
     for (int k = 0; k < (Q * Q + kCommitThreads - 1) / kCommitThreads; ++k) {
-        const int t = threadIdx.x + k * kCommitThreads;
+        const int t = tid + k * kCommitThreads;
         if (t < Q * Q) {
             const int dx = t % Q - R - 1, dy = t / Q - R - 1, li = S::at(dx, dy);
             const uint8_t *gp = &L.gray[(dy + R + 2) * G + (dx + R + 2)];
@@ -460,52 +515,39 @@ __device__ __forceinline__ double data_term(uint32_t grad, int nx, int ny, doubl
 }
 
 // New terms of the listed front pixels, four lanes per pixel: each lane
-// searches a quarter of the patch rows for the largest gradient, the quarters
-// combine in row order (a later one wins only when strictly larger: first in
+// searches a quarter of the patch rows for the largest gradient (first in
 // raster order on ties).  Terms go to global memory and the touched blocks'
 // keys; each wave leaves its best pixel in L.fk[1] / fi[1] / wC / wD.
 template <int R>
-__device__ __forceinline__ void data_terms(const JobDev &d, int px, int py, const Refresh &g, CommitLds<R> &L) {
+__device__ __forceinline__ void data_terms(int tid, const JobDev &d, int px, int py, const Refresh &g, CommitLds<R> &L) {
     using S = Stage<R>;
     constexpr int P = S::P;
-    const int part = threadIdx.x & 3, nf = L.nfront;
+    const int part = tid & 3, nf = L.nfront;
     Best best = no_best();
     double bC = 0.0, bD = 0.0;
     const int y0 = part * P / 4, y1 = (part + 1) * P / 4;
     // (every lane of a wave takes every round: the quarters combine across lanes)
-    for (int f0 = (threadIdx.x >> 6) * 16; f0 < nf; f0 += kCommitThreads / 4) {
-        const int f = f0 + ((threadIdx.x & 63) >> 2);
+    for (int f0 = (tid >> 6) * 16; f0 < nf; f0 += kCommitThreads / 4) {
+        const int f = f0 + ((tid & 63) >> 2);
         const bool on = f < nf;
         const int wi = on ? L.front[f] : 0;
         const int wx = wi % S::WIN - S::reach, wy = wi / S::WIN - S::reach;
-        uint32_t bg = 0;
-        int b = -1;
+        // size << 9 | (511 - position): the larger gradient, the earlier
+        // position on ties.  Rows past the lane's quarter repeat its last one.
+        uint32_t b = 0;
         const uint32_t *gp = &L.grad[S::at(wx - R, wy - R)];
 #pragma unroll
         for (int r = 0; r < (P + 3) / 4; ++r) {
-            const int dy = min(y0 + r, P - 1);
-            if (y0 + r >= y1) continue;
+            const int dy = max(min(y0 + r, y1 - 1), 0);
+            const uint32_t *row = gp + dy * S::pitch;
+            const uint32_t at = 511 - dy * P;
 #pragma unroll
-            for (int dx = 0; dx < P; ++dx) {
-                const uint32_t v = gp[dy * S::pitch + dx];
-                const int m = grad_size(v);
-                bg = m > b ? v : bg;
-                b = m > b ? m : b;
-            }
+            for (int dx = 0; dx < P; ++dx) b = max(b, (uint32_t)grad_size(row[dx]) << 9 | (at - dx));
         }
-        // lanes 4 q + 1, + 2 and + 3 onto lane 4 q (quad permutes)
-        const auto merge = [&](int ob, uint32_t og) {
-            bg = ob > b ? og : bg;
-            b = ob > b ? ob : b;
-        };
-        const int b1 = __builtin_amdgcn_mov_dpp(b, 0x55, 0xf, 0xf, true), b2 = __builtin_amdgcn_mov_dpp(b, 0xaa, 0xf, 0xf, true),
-                  b3 = __builtin_amdgcn_mov_dpp(b, 0xff, 0xf, 0xf, true);
-        const uint32_t g1 = __builtin_amdgcn_mov_dpp((int)bg, 0x55, 0xf, 0xf, true),
-                       g2 = __builtin_amdgcn_mov_dpp((int)bg, 0xaa, 0xf, 0xf, true),
-                       g3 = __builtin_amdgcn_mov_dpp((int)bg, 0xff, 0xf, 0xf, true);
-        merge(b1, g1);
-        merge(b2, g2);
-        merge(b3, g3);
+        b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0xb1, 0xf, 0xf, true));   // quad lanes 1, 0, 3, 2
+        b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x4e, 0xf, 0xf, true));   // 2, 3, 0, 1
+        const int best_at = 511 - (int)(b & 511);
+        const uint32_t bg = gp[best_at / P * S::pitch + best_at % P];
         if (on && part == 0) {
             const int li = S::at(wx, wy);
             const int nx = (state_of(L.img[li + 1]) != 0) - (state_of(L.img[li - 1]) != 0);
@@ -515,7 +557,7 @@ __device__ __forceinline__ void data_terms(const JobDev &d, int px, int py, cons
             const uint32_t idx = (uint32_t)(y * d.W + x);
             d.pcd[idx] = make_double2(C, D);
             const int64_t key = __double_as_longlong(C * D);
-            L.bkey[(y - 8 * g.aby0) * S::KP + (x - 8 * g.abx0)] = key;
+            L.bkey[(y - 8 * g.aby0) * S::BP + (x - 8 * g.abx0)] = key;
             if (better(key, idx, best.key, best.idx)) {
                 best = {key, idx};
                 bC = C;
@@ -524,8 +566,8 @@ __device__ __forceinline__ void data_terms(const JobDev &d, int px, int py, cons
         }
     }
     const Best w = wave_best(best);
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
+    const int wave = tid >> 6;
+    if ((tid & 63) == 0) {
         L.fk[1][wave] = w.key;
         L.fi[1][wave] = w.idx;
     }
@@ -540,6 +582,7 @@ __device__ __forceinline__ void data_terms(const JobDev &d, int px, int py, cons
 template <int R>
 __device__ __forceinline__ void post_best(CommitLds<R> &L, Best b) {
     b = wave_best(b);
+    if (threadIdx.x == 0) L.nfront = 0;   // (for the list that follows the barrier)
     if ((threadIdx.x & 63) == 0) {
         L.fk[0][threadIdx.x >> 6] = b.key;
         L.fi[0][threadIdx.x >> 6] = b.idx;
@@ -565,21 +608,23 @@ __device__ __forceinline__ Best posted_best(const CommitLds<R> &L, int set, int 
 // committer runs it while the next search is under way.  16 threads per
 // block, 4 keys each; then wave w folds the w-th touched superblock.
 template <int R>
-__device__ __forceinline__ void update_blocks(const JobDev &d, const Refresh &g, CommitLds<R> &L, BlockBest *sup) {
+__device__ __forceinline__ void update_blocks(int tid, const JobDev &d, const Refresh &g, CommitLds<R> &L, BlockBest *sup) {
     using S = Stage<R>;
     constexpr int NB = S::NBA * S::NBA;
-    const int sub = threadIdx.x & 15;
+    const int sub = tid & 15;
 #pragma unroll
     for (int b0 = 0; b0 < NB; b0 += kCommitThreads >> 4) {
-        const int b = b0 + (threadIdx.x >> 4), bc = b % S::NBA, br = b / S::NBA;
+        const int b = b0 + (tid >> 4), bc = b % S::NBA, br = b / S::NBA;
         const bool live = b < NB && bc < g.nabx && br < g.naby;
-        Best best = no_best();
-        if (live) {
+        const int64_t *kp = &L.bkey[(8 * min(br, S::NBA - 1) + (sub >> 3)) * S::BP + 8 * bc + (sub & 7)];   // rows + 0, 2, 4, 6
+        const uint32_t i0 = (uint32_t)((8 * (g.aby0 + br) + (sub >> 3)) * d.W + 8 * (g.abx0 + bc) + (sub & 7));
+        Best best = {kp[0], i0};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int e = sub + 16 * j, col = 8 * bc + (e & 7), row = 8 * br + (e >> 3);
-                take(best, L.bkey[row * S::KP + col], (uint32_t)((8 * g.aby0 + row) * d.W + 8 * g.abx0 + col));
-            }
+        for (int j = 1; j < 4; ++j) {
+            // (indices rise with j, so an equal key keeps the earlier one)
+            const int64_t key = kp[2 * j * S::BP];
+            best.idx = key > best.key ? i0 + (uint32_t)(2 * j * d.W) : best.idx;
+            best.key = key > best.key ? key : best.key;
         }
         // the block's 16 threads are one DPP row: lane 15 ends with the maximum
         const uint64_t e = (uint64_t)(best.key + 1);
@@ -599,7 +644,7 @@ __device__ __forceinline__ void update_blocks(const JobDev &d, const Refresh &g,
         }
     }
     lds_barrier();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = tid >> 6, lane = tid & 63;
     const int sx = g.sx0 + (wave & 1), sy = g.sy0 + (wave >> 1);
     if (sx > g.sx1 || sy > g.sy1) return;   // (uniform over the wave)
     Best b = no_best();
@@ -627,13 +672,13 @@ struct PatchWords {
     uint32_t w[kSlots];
 };
 template <int R>
-__device__ __forceinline__ PatchWords load_patch(const JobDev &d, int tx, int ty) {
+__device__ __forceinline__ PatchWords load_patch(int tid, const JobDev &d, int tx, int ty) {
     constexpr int P = 2 * R + 1;
     PatchWords f{};
 #pragma unroll
     for (int j = 0; j < kSlots; ++j) {
         if (j * kCommitThreads >= P * P) continue;
-        const int t = min((int)threadIdx.x + j * kCommitThreads, P * P - 1);
+        const int t = min(tid + j * kCommitThreads, P * P - 1);
         const int x = tx + t / P - R, y = ty + t % P - R;
         const uint32_t w = d.img[(uint32_t)(min(max(y, 0), d.H - 1) * d.W + min(max(x, 0), d.W - 1))];
         f.w[j] = in_img(d, x, y) ? w : kStateOut;

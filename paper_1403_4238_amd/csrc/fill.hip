@@ -561,7 +561,7 @@ __device__ void add_filled_sources(const JobDev &d, const CommitLds<R> &L, int p
 // target.  With no staged target (right after create) it only selects and
 // stages.
 template <int R, bool ISECT = false>
-__device__ void commit_body(const JobDev &d, Scratch &s, CommitLds<R> &L, CommitNote *note) {
+__device__ __forceinline__ void commit_body(const JobDev &d, Scratch &s, CommitLds<R> &L, CommitNote *note) {
     using S = Stage<R>;
     constexpr int P = S::P, T = kCommitThreads;
     Snap v = load_snap(d.st);
@@ -575,14 +575,14 @@ __device__ void commit_body(const JobDev &d, Scratch &s, CommitLds<R> &L, Commit
     int px, py;
     raster.split(v.p, &px, &py);
     const Refresh g = refresh_geometry<R>(d, px, py);
-    const int known_k = d.tgt->k;
+    const int known_k = d.tgt->k, tid = threadIdx.x;
 
     // the search partials, eight loads in flight, with the gather's
     const int ntiles = d.ntx * d.nty;
     uint64_t pv[8], best = ~0ull;
 #pragma unroll
     for (int k = 0; k < 8; ++k) pv[k] = d.partials[min((int)threadIdx.x + k * T, ntiles - 1)];
-    post_best(L, gather<R>(d, px, py, g, d.sup, L));
+    post_best(L, gather<R>(tid, d, px, py, g, d.sup, L));
 #pragma unroll
     for (int k = 0; k < 8; ++k) best = pv[k] < best ? pv[k] : best;   // clamped repeats are harmless
     for (int t = threadIdx.x + 8 * T; t < ntiles; t += T) best = d.partials[t] < best ? d.partials[t] : best;
@@ -602,25 +602,26 @@ __device__ void commit_body(const JobDev &d, Scratch &s, CommitLds<R> &L, Commit
     const uint32_t fidx = far.key >= 0 ? far.idx : v.p;
     int fx, fy;
     raster.split(fidx, &fx, &fy);
-    const PatchWords fw = load_patch<R>(d, fx, fy);
+    const PatchWords fw = load_patch<R>(tid, d, fx, fy);
     const double2 fcd = d.pcd[fidx];
 
     const uint32_t q = (uint32_t)best;
     int qx, qy;
     raster.split(q, &qx, &qy);
-    const FillSlots fs = mark_filled<R>(d, px, py, v.C, g, L, [&](int t) {
+    const FillSlots fs = mark_filled<R>(tid, d, px, py, v.C, g, L, [&](int t) {
         // INTERSECT: the flag byte of the source word, read before any of
         // this copy's writes (the padded plane covers R pixels around the image)
         return !ISECT || (d.srcp[(int64_t)(qy + t / P - R + kPadT) * d.pitch + (qx + t % P - R + kPadL)] >> 24) != 0;
     });
-    stage_gray<R>(L);
+    stage_gray<R>(tid, L);
+    if (!ISECT) list_front<R, true>(tid, L);
     lds_barrier();
-    copy_colours<R>(d, px, py, qx, qy, fs, L);
+    copy_colours<R>(tid, d, px, py, qx, qy, fs, L);
     const int filled = filled_count(L.cnt);
-    list_front<R>(L);
+    if (ISECT) list_front<R, false>(tid, L);
     lds_barrier();
-    refresh_grads<R>(d, px, py, L);
-    confidence_terms<R>(L);
+    refresh_grads<R>(tid, d, px, py, L);
+    confidence_terms<R>(tid, L);
     const int64_t remaining = v.remaining - filled;
     if (threadIdx.x == 0) {
         if (note) {
@@ -647,7 +648,7 @@ __device__ void commit_body(const JobDev &d, Scratch &s, CommitLds<R> &L, Commit
     }
     if (remaining == 0) return;
     lds_barrier();
-    data_terms<R>(d, px, py, g, L);
+    data_terms<R>(tid, d, px, py, g, L);
     lds_barrier();
     int wv;
     const Best near = posted_best(L, 1, &wv);
@@ -675,7 +676,7 @@ __device__ void commit_body(const JobDev &d, Scratch &s, CommitLds<R> &L, Commit
         st->Pr = C * D;
         st->pending = 1;
     }
-    update_blocks<R>(d, g, L, nullptr);
+    update_blocks<R>(tid, d, g, L, nullptr);
 }
 
 // ---- persistent fill: one dispatch runs many iterations ------------------
@@ -729,21 +730,26 @@ __device__ __forceinline__ uint64_t slot_word(uint64_t key, uint32_t tag) {
 // invalidation).
 template <int R>
 __device__ __forceinline__ void collect_slots(const uint64_t *fs, int ntiles, uint32_t tag, CommitLds<R> &L) {
-    constexpr int T = kCommitThreads;
-    uint64_t best;
-    bool pend = true;
+    // The first wave sums confidences meanwhile.
+    constexpr int T = kCommitThreads - 64, U = 4;
+    uint64_t best = ~0ull;
+    bool pend = false;
     // Each thread polls its own slots (no barrier per round), so the last
-    // report is seen one load latency after it lands; two loads in flight
-    // cover the resident tiles of a single image.
-    for (uint32_t spin = 0; spin < kSpinLimit; ++spin) {
+    // report is seen one load latency after it lands; U loads in flight cover
+    // the resident tiles of a single image.
+    for (uint32_t spin = 0; threadIdx.x >= 64 && spin < kSpinLimit; ++spin) {
         best = ~0ull;
         pend = false;
-        for (int t = threadIdx.x; t < ntiles; t += 2 * T) {
-            const uint64_t w0 = __hip_atomic_load(&fs[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t w1 = __hip_atomic_load(&fs[t + T < ntiles ? t + T : t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            pend |= (w0 & 255u) != tag || (w1 & 255u) != tag;
-            best = (w0 >> 8) < best ? (w0 >> 8) : best;
-            best = (w1 >> 8) < best ? (w1 >> 8) : best;
+        for (int t = (int)threadIdx.x - 64; t < ntiles; t += U * T) {
+            uint64_t w[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                w[u] = __hip_atomic_load(&fs[t + u * T < ntiles ? t + u * T : t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                pend |= (w[u] & 255u) != tag;
+                best = (w[u] >> 8) < best ? (w[u] >> 8) : best;
+            }
         }
         if (!pend) break;
         __builtin_amdgcn_s_sleep(1);
@@ -776,12 +782,12 @@ struct FillCommitLds {
 // copy the colours, and choose and stage the next target.  The loop state
 // stays in registers, the same in every thread.
 template <int R>
-__device__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t epoch, FillCommitLds<R> &C) {
+__device__ __forceinline__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t epoch, FillCommitLds<R> &C) {
     using S = Stage<R>;
     constexpr int P = S::P, T = kCommitThreads;
     CommitLds<R> &L = C.c;
     FillSync *sy = d.sync;
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
     Snap v = load_snap(d.st);
     if (!v.done && !v.err && !v.pending) v.err = INPAINT_DEVICE;   // (create and import stage a target)
     const Raster raster(d.W);
@@ -803,15 +809,20 @@ __device__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t e
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    bool ran = false, stale = false;   // stale: the block maxima lag the last refresh
+    bool ran = false;
+    bool logged = false, stale = false;   // the log and the block maxima lag the last iteration
     Refresh g{};
     for (uint32_t k = 0;; ++k) {
+        tid = thread_number();
         // The words of a record say themselves which iteration they belong
         // to, so go needs no order after them.
         const bool stop = v.done || v.err || !v.pending || v.iter >= v.limit || (int)k >= n_iters;
         if (k == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the slot resets
         publish_go(sy, stop ? go_stop(epoch) : go_word(epoch, k + 1, rec_tag(v.iter)));
-        if (stale) update_blocks<R>(d, g, L, C.sup);
+        if (logged && tid >= T - 64 && tid < T - 64 + (int)sizeof(StepRec) / 4 && v.iter <= d.log_cap)
+            ((uint32_t *)&d.log[v.iter - 1])[tid - (T - 64)] = ((const uint32_t *)&C.last)[tid - (T - 64)];
+        logged = false;
+        if (stale) update_blocks<R>(tid, d, g, L, C.sup);
         stale = false;
         // every store of the last iteration is visible to the loads below
         __syncthreads();
@@ -822,7 +833,7 @@ __device__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t e
         px = __builtin_amdgcn_readfirstlane(px);
         py = __builtin_amdgcn_readfirstlane(py);
         g = refresh_geometry<R>(d, px, py);
-        post_best(L, gather<R>(d, px, py, g, C.sup, L));
+        post_best(L, gather<R>(tid, d, px, py, g, C.sup, L));
         lds_barrier();
         // the best pixel that keeps its priority: the usual next target when
         // that is far; its patch and terms are loaded while the search runs
@@ -830,17 +841,15 @@ __device__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t e
         const uint32_t fidx = far.key >= 0 ? far.idx : v.p;
         int fx, fy;
         raster.split(fidx, &fx, &fy);
-        const PatchWords fw = load_patch<R>(d, fx, fy);
+        const PatchWords fw = load_patch<R>(tid, d, fx, fy);
         const double2 fcd = d.pcd[fidx];
-        const FillSlots fs = mark_filled<R>(d, px, py, v.C, g, L, [](int) { return true; });
-        stage_gray<R>(L);
+        const FillSlots fs = mark_filled<R>(tid, d, px, py, v.C, g, L, [](int) { return true; });
+        stage_gray<R>(tid, L);
+        list_front<R, true>(tid, L);
         lds_barrier();
         const int filled = filled_count(L.cnt);
-        list_front<R>(L);
-        lds_barrier();
-        confidence_terms<R>(L);
-
-        collect_slots<R>(d.fslot, ntiles, slot_tag(k), L);
+        confidence_terms<R>(tid, L);   // (wave 0, unless the front is long)
+        collect_slots<R>(d.fslot, ntiles, slot_tag(k), L);   // (the other waves)
         lds_barrier();
         uint64_t best = ~0ull;
 #pragma unroll
@@ -853,10 +862,10 @@ __device__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t e
         if (v.err) continue;   // publishes stop
         int qx, qy;
         raster.split(q, &qx, &qy);
-        copy_colours<R>(d, px, py, qx, qy, fs, L);
+        copy_colours<R>(tid, d, px, py, qx, qy, fs, L);
         const int64_t remaining = v.remaining - filled;
-        if (tid == 0) {
-            StepRec rec;
+        if (tid == T - 64) {   // (the last wave has few slots to copy)
+            StepRec &rec = C.last;
             rec.target_index = v.p;
             rec.source_index = q;
             rec.ssd = ssd;
@@ -868,10 +877,8 @@ __device__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t e
             rec.confidence = v.C;
             rec.data_term = v.D;
             rec.remaining = remaining;
-            if (v.iter < d.log_cap) d.log[v.iter] = rec;
-            C.last = rec;
         }
-        ran = true;
+        ran = logged = true;
         v.iter += 1;
         v.remaining = remaining;
         v.pending = 0;
@@ -880,9 +887,9 @@ __device__ void fill_commit(const JobDev &d, int ntiles, int n_iters, uint32_t e
             continue;
         }
         lds_barrier();
-        refresh_grads<R>(d, px, py, L);
+        refresh_grads<R>(tid, d, px, py, L);
         lds_barrier();
-        data_terms<R>(d, px, py, g, L);
+        data_terms<R>(tid, d, px, py, g, L);
         lds_barrier();
         stale = true;
         int wv;
@@ -1001,6 +1008,39 @@ __device__ __forceinline__ void build_target(const RecWords<R> &rw, tile::Target
     __syncthreads();
 }
 
+// A SIMT search group's wait for iteration k (whole group): one lane polls
+// the go word, then every thread reads its words until they are fresh.  (Up to
+// four such groups share a CU, a thousand the device: polling whole records
+// slows the committer's own loads more than the round trip it saves.)  False
+// on stop or time-out.
+template <int R>
+__device__ __forceinline__ bool wait_go(const FillRec *rec, uint32_t epoch, uint32_t k, bool words, RecWords<R> &rw,
+                                        int32_t *flag, uint32_t *tag) {
+    if (threadIdx.x == 0) {
+        int f = 0;
+        for (uint32_t spin = 0; spin < kSpinLimit; ++spin) {
+            const uint64_t v = __hip_atomic_load(&rec->go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (go_is(v, epoch, k + 1)) {
+                *tag = go_tag(v);
+                f = 1;
+                break;
+            }
+            if (v == go_stop(epoch)) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        *flag = f;
+    }
+    __syncthreads();
+    if (!*flag) return false;
+    const uint32_t want = *tag;
+    bool ok = !words;
+    for (uint32_t spin = 0; !ok && spin < kSpinLimit; ++spin) {
+        rw.load(rec);
+        ok = rw.fresh(want);
+    }
+    return !words || __syncthreads_and(ok);
+}
+
 // A search group's wait for iteration k (whole group): each poll reads the go
 // word (thread 0) and the record's words together, so the target arrives with
 // the go word instead of one memory round trip after it; stale words are read
@@ -1047,7 +1087,7 @@ union FillLds {
 };
 
 template <int R, int NY>
-__device__ void fill_search(const JobDev &d, int ntiles, uint32_t epoch, SearchLds<R, NY> &S) {
+__device__ __forceinline__ void fill_search(const JobDev &d, int ntiles, uint32_t epoch, SearchLds<R, NY> &S) {
     // The tile stays in this group's LDS for the whole dispatch, so the
     // order of tiles over the XCDs does not matter here.
     const int t = (int)blockIdx.x - 1;
@@ -1058,7 +1098,7 @@ __device__ void fill_search(const JobDev &d, int ntiles, uint32_t epoch, SearchL
     const FillRec *rec = &d.sync->rec[t % kGoCopies];
     for (uint32_t k = 0;; ++k) {
         RecWords<R> rw;
-        if (!wait_target<R>(rec, epoch, k, anyv, rw, &S.flag, &S.tag)) break;
+        if (!wait_go<R>(rec, epoch, k, anyv, rw, &S.flag, &S.tag)) break;
         uint64_t best = ~0ull;
         if (anyv) {
             build_target<R>(rw, &S.tgt, S.t2p);
@@ -1075,31 +1115,36 @@ __device__ void fill_search(const JobDev &d, int ntiles, uint32_t epoch, SearchL
     }
 }
 
-template <int R>
+// Search tiles a group of the batched MFMA dispatch keeps in LDS: with two
+// groups per CU, two tiles of every radius fit beside the tables.
+constexpr int kMultiTiles = 2;
+
+template <int R, int NT = 1>
 struct SearchLdsMfma {
-    mtile::MfmaTile<R> tile;
+    mtile::MfmaTile<R> tile[NT];
     mtile::FragTables<R> ft;
     uint64_t red[kSearchWaves];
     int32_t flag;
     uint32_t tag;
 };
 
-template <int R>
+template <int R, int NT = 1>
 union FillLdsMfma {
     FillCommitLds<R> c;
-    SearchLdsMfma<R> s;
+    SearchLdsMfma<R, NT> s;
 };
+static_assert(sizeof(FillLdsMfma<kMfmaMaxRadius, kMultiTiles>) + 256 <= 80 * 1024, "two work-groups per CU");
 
 // Search group of the MFMA form: one 64 x 64 tile of the MFMA tiling, staged
 // once; per target it builds the B-operand tables in LDS from the record and
 // scores the tile on the matrix cores.
 template <int R>
-__device__ void fill_search_mfma(const JobDev &d, uint32_t epoch, SearchLdsMfma<R> &S) {
+__device__ __forceinline__ void fill_search_mfma(const JobDev &d, uint32_t epoch, SearchLdsMfma<R> &S) {
     const int t = (int)blockIdx.x - 1;
     int tx0, ty0;
     mtile::tile_origin<R>(d.rx0, d.ry0, d.ntx, t, &tx0, &ty0);
     mtile::clear_tables<R>(&S.ft);
-    const uint32_t vmask = mtile::stage_tile<R>(d, tx0, ty0, d.rx0, d.rx1, d.ry1, S.tile);
+    const uint32_t vmask = mtile::stage_tile<R>(d, tx0, ty0, d.rx0, d.rx1, d.ry1, S.tile[0]);
     const bool anyv = __syncthreads_or(vmask != 0);
     const FillRec *rec = &d.sync->rec[t % kGoCopies];
     for (uint32_t k = 0;; ++k) {
@@ -1111,7 +1156,7 @@ __device__ void fill_search_mfma(const JobDev &d, uint32_t epoch, SearchLdsMfma<
             mtile::build_tables<R>(
                 &S.ft, [&](int, int j) { return rw.w[j]; }, [&](int, int j) { return rw.known(j); });
             __syncthreads();
-            best = tile::wave_min_u64(mtile::score_tile_rows<R>(d, &S.ft, tx0, ty0, vmask, S.tile));
+            best = tile::wave_min_u64(mtile::score_tile_rows<R>(d, &S.ft, tx0, ty0, vmask, S.tile[0]));
             if ((threadIdx.x & 63) == 0) S.red[threadIdx.x >> 6] = best;
             __syncthreads();
             if (threadIdx.x == 0)
@@ -1212,53 +1257,68 @@ __device__ __forceinline__ bool read_record(const FillRec *rec, uint32_t tag, Re
     return false;
 }
 
-// Scores item (job d, tile t) for iteration k of the MFMA form and reports
-// in the job's slot word.  restage: the tile in LDS is not this item's.
+// What a search group does with one item (job d, tile t) for iteration k.
+struct ServeItem {
+    int t;
+    uint32_t k, tag;   // the job's iteration and the record tag its go word carried
+    int at;            // LDS tile to use
+    bool restage;      // that tile is not this item's
+    bool build;        // the target's tables in LDS are not this job's for iteration k
+};
+
+// Scores an item of the MFMA form and reports in the job's slot word.  True
+// when the target tables are now the job's of iteration k.
 template <int R>
-__device__ __forceinline__ void multi_serve_mfma(const JobDev &d, int t, uint32_t k, uint32_t tag, bool restage,
-                                                 SearchLdsMfma<R> &S, uint32_t &vmask, bool &anyv) {
+__device__ __forceinline__ bool multi_serve_mfma(const JobDev &d, const ServeItem &it, SearchLdsMfma<R, kMultiTiles> &S,
+                                                 uint32_t &vmask, bool &anyv) {
     int tx0, ty0;
-    mtile::tile_origin<R>(d.rx0, d.ry0, d.ntx, t, &tx0, &ty0);
-    if (restage) {
-        vmask = mtile::stage_tile<R>(d, tx0, ty0, d.rx0, d.rx1, d.ry1, S.tile);
+    mtile::tile_origin<R>(d.rx0, d.ry0, d.ntx, it.t, &tx0, &ty0);
+    mtile::MfmaTile<R> &tile = S.tile[it.at];
+    if (it.restage) {
+        vmask = mtile::stage_tile<R>(d, tx0, ty0, d.rx0, d.rx1, d.ry1, tile);
         anyv = __syncthreads_or(vmask != 0);
     }
-    uint64_t best = ~0ull;
-    if (anyv) {
+    if (it.build && anyv) {
         // the record words of iteration k: read until every one carries the
         // go word's tag (bounded; on a time-out no slot word is written, and
         // the committer's bounded wait reports the device error)
         RecWords<R> rw;
-        if (!read_record<R>(&d.sync->rec[t % kGoCopies], tag, rw)) return;
+        if (!read_record<R>(&d.sync->rec[it.t % kGoCopies], it.tag, rw)) return false;
         mtile::build_tables<R>(
             &S.ft, [&](int, int j) { return rw.w[j]; }, [&](int, int j) { return rw.known(j); });
         __syncthreads();
-        best = tile::wave_min_u64(mtile::score_tile_rows<R>(d, &S.ft, tx0, ty0, vmask, S.tile));
+    }
+    uint64_t best = ~0ull;
+    if (anyv) {
+        best = tile::wave_min_u64(mtile::score_tile_rows<R>(d, &S.ft, tx0, ty0, vmask, tile));
         if ((threadIdx.x & 63) == 0) S.red[threadIdx.x >> 6] = best;
         __syncthreads();
         if (threadIdx.x == 0)
             for (int w = 0; w < kSearchWaves; ++w) best = S.red[w] < best ? S.red[w] : best;
     }
     if (threadIdx.x == 0)
-        __hip_atomic_store(&d.fslot[t], slot_word(best, slot_tag(k)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&d.fslot[it.t], slot_word(best, slot_tag(it.k)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return anyv || !it.build;
 }
 
 // The same for the SIMT form.
 template <int R>
-__device__ __forceinline__ void multi_serve_simt(const JobDev &d, int t, uint32_t k, uint32_t tag, bool restage,
-                                 SearchLds<R, kFillTileRows> &S, uint32_t &vmask, bool &anyv) {
+__device__ __forceinline__ bool multi_serve_simt(const JobDev &d, const ServeItem &it, SearchLds<R, kFillTileRows> &S,
+                                                 uint32_t &vmask, bool &anyv) {
     constexpr int NY = kFillTileRows;
     int tx0, ty0;
-    tile::tile_origin<R, NY>(d.rx0, d.ry0, d.ntx, t, &tx0, &ty0);
-    if (restage) {
+    tile::tile_origin<R, NY>(d.rx0, d.ry0, d.ntx, it.t, &tx0, &ty0);
+    if (it.restage) {
         vmask = tile::stage_tile<R, NY>(d, tx0, ty0, d.rx1, d.ry1, S.tile);
         anyv = __syncthreads_or(vmask != 0);
     }
+    if (it.build && anyv) {
+        RecWords<R> rw;
+        if (!read_record<R>(&d.sync->rec[it.t % kGoCopies], it.tag, rw)) return false;
+        build_target<R>(rw, &S.tgt, S.t2p);
+    }
     uint64_t best = ~0ull;
     if (anyv) {
-        RecWords<R> rw;
-        if (!read_record<R>(&d.sync->rec[t % kGoCopies], tag, rw)) return;
-        build_target<R>(rw, &S.tgt, S.t2p);
         const tile::LdsTarget view{&S.tgt};
         best = tile::wave_min_u64(tile::score_tile<R, NY>(d, view, tx0, ty0, vmask, S.tile));
         if ((threadIdx.x & 63) == 0) S.red[threadIdx.x >> 6] = best;
@@ -1267,12 +1327,16 @@ __device__ __forceinline__ void multi_serve_simt(const JobDev &d, int t, uint32_
             for (int w = 0; w < kSearchWaves; ++w) best = S.red[w] < best ? S.red[w] : best;
     }
     if (threadIdx.x == 0)
-        __hip_atomic_store(&d.fslot[t], slot_word(best, slot_tag(k)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&d.fslot[it.t], slot_word(best, slot_tag(it.k)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return anyv || !it.build;
 }
 
-// Search group w of a batched dispatch; serve(d, tile, k, tag, restage,
-// vmask, anyv) scores one item (tag: the record tag its go word carried).
-template <class Serve>
+// Search group w of a batched dispatch; serve(d, item, vmask, anyv) scores
+// one item.  Of NT LDS tiles, item i of a group with more than NT items uses
+// tile min(i, NT - 1): the first NT - 1 items stay in LDS for the whole
+// dispatch and the others take turns in the last tile (least-recently-used
+// tiles would all miss, as items come round in turn).
+template <int NT, class Serve>
 __device__ __forceinline__ void multi_search(const MultiPlan &m, int w, uint32_t epoch, MultiPick *pk, Serve serve) {
     const int i0 = m.first[w], ni = m.first[w + 1] - i0;   // 0 <= ni <= kMultiMaxItems (host-checked)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1287,14 +1351,18 @@ __device__ __forceinline__ void multi_search(const MultiPlan &m, int w, uint32_t
         my_go = &m.slots[my_slot].sync->rec[my_tile % kGoCopies].go;
         my_done = false;
     }
-    uint32_t vmask = 0;
-    bool anyv = false;
-    int staged = -1;   // item whose tile is in LDS
+    uint32_t vmask[NT] = {};
+    bool anyv[NT] = {};
+    int staged[NT];   // items whose tiles are in LDS
+#pragma unroll
+    for (int j = 0; j < NT; ++j) staged[j] = -1;
+    int built_slot = -1;   // the target tables in LDS are this job's
+    uint32_t built_k = 0;  // for this iteration
     int rot = 0;
     for (uint32_t spin = 0; spin < kSpinLimit;) {
         if (wave == 0) multi_poll(my_go, my_slot, my_tile, my_k, my_done, rot, epoch, pk);
         __syncthreads();
-        const int pick = pk->pick;
+        const int pick = __builtin_amdgcn_readfirstlane(pk->pick);
         if (pick < 0) {
             if (pk->all_done) break;
             ++spin;
@@ -1304,10 +1372,35 @@ __device__ __forceinline__ void multi_search(const MultiPlan &m, int w, uint32_t
         }
         spin = 0;
         rot = pick + 1 < ni ? pick + 1 : 0;
-        // (by value: the fields the search reads become scalar registers)
-        const JobDev d = m.slots[pk->slot];
-        serve(d, pk->tile, pk->k, pk->tag, staged != pick, vmask, anyv);
-        staged = pick;
+        // (uniform: the job's fields the search reads become scalar loads)
+        const int slot = __builtin_amdgcn_readfirstlane(pk->slot);
+        ServeItem it;
+        it.t = __builtin_amdgcn_readfirstlane(pk->tile);
+        it.k = (uint32_t)__builtin_amdgcn_readfirstlane((int)pk->k);
+        it.tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)pk->tag);
+        it.at = min(pick, NT - 1);
+        it.build = slot != built_slot || it.k != built_k;
+        uint32_t vm = 0;
+        bool av = false;
+        it.restage = true;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            if (j == it.at) {
+                it.restage = staged[j] != pick;
+                vm = vmask[j];
+                av = anyv[j];
+            }
+        const JobDev d = m.slots[slot];
+        const bool ok = serve(d, it, vm, av);
+        built_slot = ok ? slot : -1;
+        built_k = it.k;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+            if (j == it.at) {
+                staged[j] = pick;
+                vmask[j] = vm;
+                anyv[j] = av;
+            }
         __syncthreads();
     }
 }
@@ -1315,7 +1408,7 @@ __device__ __forceinline__ void multi_search(const MultiPlan &m, int w, uint32_t
 template <int R>
 __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_fill_multi_mfma(
     MultiPlan m, int n_iters, uint32_t epoch) {
-    __shared__ FillLdsMfma<R> lds;
+    __shared__ FillLdsMfma<R, kMultiTiles> lds;
     __shared__ MultiPick pk;
     if ((int)blockIdx.x < m.n_commit) {
         // by value: held through a reference to device memory, the job's
@@ -1325,9 +1418,9 @@ __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(
         return;
     }
     mtile::clear_tables<R>(&lds.s.ft);   // (published by the first poll's barrier)
-    multi_search(m, (int)blockIdx.x - m.n_commit, epoch, &pk,
-                 [&](const JobDev &d, int t, uint32_t k, uint32_t tag, bool restage, uint32_t &vmask, bool &anyv)
-                     __attribute__((always_inline)) { multi_serve_mfma<R>(d, t, k, tag, restage, lds.s, vmask, anyv); });
+    multi_search<kMultiTiles>(m, (int)blockIdx.x - m.n_commit, epoch, &pk,
+                              [&](const JobDev &d, const ServeItem &it, uint32_t &vmask, bool &anyv)
+                                  __attribute__((always_inline)) { return multi_serve_mfma<R>(d, it, lds.s, vmask, anyv); });
 }
 
 template <int R>
@@ -1340,11 +1433,9 @@ __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(
         fill_commit<R>(d, d.ntx * d.nty, n_iters, epoch, lds.c);
         return;
     }
-    multi_search(m, (int)blockIdx.x - m.n_commit, epoch, &pk,
-                 [&](const JobDev &d, int t, uint32_t k, uint32_t tag, bool restage, uint32_t &vmask, bool &anyv)
-                     __attribute__((always_inline)) {
-                     multi_serve_simt<R>(d, t, k, tag, restage, lds.s, vmask, anyv);
-                 });
+    multi_search<1>(m, (int)blockIdx.x - m.n_commit, epoch, &pk,
+                    [&](const JobDev &d, const ServeItem &it, uint32_t &vmask, bool &anyv)
+                        __attribute__((always_inline)) { return multi_serve_simt<R>(d, it, lds.s, vmask, anyv); });
 }
 
 // The MFMA form for jobs of several radii in one dispatch: the LDS of the
@@ -1353,16 +1444,16 @@ __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(
 // radius only), so every work-group runs the per-radius code of its own
 // radius for the whole dispatch.
 union MixLdsMfma {
-    FillLdsMfma<1> r1;
-    FillLdsMfma<2> r2;
-    FillLdsMfma<3> r3;
-    FillLdsMfma<4> r4;
-    FillLdsMfma<5> r5;
+    FillLdsMfma<1, kMultiTiles> r1;
+    FillLdsMfma<2, kMultiTiles> r2;
+    FillLdsMfma<3, kMultiTiles> r3;
+    FillLdsMfma<4, kMultiTiles> r4;
+    FillLdsMfma<5, kMultiTiles> r5;
 };
 static_assert(kMultiMixMaxR == 5, "MixLdsMfma holds radii 1..5");
 
 template <int R>
-__device__ __forceinline__ void mixed_role(const MultiPlan &m, int n_iters, uint32_t epoch, FillLdsMfma<R> &lds,
+__device__ __forceinline__ void mixed_role(const MultiPlan &m, int n_iters, uint32_t epoch, FillLdsMfma<R, kMultiTiles> &lds,
                                            MultiPick *pk) {
     if ((int)blockIdx.x < m.n_commit) {
         const JobDev d = m.slots[m.commit[blockIdx.x]];   // by value, see k_fill_multi_mfma
@@ -1370,9 +1461,9 @@ __device__ __forceinline__ void mixed_role(const MultiPlan &m, int n_iters, uint
         return;
     }
     mtile::clear_tables<R>(&lds.s.ft);   // (published by the first poll's barrier)
-    multi_search(m, (int)blockIdx.x - m.n_commit, epoch, pk,
-                 [&](const JobDev &d, int t, uint32_t k, uint32_t tag, bool restage, uint32_t &vmask, bool &anyv)
-                     __attribute__((always_inline)) { multi_serve_mfma<R>(d, t, k, tag, restage, lds.s, vmask, anyv); });
+    multi_search<kMultiTiles>(m, (int)blockIdx.x - m.n_commit, epoch, pk,
+                              [&](const JobDev &d, const ServeItem &it, uint32_t &vmask, bool &anyv)
+                                  __attribute__((always_inline)) { return multi_serve_mfma<R>(d, it, lds.s, vmask, anyv); });
 }
 
 #if INPAINT_FILL_PART == 3
