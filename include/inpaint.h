@@ -79,9 +79,11 @@ extern "C" {
 #define INPAINT_FORM_GRAPH  2    /* replay a hipGraph of iters_per_check      */
 #define INPAINT_FORM_PERSISTENT 3 /* one dispatch of iters_per_check, check  */
 
+/* AUTO: the matrix cores for whole-window scoring with tile_rows 0, at every
+ * radius, else the SIMT search.  Same results either way. */
 #define INPAINT_PATH_AUTO 0
 #define INPAINT_PATH_SIMT 1      /* integer dot-product SSD on the VALU      */
-#define INPAINT_PATH_MFMA 2      /* int8 matrix-core cross term (exact)      */
+#define INPAINT_PATH_MFMA 2      /* int8 matrix-core cross term (exact), r <= 6 */
 /* The SIMT search with no LDS staging: each lane reads its source words from
  * device memory through the vector caches, as the paper's kernel without
  * local memory does (Alg. 1, against the local-memory kernel of Alg. 2).

@@ -9,7 +9,7 @@
 // of barriers and memory round trips in it, not bandwidth: four waves issue
 // one vector instruction each per four cycles.  Hence the layout below: no
 // integer division by a run-time value, one 32-bit word per pixel for colour
-// and state, gradients kept in a plane instead of being formed again, and
+// and state, gradients kept instead of being formed again, and
 // the maxima of untouched priority blocks kept in superblocks.
 //
 // Priorities are binary64 and must match a plain sequential CPU evaluation
@@ -63,10 +63,15 @@ __device__ __forceinline__ int gray_of(uint32_t w) {
     return (int)((299 * (w & 255) + 587 * ((w >> 8) & 255) + 114 * ((w >> 16) & 255) + 500) / 1000);
 }
 
-// A gradient as the grad plane and the LDS copy hold it: gx in the low and gy
-// in the high 16 bits, 0 where the pixel or one of its four neighbours is not
-// known (a zero gradient and none give the same isophote).
+// A gradient as kept: gx in the low and gy in the high 16 bits, 0 where the
+// pixel or one of its four neighbours is not known (a zero gradient and none
+// give the same isophote).  In global memory a known pixel's gradient sits in
+// the priority terms' D, which only front pixels, never known ones, use.
 __device__ __forceinline__ uint32_t pack_grad(int gx, int gy) { return (uint32_t)(gx & 0xffff) | (uint32_t)gy << 16; }
+__device__ __forceinline__ uint32_t *grad_word(double2 *cd) { return (uint32_t *)&cd->y; }
+__device__ __forceinline__ double2 off_front(uint32_t grad) {
+    return make_double2(-1.0, __longlong_as_double((long long)grad));
+}
 typedef short short2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int grad_size(uint32_t g) {
     const short2_t v = __builtin_bit_cast(short2_t, g);
@@ -256,7 +261,7 @@ __device__ __forceinline__ Best gather(int tid, const JobDev &d, int px, int py,
                        ky0 + KR <= d.H;
     if (inner) {
         const int64_t o = (int64_t)oy * W + ox, ko = (int64_t)ky0 * W + kx0;
-        const uint32_t *pi = d.img + o, *pg = d.grad + o;
+        const uint32_t *pi = d.img + o, *pg = grad_word(d.pcd + o);
         const double *pc = d.conf + o;
         const double2 *pk = d.pcd + ko;
 #pragma unroll
@@ -265,7 +270,7 @@ __device__ __forceinline__ Best gather(int tid, const JobDev &d, int px, int py,
             const uint32_t i = (uint32_t)(t / S::cols) * (uint32_t)W + (uint32_t)(t % S::cols);
             im[k] = *(const uint32_t *)((const char *)pi + 4 * i);
             c[k] = *(const double *)((const char *)pc + 8 * i);
-            gr[k] = *(const uint32_t *)((const char *)pg + 4 * i);
+            gr[k] = *(const uint32_t *)((const char *)pg + 16 * i);
         }
 #pragma unroll
         for (int k = 0; k < KIT; ++k) {
@@ -279,7 +284,7 @@ __device__ __forceinline__ Best gather(int tid, const JobDev &d, int px, int py,
             const uint32_t i = (uint32_t)(min(max(ly, 0), d.H - 1) * W + min(max(lx, 0), W - 1));
             im[k] = in_img(d, lx, ly) ? d.img[i] : kStateOut;
             c[k] = d.conf[i];
-            gr[k] = d.grad[i];
+            gr[k] = *grad_word(d.pcd + i);
         }
 #pragma unroll
         for (int k = 0; k < KIT; ++k) {
@@ -313,7 +318,7 @@ __device__ __forceinline__ Best gather(int tid, const JobDev &d, int px, int py,
         if ((k + 1) * T <= S::n || t < S::n) {
             const int li = (t / S::cols) * S::pitch + t % S::cols;
             L.img[li] = im[k];
-            L.grad[li] = gr[k];
+            L.grad[li] = state_of(im[k]) == 0 ? gr[k] : 0u;
             L.conf[li] = state_of(im[k]) == 0 ? c[k] : 0.0;
         }
     }
@@ -365,7 +370,7 @@ __device__ __forceinline__ FillSlots mark_filled(int tid, const JobDev &d, int p
             const uint32_t dst = (uint32_t)(y * d.W + x);
             d.conf[dst] = C;
             d.hole[dst] = 0;
-            d.pcd[dst] = make_double2(-1.0, 0.0);
+            d.pcd[dst] = off_front(0);
             L.img[li] = 0;
             L.conf[li] = C;
             L.bkey[(y - 8 * g.aby0) * S::BP + (x - 8 * g.abx0)] = -1;
@@ -475,10 +480,12 @@ __device__ __forceinline__ void copy_colours(int tid, const JobDev &d, int px, i
         const int t = tid + j * kCommitThreads;
         if (f.fill[j]) {
             const int dx = t % P - R, dy = t / P - R;
-            const uint32_t pix = d.img[(uint32_t)((qy + dy) * d.W + (qx + dx))];
-            d.img[(uint32_t)((py + dy) * d.W + (px + dx))] = pix;
+            const uint32_t pix = d.img[(uint32_t)((qy + dy) * d.W + (qx + dx))], dst = (uint32_t)((py + dy) * d.W + (px + dx));
+            const uint8_t gv = (uint8_t)gray_of(pix);
+            d.img[dst] = pix;
+            d.gray[dst] = gv;
             L.img[S::at(dx, dy)] = pix;
-            L.gray[(dy + R + 2) * G + (dx + R + 2)] = (uint8_t)gray_of(pix);
+            L.gray[(dy + R + 2) * G + (dx + R + 2)] = gv;
         }
     }
 }
@@ -497,7 +504,7 @@ __device__ __forceinline__ void refresh_grads(int tid, const JobDev &d, int px, 
             const uint32_t any = (L.img[li] | L.img[li + 1] | L.img[li - 1] | L.img[li + S::pitch] | L.img[li - S::pitch]) >> 24;
             const uint32_t v = any == 0 ? pack_grad((int)gp[1] - (int)gp[-1], (int)gp[G] - (int)gp[-G]) : 0u;
             L.grad[li] = v;
-            if (in_img(d, px + dx, py + dy)) d.grad[(uint32_t)((py + dy) * d.W + (px + dx))] = v;
+            if (state_of(L.img[li]) == 0) *grad_word(d.pcd + (uint32_t)((py + dy) * d.W + (px + dx))) = v;
         }
     }
 }

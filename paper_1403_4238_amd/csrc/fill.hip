@@ -52,9 +52,9 @@ struct GlobalView {
     __device__ int grad(int x, int y, int *gx, int *gy) const {
         if (!known(x, y) || !known(x + 1, y) || !known(x - 1, y) || !known(x, y + 1) || !known(x, y - 1))
             return -1;
-        const uint32_t *p = d.img + (int64_t)y * d.W + x;
-        *gx = gray_of(p[1]) - gray_of(p[-1]);
-        *gy = gray_of(p[d.W]) - gray_of(p[-d.W]);
+        const uint8_t *p = d.gray + (int64_t)y * d.W + x;
+        *gx = (int)p[1] - (int)p[-1];
+        *gy = (int)p[d.W] - (int)p[-d.W];
         return *gx * *gx + *gy * *gy;
     }
 };
@@ -274,8 +274,8 @@ __global__ void k_init_info(InitInfo *info, uint32_t nonce) {
 
 __global__ void k_seal(InitInfo *info, uint32_t nonce) { info->seal = nonce; }
 
-// Initialisation: zero the hole pixels, RGBX image with the pixel state, hole
-// map, confidence 1 / 0, hole count and bounding box.
+// Initialisation: zero the hole pixels, RGBX image with the pixel state, integer
+// BT.601 gray, hole map, confidence 1 / 0, hole count and bounding box.
 __global__ __launch_bounds__(256) void k_init_pixels(JobDev d, const uint8_t *rgb, int ch,
                                                      const uint8_t *mask) {
     const int64_t n = (int64_t)d.W * d.H;
@@ -295,6 +295,7 @@ __global__ __launch_bounds__(256) void k_init_pixels(JobDev d, const uint8_t *rg
         const uint32_t R = h ? 0 : rgb[i * ch], G = h ? 0 : rgb[i * ch + 1],
                        B = h ? 0 : rgb[i * ch + 2];
         d.img[i] = R | (G << 8) | (B << 16) | (h ? kStateHole : 0u);
+        d.gray[i] = (uint8_t)gray_of(R | (G << 8) | (B << 16));
         d.hole[i] = h ? 1 : 0;
         d.hole0[i] = h ? 1 : 0;
         d.conf[i] = h ? 0.0 : 1.0;
@@ -336,8 +337,8 @@ __global__ __launch_bounds__(256) void k_import_check(JobDev d, const uint8_t *h
 }
 
 // Overlays a checked checkpoint on the original-hole pixels: those still in
-// its hole become hole again (zeroed), the others take its colour and its
-// confidence.  Other pixels keep their values.
+// its hole become hole again (zeroed), the others take its colour, the gray
+// value of that colour and its confidence.  Other pixels keep their values.
 __global__ __launch_bounds__(256) void k_import_apply(JobDev d, const uint8_t *rgb, int ch, const uint8_t *hole,
                                                       const double *conf) {
     const int64_t n = (int64_t)d.W * d.H;
@@ -349,6 +350,7 @@ __global__ __launch_bounds__(256) void k_import_apply(JobDev d, const uint8_t *r
         const bool h = hole[i] != 0;
         const uint32_t R = h ? 0 : rgb[i * ch], G = h ? 0 : rgb[i * ch + 1], B = h ? 0 : rgb[i * ch + 2];
         d.img[i] = R | (G << 8) | (B << 16) | (h ? kStateHole : 0u);
+        d.gray[i] = (uint8_t)gray_of(R | (G << 8) | (B << 16));
         d.hole[i] = h ? 1 : 0;
         d.conf[i] = h ? 0.0 : conf[i];
         if (h) atomicAdd(&s_cnt, 1);
@@ -461,8 +463,8 @@ __global__ __launch_bounds__(256) void k_prio_init(JobDev d) {
     const GlobalView v{d};
     if (in_img(d, x, y)) {
         int gx = 0, gy = 0;
-        d.grad[(int64_t)y * d.W + x] = v.grad(x, y, &gx, &gy) >= 0 ? pack_grad(gx, gy) : 0u;
-        d.pcd[(int64_t)y * d.W + x] = pixel_terms<R>(v, d, x, y);
+        const bool has = v.grad(x, y, &gx, &gy) >= 0;
+        d.pcd[(int64_t)y * d.W + x] = has ? off_front(pack_grad(gx, gy)) : pixel_terms<R>(v, d, x, y);
     }
     refresh_block_wave(d, bx, by);   // same wave: its own writes are visible
 }
@@ -1115,9 +1117,12 @@ __device__ __forceinline__ void fill_search(const JobDev &d, int ntiles, uint32_
     }
 }
 
-// Search tiles a group of the batched MFMA dispatch keeps in LDS: with two
-// groups per CU, two tiles of every radius fit beside the tables.
-constexpr int kMultiTiles = 2;
+// Search tiles a group of the batched MFMA dispatch keeps in LDS.  Two of
+// radius up to 6 fit beside the tables with two groups per CU; the commit of
+// radius 7 leaves room for one, that of radius 8 only lets one group onto a
+// CU, which then holds three.
+template <int R>
+constexpr int kMultiTiles = R <= 6 ? 2 : (R == 7 ? 1 : 3);
 
 template <int R, int NT = 1>
 struct SearchLdsMfma {
@@ -1133,7 +1138,9 @@ union FillLdsMfma {
     FillCommitLds<R> c;
     SearchLdsMfma<R, NT> s;
 };
-static_assert(sizeof(FillLdsMfma<kMfmaMaxRadius, kMultiTiles>) + 256 <= 80 * 1024, "two work-groups per CU");
+static_assert(sizeof(FillLdsMfma<6, kMultiTiles<6>>) + 256 <= 80 * 1024 && sizeof(FillLdsMfma<7, kMultiTiles<7>>) + 256 <= 80 * 1024,
+              "two work-groups per CU");
+static_assert(sizeof(FillLdsMfma<8, kMultiTiles<8>>) + 256 <= 160 * 1024, "one work-group per CU");
 
 // Search group of the MFMA form: one 64 x 64 tile of the MFMA tiling, staged
 // once; per target it builds the B-operand tables in LDS from the record and
@@ -1168,8 +1175,11 @@ __device__ __forceinline__ void fill_search_mfma(const JobDev &d, uint32_t epoch
     }
 }
 
+// Waves per SIMD of the MFMA form: radius 8 has LDS for one group per CU.
+constexpr int mfma_waves(int r) { return r <= 7 ? 2 : 1; }
+
 template <int R>
-__global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_fill_mfma(JobDev d, int ntiles, int n_iters, uint32_t epoch) {
+__global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(mfma_waves(R)))) void k_fill_mfma(JobDev d, int ntiles, int n_iters, uint32_t epoch) {
     __shared__ FillLdsMfma<R> lds;
     if (blockIdx.x == 0)
         fill_commit<R>(d, ntiles, n_iters, epoch, lds.c);
@@ -1269,7 +1279,7 @@ struct ServeItem {
 // Scores an item of the MFMA form and reports in the job's slot word.  True
 // when the target tables are now the job's of iteration k.
 template <int R>
-__device__ __forceinline__ bool multi_serve_mfma(const JobDev &d, const ServeItem &it, SearchLdsMfma<R, kMultiTiles> &S,
+__device__ __forceinline__ bool multi_serve_mfma(const JobDev &d, const ServeItem &it, SearchLdsMfma<R, kMultiTiles<R>> &S,
                                                  uint32_t &vmask, bool &anyv) {
     int tx0, ty0;
     mtile::tile_origin<R>(d.rx0, d.ry0, d.ntx, it.t, &tx0, &ty0);
@@ -1406,9 +1416,9 @@ __device__ __forceinline__ void multi_search(const MultiPlan &m, int w, uint32_t
 }
 
 template <int R>
-__global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_fill_multi_mfma(
+__global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(mfma_waves(R)))) void k_fill_multi_mfma(
     MultiPlan m, int n_iters, uint32_t epoch) {
-    __shared__ FillLdsMfma<R, kMultiTiles> lds;
+    __shared__ FillLdsMfma<R, kMultiTiles<R>> lds;
     __shared__ MultiPick pk;
     if ((int)blockIdx.x < m.n_commit) {
         // by value: held through a reference to device memory, the job's
@@ -1418,7 +1428,7 @@ __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(
         return;
     }
     mtile::clear_tables<R>(&lds.s.ft);   // (published by the first poll's barrier)
-    multi_search<kMultiTiles>(m, (int)blockIdx.x - m.n_commit, epoch, &pk,
+    multi_search<kMultiTiles<R>>(m, (int)blockIdx.x - m.n_commit, epoch, &pk,
                               [&](const JobDev &d, const ServeItem &it, uint32_t &vmask, bool &anyv)
                                   __attribute__((always_inline)) { return multi_serve_mfma<R>(d, it, lds.s, vmask, anyv); });
 }
@@ -1444,16 +1454,16 @@ __global__ __launch_bounds__(kCommitThreads) __attribute__((amdgpu_waves_per_eu(
 // radius only), so every work-group runs the per-radius code of its own
 // radius for the whole dispatch.
 union MixLdsMfma {
-    FillLdsMfma<1, kMultiTiles> r1;
-    FillLdsMfma<2, kMultiTiles> r2;
-    FillLdsMfma<3, kMultiTiles> r3;
-    FillLdsMfma<4, kMultiTiles> r4;
-    FillLdsMfma<5, kMultiTiles> r5;
+    FillLdsMfma<1, kMultiTiles<1>> r1;
+    FillLdsMfma<2, kMultiTiles<2>> r2;
+    FillLdsMfma<3, kMultiTiles<3>> r3;
+    FillLdsMfma<4, kMultiTiles<4>> r4;
+    FillLdsMfma<5, kMultiTiles<5>> r5;
 };
 static_assert(kMultiMixMaxR == 5, "MixLdsMfma holds radii 1..5");
 
 template <int R>
-__device__ __forceinline__ void mixed_role(const MultiPlan &m, int n_iters, uint32_t epoch, FillLdsMfma<R, kMultiTiles> &lds,
+__device__ __forceinline__ void mixed_role(const MultiPlan &m, int n_iters, uint32_t epoch, FillLdsMfma<R, kMultiTiles<R>> &lds,
                                            MultiPick *pk) {
     if ((int)blockIdx.x < m.n_commit) {
         const JobDev d = m.slots[m.commit[blockIdx.x]];   // by value, see k_fill_multi_mfma
@@ -1461,7 +1471,7 @@ __device__ __forceinline__ void mixed_role(const MultiPlan &m, int n_iters, uint
         return;
     }
     mtile::clear_tables<R>(&lds.s.ft);   // (published by the first poll's barrier)
-    multi_search<kMultiTiles>(m, (int)blockIdx.x - m.n_commit, epoch, pk,
+    multi_search<kMultiTiles<R>>(m, (int)blockIdx.x - m.n_commit, epoch, pk,
                               [&](const JobDev &d, const ServeItem &it, uint32_t &vmask, bool &anyv)
                                   __attribute__((always_inline)) { return multi_serve_mfma<R>(d, it, lds.s, vmask, anyv); });
 }
@@ -1668,6 +1678,8 @@ const void *fill_mfma_kernel(int r) {
         case 4: return (const void *)k_fill_mfma<4>;
         case 5: return (const void *)k_fill_mfma<5>;
         case 6: return (const void *)k_fill_mfma<6>;
+        case 7: return (const void *)k_fill_mfma<7>;
+        case 8: return (const void *)k_fill_mfma<8>;
         default: return nullptr;
     }
 }
@@ -1696,6 +1708,8 @@ const void *multi_mfma_kernel(int r) {
         case 4: return (const void *)k_fill_multi_mfma<4>;
         case 5: return (const void *)k_fill_multi_mfma<5>;
         case 6: return (const void *)k_fill_multi_mfma<6>;
+        case 7: return (const void *)k_fill_multi_mfma<7>;
+        case 8: return (const void *)k_fill_multi_mfma<8>;
         default: return nullptr;
     }
 }

@@ -20,7 +20,8 @@ constexpr int kMaxSuper = 512;
 constexpr int kTileW = 64;                             // search tile width (one wave)
 constexpr int kSearchWaves = 4;                        // waves per search work-group
 constexpr int kCommitThreads = 256;   // one work-group per image; 512 VGPRs per thread
-constexpr int kMfmaMaxRadius = 6;     // int8-MFMA search: patches up to 13x13
+constexpr int kMfmaMaxRadius = 8;     // int8-MFMA search: the band of 16 columns and 2r pixels fits two MFMAs
+constexpr int kMfmaPathRadius = 6;    // largest radius INPAINT_PATH_MFMA is accepted for
 constexpr int kMfmaTileRows = 16;     // MFMA search tile: 64 x 64 candidates
 constexpr int kFillTileRows = 8;      // persistent fill: candidate rows per search thread
 
@@ -126,12 +127,13 @@ struct InitInfo {
 // single-image kernels and stored in the slot table for batched ones.
 struct JobDev {
     uint32_t *img;       // RGB and the pixel state (0 known, 1 hole) in the 4th byte, W*H
-    uint32_t *grad;      // packed gradients of the priority range's pixels, W*H
+    uint8_t *gray;       // W*H
     uint8_t *hole;       // W*H, 1 = still to fill
     uint8_t *hole0;      // W*H, 1 = in the original hole (fixed at create)
     uint8_t *vrad;       // W*H, largest r <= 8 with a valid patch at the centre
     double *conf;        // W*H
-    double2 *pcd;        // W*H (C, D) of front pixels; C = -1 elsewhere
+    double2 *pcd;        // W*H (C, D) of front pixels; elsewhere C = -1, and in the priority range
+                         // the packed gradient in the low word of D
     BlockBest *blk;      // ceil(W/8)*ceil(H/8)
     BlockBest *sup;      // maxima of superblocks of the priority range, kMaxSuper
     uint64_t *partials;  // one (ssd << 32 | index) per search tile

@@ -121,7 +121,7 @@ static MaskStats mask_stats(const uint8_t *m, int stride, int W, int H) {
 }
 
 struct Layout {
-    uint64_t img, grad, hole, hole0, vrad, conf, pcd, blk, sup, partials, tgt, qtgt, srcp, vradp, hdist, st,
+    uint64_t img, gray, hole, hole0, vrad, conf, pcd, blk, sup, partials, tgt, qtgt, srcp, vradp, hdist, st,
         sync, fslot, info, key, mplan, log, total;
     int64_t log_cap;
     int max_tiles;
@@ -143,7 +143,7 @@ Layout make_layout(int W, int H, const inpaint_params &p) {
         return o;
     };
     L.img = take(4 * n);
-    L.grad = take(4 * n);
+    L.gray = take(n);
     L.hole = take(n);
     L.hole0 = take(n);
     L.vrad = take(n);
@@ -320,7 +320,7 @@ static int32_t check_params(int32_t W, int32_t H, const inpaint_params *p, std::
         *why = "tile_rows must be 0, 4, 8 or 16";
         return INPAINT_INVALID_ARGUMENT;
     }
-    if (p->path == INPAINT_PATH_MFMA && !mfma_supported(p->patch_radius)) {
+    if (p->path == INPAINT_PATH_MFMA && p->patch_radius > kMfmaPathRadius) {
         *why = "the int8-MFMA search supports patch radius 1..6";
         return INPAINT_INVALID_ARGUMENT;
     }
@@ -557,7 +557,7 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     JobDev &d = c->d;
     uint8_t *ws = c->ws;
     d.img = (uint32_t *)(ws + L.img);
-    d.grad = (uint32_t *)(ws + L.grad);
+    d.gray = ws + L.gray;
     d.hole = ws + L.hole;
     d.hole0 = ws + L.hole0;
     d.vrad = ws + L.vrad;
@@ -568,7 +568,13 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     d.partials = (uint64_t *)(ws + L.partials);
     d.tgt = (TargetStage *)(ws + L.tgt);
     d.qtgt = (TargetStage *)(ws + L.qtgt);
-    d.mfma = p->path == INPAINT_PATH_MFMA ? 1 : 0;
+    // AUTO searches on the matrix cores wherever that search can run: a
+    // candidate's whole window is scored (INTERSECT counts per pixel) and the
+    // caller asks for no SIMT tile height.  A search launch at 1080p takes 9
+    // (9x9) to 25 us less than the SIMT one, a persistent removal half the
+    // time, at every size from 128 x 96 up.
+    d.mfma = p->path == INPAINT_PATH_MFMA ||
+             (p->path == INPAINT_PATH_AUTO && p->scoring == INPAINT_SCORE_WHOLE && p->tile_rows == 0);
     d.srcp = (uint32_t *)(ws + L.srcp);
     d.vradp = ws + L.vradp;
     d.hdist = L.hdist ? ws + L.hdist : nullptr;
@@ -631,7 +637,7 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     d.ry0 = k[1];
     d.rx1 = std::max(k[2], k[0]);
     d.ry1 = std::max(k[3], k[1]);
-    c->mfma = p->path == INPAINT_PATH_MFMA;
+    c->mfma = d.mfma != 0;
     c->direct = p->path == INPAINT_PATH_SIMT_DIRECT;
     set_tiles(d, c->mfma ? kMfmaTileRows : (p->tile_rows ? p->tile_rows : kDefaultTileRows), c->mfma ? d.r : 0);
 
@@ -755,7 +761,10 @@ int32_t inpaint_find_exemplar_static(inpaint_ctx *ctx, int32_t tx, int32_t ty, i
     q.ry1 = k[3];
     const bool mfma = ctx->mfma && mfma_supported(r);
     set_tiles(q, d.tile_rows, mfma ? r : 0);
-    if ((int64_t)q.ntx * q.nty > kStaticMaxTiles)
+    // (AUTO's limit is that of the default SIMT tile, whichever search runs)
+    JobDev lim = q;
+    if (mfma && ctx->p.path == INPAINT_PATH_AUTO) set_tiles(lim, kDefaultTileRows);
+    if ((int64_t)lim.ntx * lim.nty > kStaticMaxTiles)
         return ctx->fail(INPAINT_INVALID_ARGUMENT, "search rect needs more than " + std::to_string(kStaticMaxTiles) +
                                                        " search tiles (the static scratch limit)");
     q.qtgt = (TargetStage *)(base + kStaticStageOff);

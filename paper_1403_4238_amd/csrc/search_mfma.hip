@@ -164,6 +164,8 @@ hipError_t launch_search_batched_mfma(const JobDev *slots, const WorkItem *items
         case 4: CALL(4); break;
         case 5: CALL(5); break;
         case 6: CALL(6); break;
+        case 7: CALL(7); break;
+        case 8: CALL(8); break;
         default: return hipErrorInvalidValue;
     }
 #undef CALL
@@ -179,6 +181,8 @@ hipError_t launch_search_mfma(const JobDev &d, bool query, int r, int rx0, int r
         case 4: return launch_mfma_t<4>(d, query, rx0, ry0, rx1, ry1, ntx, nty, s, e0, e1);
         case 5: return launch_mfma_t<5>(d, query, rx0, ry0, rx1, ry1, ntx, nty, s, e0, e1);
         case 6: return launch_mfma_t<6>(d, query, rx0, ry0, rx1, ry1, ntx, nty, s, e0, e1);
+        case 7: return launch_mfma_t<7>(d, query, rx0, ry0, rx1, ry1, ntx, nty, s, e0, e1);
+        case 8: return launch_mfma_t<8>(d, query, rx0, ry0, rx1, ry1, ntx, nty, s, e0, e1);
         default: return hipErrorInvalidValue;
     }
 }
