@@ -15,6 +15,8 @@
 // and from the LDS copy of the neighbourhood (per iteration).
 #pragma clang fp contract(off)
 
+#include <algorithm>
+
 #include "commit.h"
 #include "search_mfma_tile.h"
 
@@ -259,27 +261,61 @@ __device__ void select_and_stage(const JobDev &d, Scratch &s, int64_t *fk, uint3
 // ----------------------------------------------------------------- kernels
 
 #if INPAINT_FILL_PART == 0
-__global__ void k_init_info(InitInfo *info, uint32_t nonce) {
-    info->hole_count = 0;
-    info->bad = 0;
-    info->bx0 = INT32_MAX;
-    info->by0 = INT32_MAX;
-    info->bx1 = INT32_MIN;
-    info->by1 = INT32_MIN;
-    info->valid_count = 0;
-    info->nonce = nonce;
-    info->seal = 0;
-    info->blocks = 0;
+// Cleared results, the loop state of a fresh removal (nothing staged), and no
+// go or slot word of an earlier use of the workspace.
+__global__ __launch_bounds__(256) void k_init_info(JobDev d, int64_t remaining, int nslots, uint32_t nonce) {
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x), n = (int)(gridDim.x * blockDim.x);
+    for (int t = i; t < nslots; t += n) d.fslot[t] = 0;
+    for (int t = i; t < (int)(sizeof(FillSync) / 4); t += n) ((uint32_t *)d.sync)[t] = 0;
+    for (int t = i; t < (int)(sizeof(IterState) / 4); t += n) ((uint32_t *)d.st)[t] = 0;
+    __syncthreads();
+    if (i == 0) {   // (block 0 cleared the state: it has more threads than that has words)
+        static_assert(sizeof(IterState) / 4 <= 256, "one block clears the state");
+        d.st->remaining = remaining;
+        d.st->iter_limit = INT64_MAX;
+        InitInfo *info = d.info;
+        info->hole_count = 0;
+        info->bad = 0;
+        info->bx0 = INT32_MAX;
+        info->by0 = INT32_MAX;
+        info->bx1 = INT32_MIN;
+        info->by1 = INT32_MIN;
+        info->valid_count = 0;
+        info->nonce = nonce;
+        info->seal = 0;
+        info->blocks = 0;
+    }
 }
 
 __global__ void k_seal(InitInfo *info, uint32_t nonce) { info->seal = nonce; }
 
 // Initialisation: zero the hole pixels, RGBX image with the pixel state, integer
-// BT.601 gray, hole map, confidence 1 / 0, hole count and bounding box.
-__global__ __launch_bounds__(256) void k_init_pixels(JobDev d, const uint8_t *rgb, int ch,
-                                                     const uint8_t *mask) {
+// BT.601 gray, hole map, confidence 1 / 0, hole count and bounding box.  Four
+// pixels per thread and round, at most kInitBlocks work-groups: one thread per
+// pixel moved single bytes and counted 8100 work-groups at one address (1080p:
+// 144 us, now 41).
+constexpr unsigned kInitBlocks = 512;
+__device__ __forceinline__ void unpack_rgb(const uint8_t *rgb, int ch, int64_t i, bool whole, int left, uint32_t *w) {
+    if (whole && ch == 4) {
+        const uint4 v = *(const uint4 *)(rgb + 4 * i);
+        w[0] = v.x & kColour, w[1] = v.y & kColour, w[2] = v.z & kColour, w[3] = v.w & kColour;
+    } else if (whole) {
+        const uint32_t *p = (const uint32_t *)(rgb + 3 * i);
+        const uint32_t a = p[0], b = p[1], c = p[2];
+        w[0] = a & kColour;
+        w[1] = a >> 24 | (b & 0xffffu) << 8;
+        w[2] = b >> 16 | (c & 0xffu) << 16;
+        w[3] = c >> 8;
+    } else {
+        for (int j = 0; j < 4; ++j) {
+            const uint8_t *p = rgb + (i + min(j, left - 1)) * ch;
+            w[j] = p[0] | (uint32_t)p[1] << 8 | (uint32_t)p[2] << 16;
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_init_pixels(JobDev d, const uint8_t *rgb, int ch, const uint8_t *mask) {
     const int64_t n = (int64_t)d.W * d.H;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     __shared__ int s_cnt, s_x0, s_y0, s_x1, s_y1;
     if (threadIdx.x == 0) {
         s_cnt = 0;
@@ -289,23 +325,57 @@ __global__ __launch_bounds__(256) void k_init_pixels(JobDev d, const uint8_t *rg
         s_y1 = INT32_MIN;
     }
     __syncthreads();
-    if (i < n) {
-        const int x = col_of(i, d.W), y = row_of(i, d.W);
-        const bool h = mask[i] != 0;
-        const uint32_t R = h ? 0 : rgb[i * ch], G = h ? 0 : rgb[i * ch + 1],
-                       B = h ? 0 : rgb[i * ch + 2];
-        d.img[i] = R | (G << 8) | (B << 16) | (h ? kStateHole : 0u);
-        d.gray[i] = (uint8_t)gray_of(R | (G << 8) | (B << 16));
-        d.hole[i] = h ? 1 : 0;
-        d.hole0[i] = h ? 1 : 0;
-        d.conf[i] = h ? 0.0 : 1.0;
-        if (h) {
-            atomicAdd(&s_cnt, 1);
-            atomicMin(&s_x0, x);
-            atomicMin(&s_y0, y);
-            atomicMax(&s_x1, x + 1);
-            atomicMax(&s_y1, y + 1);
+    int cnt = 0, x0 = INT32_MAX, y0 = INT32_MAX, x1 = INT32_MIN, y1 = INT32_MIN;
+    for (int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); i < n; i += 4 * 256 * (int64_t)gridDim.x) {
+        const int left = (int)min(n - i, (int64_t)4);
+        const bool whole = left == 4;
+        uint32_t w[4], m = 0;
+        unpack_rgb(rgb, ch, i, whole, left, w);
+        if (whole) m = *(const uint32_t *)(mask + i);
+        else
+            for (int j = 0; j < left; ++j) m |= (uint32_t)mask[i + j] << (8 * j);
+        uint32_t g = 0, hole = 0;
+        double c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool h = ((m >> (8 * j)) & 255u) != 0;
+            g |= h ? 0u : (uint32_t)gray_of(w[j]) << (8 * j);
+            hole |= h ? 1u << (8 * j) : 0u;
+            w[j] = h ? kStateHole : w[j];
+            c[j] = h ? 0.0 : 1.0;
         }
+        if (whole) {
+            *(uint4 *)(d.img + i) = make_uint4(w[0], w[1], w[2], w[3]);
+            *(uint32_t *)(d.gray + i) = g;
+            *(uint32_t *)(d.hole + i) = hole;
+            *(uint32_t *)(d.hole0 + i) = hole;
+            *(double2 *)(d.conf + i) = make_double2(c[0], c[1]);
+            *(double2 *)(d.conf + i + 2) = make_double2(c[2], c[3]);
+        } else {
+            for (int j = 0; j < left; ++j) {
+                d.img[i + j] = w[j];
+                d.gray[i + j] = (uint8_t)(g >> (8 * j));
+                d.hole[i + j] = d.hole0[i + j] = (uint8_t)(hole >> (8 * j));
+                d.conf[i + j] = c[j];
+            }
+        }
+        if (hole) {
+            int x = col_of(i, d.W), y = row_of(i, d.W);
+            for (int j = 0; j < left; ++j) {
+                if ((hole >> (8 * j)) & 1u) {
+                    ++cnt;
+                    x0 = min(x0, x), x1 = max(x1, x + 1), y0 = min(y0, y), y1 = max(y1, y + 1);
+                }
+                if (++x == d.W) x = 0, ++y;
+            }
+        }
+    }
+    if (cnt) {
+        atomicAdd(&s_cnt, cnt);
+        atomicMin(&s_x0, x0);
+        atomicMin(&s_y0, y0);
+        atomicMax(&s_x1, x1);
+        atomicMax(&s_y1, y1);
     }
     __syncthreads();
     if (threadIdx.x == 0 && s_cnt > 0) {
@@ -318,6 +388,22 @@ __global__ __launch_bounds__(256) void k_init_pixels(JobDev d, const uint8_t *rg
     if (threadIdx.x == 0) atomicAdd(&d.info->blocks, 1u);
 }
 
+// The colours of `count` pixels, packed, 4 pixels per thread.
+__global__ __launch_bounds__(256) void k_pack_rgb(const uint32_t *img, int64_t count, uint8_t *out) {
+    const int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (i >= count) return;
+    if (i + 4 <= count) {
+        const uint4 v = *(const uint4 *)(img + i);
+        uint32_t *o = (uint32_t *)(out + 3 * i);
+        o[0] = (v.x & kColour) | v.y << 24;
+        o[1] = ((v.y >> 8) & 0xffffu) | v.z << 16;
+        o[2] = ((v.z >> 16) & 0xffu) | v.w << 8;
+    } else {
+        for (int64_t j = i; j < count; ++j)
+            for (int c = 0; c < 3; ++c) out[3 * j + c] = (uint8_t)(img[j] >> (8 * c));
+    }
+}
+
 // ---- checkpoint import (resume / iterative editing) ------------------------
 
 // Counts the pixels of a checkpoint that fail its checks: a hole pixel
@@ -325,14 +411,13 @@ __global__ __launch_bounds__(256) void k_init_pixels(JobDev d, const uint8_t *rg
 // confidence is not in [0, 1] (NaN included).  Writes nothing else.
 __global__ __launch_bounds__(256) void k_import_check(JobDev d, const uint8_t *hole, const double *conf) {
     const int64_t n = (int64_t)d.W * d.H;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int bad = 0;
-    if (i < n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * (int64_t)gridDim.x) {
         const bool h = hole[i] != 0, h0 = d.hole0[i] != 0;
         const double c = conf[i];
-        bad = (h && !h0) || (h0 && !h && !(c >= 0.0 && c <= 1.0));
+        bad += (h && !h0) || (h0 && !h && !(c >= 0.0 && c <= 1.0));
     }
-    if (bad) atomicAdd((unsigned long long *)&d.info->bad, 1ull);
+    if (bad) atomicAdd((unsigned long long *)&d.info->bad, (unsigned long long)bad);
     if (threadIdx.x == 0) atomicAdd(&d.info->blocks, 1u);
 }
 
@@ -342,19 +427,21 @@ __global__ __launch_bounds__(256) void k_import_check(JobDev d, const uint8_t *h
 __global__ __launch_bounds__(256) void k_import_apply(JobDev d, const uint8_t *rgb, int ch, const uint8_t *hole,
                                                       const double *conf) {
     const int64_t n = (int64_t)d.W * d.H;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     __shared__ int s_cnt;
     if (threadIdx.x == 0) s_cnt = 0;
     __syncthreads();
-    if (i < n && d.hole0[i]) {
+    int cnt = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 256 * (int64_t)gridDim.x) {
+        if (!d.hole0[i]) continue;
         const bool h = hole[i] != 0;
         const uint32_t R = h ? 0 : rgb[i * ch], G = h ? 0 : rgb[i * ch + 1], B = h ? 0 : rgb[i * ch + 2];
         d.img[i] = R | (G << 8) | (B << 16) | (h ? kStateHole : 0u);
         d.gray[i] = (uint8_t)gray_of(R | (G << 8) | (B << 16));
         d.hole[i] = h ? 1 : 0;
         d.conf[i] = h ? 0.0 : conf[i];
-        if (h) atomicAdd(&s_cnt, 1);
+        cnt += h;
     }
+    if (cnt) atomicAdd(&s_cnt, cnt);
     __syncthreads();
     if (threadIdx.x == 0 && s_cnt > 0) atomicAdd((unsigned long long *)&d.info->hole_count, (unsigned long long)s_cnt);
     if (threadIdx.x == 0) atomicAdd(&d.info->blocks, 1u);
@@ -368,85 +455,79 @@ __global__ void k_import_reset(InitInfo *info, uint32_t nonce) {
     info->blocks = 0;
 }
 
-// Horizontal distance (capped at 10) from each pixel to the nearest hole or
-// out-of-image pixel of its row.
-__global__ __launch_bounds__(256) void k_init_hdist(JobDev d, uint8_t *hdist) {
-    const int64_t n = (int64_t)d.W * d.H;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int x = col_of(i, d.W), y = row_of(i, d.W);
-    int h = 10;
-    for (int dx = 0; dx < 10; ++dx) {
-        const int xl = x - dx, xr = x + dx;
-        if (xl < 0 || xr >= d.W || d.hole[(int64_t)y * d.W + xl] || d.hole[(int64_t)y * d.W + xr]) {
-            h = dx;
-            break;
-        }
-    }
-    hdist[i] = (uint8_t)h;
-}
-
+// Validity radii and the padded search planes, one 64 x 16 tile of the padded
+// plane per work-group.
+//
 // vrad = (Chebyshev distance to the nearest hole or out-of-image pixel) - 1,
 // clamped to [0, 8]: the patch of radius r at a centre lies inside the image
-// and the original known region iff vrad >= r.
-__global__ __launch_bounds__(256) void k_init_vrad(JobDev d, const uint8_t *hdist) {
-    const int64_t n = (int64_t)d.W * d.H;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int x = col_of(i, d.W), y = row_of(i, d.W);
-    int dist = 10;
-    for (int dy = -9; dy <= 9; ++dy) {
-        const int yy = y + dy, ady = dy < 0 ? -dy : dy;
-        const int h = (yy < 0 || yy >= d.H) ? 0 : hdist[(int64_t)yy * d.W + x];
-        const int m = ady > h ? ady : h;
-        dist = m < dist ? m : dist;
+// and the original known region iff vrad >= r.  A row's holes are two wave
+// ballots (64 columns and 9 on either side), from which each lane takes the
+// distance to the nearest along the row (capped at 10) with a shift and two
+// bit scans; the rows combine through LDS.  The padded planes hold the
+// original image (hole pixels zero) and vrad, zero outside the image; with
+// INTERSECT scoring the 4th byte of a source pixel's word is 1 and the
+// validity plane only flags source pixels (a candidate centre needs to be
+// one).  hdist (or null) keeps the row distances.  In place of three kernels
+// that read the holes byte by byte (1080p: 52 us together, now 18).
+__global__ __launch_bounds__(256) void k_init_planes(JobDev d, uint8_t *hdist) {
+    constexpr int TH = 16, RD = 9;
+    __shared__ uint8_t hd[TH + 2 * RD][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int x0 = (int)blockIdx.x * 64 - kPadL, y0 = (int)blockIdx.y * TH - kPadT, x = x0 + lane;
+    const auto bad = [&](int px, int py) { return !in_img(d, px, py) || d.hole[(int64_t)py * d.W + px] != 0; };
+    for (int r = wave; r < TH + 2 * RD; r += 4) {
+        const int y = y0 - RD + r;
+        const uint64_t b0 = __ballot(bad(x - RD, y)), b1 = __ballot(lane < 2 * RD && bad(x - RD + 64, y));
+        // bits 0 .. 18: columns x - 9 .. x + 9
+        const uint32_t w = (uint32_t)((b0 >> lane) | (lane ? b1 << (64 - lane) : 0ull)) & 0x7ffffu;
+        const uint32_t right = w >> RD, leftw = w & 0x3ffu;
+        const int dr = right ? __builtin_ctz(right) : 10, dl = leftw ? __builtin_clz(leftw) - 22 : 10;
+        const uint8_t h = (uint8_t)min(dr, dl);
+        hd[r][lane] = h;
+        if (hdist && r >= RD && r < TH + RD && in_img(d, x, y)) hdist[(int64_t)y * d.W + x] = h;
     }
-    int v = dist - 1;
-    v = v < 0 ? 0 : (v > kMaxRadius ? kMaxRadius : v);
-    d.vrad[i] = (uint8_t)v;
-}
-
-// Search planes: the original image (hole pixels zero) and vrad in the
-// zero-padded layout the search stages from.  With INTERSECT scoring the 4th
-// byte of a source pixel's word is 1 and the validity plane only flags
-// source pixels (a candidate centre needs to be one).
-__global__ __launch_bounds__(256) void k_init_padded(JobDev d) {
-    const int pitch = d.pitch;
-    const int64_t n = (int64_t)pitch * padded_rows(d.H);
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int x = (int)(i % pitch) - kPadL, y = (int)(i / pitch) - kPadT;
-    uint32_t pix = 0;
-    uint8_t vr = 0;
-    if (x >= 0 && x < d.W && y >= 0 && y < d.H) {
-        pix = d.img[(int64_t)y * d.W + x] & kColour;
-        vr = d.vrad[(int64_t)y * d.W + x];
-        if (d.isect) {
-            const bool src = d.hole[(int64_t)y * d.W + x] == 0;
-            pix |= src ? 1u << 24 : 0u;
-            vr = src ? 1 : 0;
+    __syncthreads();
+    if (x + kPadL >= d.pitch) return;
+    for (int q = 0; q < TH / 4; ++q) {
+        const int r = wave * (TH / 4) + q, y = y0 + r;
+        if (y + kPadT >= padded_rows(d.H)) return;
+        int dist = 10;
+#pragma unroll
+        for (int dy = -RD; dy <= RD; ++dy) dist = min(dist, max(dy < 0 ? -dy : dy, (int)hd[r + RD + dy][lane]));
+        uint32_t pix = 0;
+        uint8_t vr = 0;
+        if (in_img(d, x, y)) {
+            const int64_t i = (int64_t)y * d.W + x;
+            vr = (uint8_t)min(max(dist - 1, 0), kMaxRadius);
+            d.vrad[i] = vr;
+            const uint32_t w = d.img[i];
+            pix = w & kColour;
+            if (d.isect) {
+                vr = state_of(w) == 0 ? 1 : 0;
+                pix |= (uint32_t)vr << 24;
+            }
         }
+        const int64_t o = (int64_t)(y + kPadT) * d.pitch + (x + kPadL);
+        d.srcp[o] = pix;
+        d.vradp[o] = vr;
     }
-    d.srcp[i] = pix;
-    d.vradp[i] = vr;
 }
 
-// Number of valid source centres in the search rectangle.
+// Number of valid source centres in the search rectangle, a row per work-group
+// and round (1080p: 12 us; a shared-memory atomic per centre took 97).
 __global__ __launch_bounds__(256) void k_count_valid(JobDev d) {
-    const int rw = d.rx1 - d.rx0;
-    const int64_t n = (int64_t)rw * (d.ry1 - d.ry0);
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    __shared__ int s_cnt;
-    if (threadIdx.x == 0) s_cnt = 0;
+    __shared__ int s_cnt[4];
+    int cnt = 0;
+    for (int y = d.ry0 + (int)blockIdx.x; y < d.ry1; y += (int)gridDim.x)
+        for (int x = d.rx0 + (int)threadIdx.x; x < d.rx1; x += 256) {
+            const int64_t j = (int64_t)y * d.W + x;
+            cnt += d.isect ? d.hole[j] == 0 : d.vrad[j] >= d.r;
+        }
+    cnt = (int)dpp::sum_u32((uint32_t)cnt);
+    if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
     __syncthreads();
-    if (i < n) {
-        const int x = d.rx0 + (int)(i % rw), y = d.ry0 + (int)(i / rw);
-        const int64_t j = (int64_t)y * d.W + x;
-        if (d.isect ? d.hole[j] == 0 : d.vrad[j] >= d.r) atomicAdd(&s_cnt, 1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && s_cnt)
-        atomicAdd((unsigned long long *)&d.info->valid_count, (unsigned long long)s_cnt);
+    cnt = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    if (threadIdx.x == 0 && cnt) atomicAdd((unsigned long long *)&d.info->valid_count, (unsigned long long)cnt);
 }
 #endif  // INPAINT_FILL_PART 0
 
@@ -1575,54 +1656,53 @@ __global__ void k_count_active(const JobDev *slots, int nslots, int64_t *out, in
 
 static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-uint32_t init_pixel_blocks(const JobDev &d) { return blocks_for((int64_t)d.W * d.H, 256); }
+uint32_t init_pixel_blocks(const JobDev &d) {
+    return std::min(blocks_for((int64_t)d.W * d.H, 1024), kInitBlocks);
+}
+
+static void launch_planes(const JobDev &d, hipStream_t s) {
+    hipLaunchKernelGGL(k_init_planes, dim3(blocks_for(d.pitch, 64), blocks_for(padded_rows(d.H), 16)), dim3(256), 0, s, d,
+                       d.hdist);
+}
 
 hipError_t launch_seal(const JobDev &d, uint32_t nonce, hipStream_t s) {
     hipLaunchKernelGGL(k_seal, dim3(1), dim3(1), 0, s, d.info, nonce);
     return hipGetLastError();
 }
 
-hipError_t launch_init(const JobDev &d, const uint8_t *stage_rgb, int channels,
-                       const uint8_t *stage_mask, uint8_t *hdist, uint32_t nonce, hipStream_t s) {
-    const int64_t n = (int64_t)d.W * d.H;
-    hipLaunchKernelGGL(k_init_info, dim3(1), dim3(1), 0, s, d.info, nonce);
-    hipLaunchKernelGGL(k_init_pixels, dim3(blocks_for(n, 256)), dim3(256), 0, s, d, stage_rgb,
-                       channels, stage_mask);
-    hipLaunchKernelGGL(k_init_hdist, dim3(blocks_for(n, 256)), dim3(256), 0, s, d, hdist);
-    hipLaunchKernelGGL(k_init_vrad, dim3(blocks_for(n, 256)), dim3(256), 0, s, d,
-                       (const uint8_t *)hdist);
-    const int64_t np = (int64_t)d.pitch * padded_rows(d.H);
-    hipLaunchKernelGGL(k_init_padded, dim3(blocks_for(np, 256)), dim3(256), 0, s, d);
+hipError_t launch_init(const JobDev &d, const uint8_t *stage_rgb, int channels, const uint8_t *stage_mask,
+                       int64_t remaining, int nslots, uint32_t nonce, hipStream_t s) {
+    hipLaunchKernelGGL(k_init_info, dim3(std::min(blocks_for(nslots, 256), 64u)), dim3(256), 0, s, d, remaining, nslots,
+                       nonce);
+    hipLaunchKernelGGL(k_init_pixels, dim3(init_pixel_blocks(d)), dim3(256), 0, s, d, stage_rgb, channels, stage_mask);
+    launch_planes(d, s);
     return hipGetLastError();
 }
 
 hipError_t launch_import_check(const JobDev &d, const uint8_t *hole, const double *conf, uint32_t nonce,
                                hipStream_t s) {
-    const int64_t n = (int64_t)d.W * d.H;
     hipLaunchKernelGGL(k_import_reset, dim3(1), dim3(1), 0, s, d.info, nonce);
-    hipLaunchKernelGGL(k_import_check, dim3(blocks_for(n, 256)), dim3(256), 0, s, d, hole, conf);
+    hipLaunchKernelGGL(k_import_check, dim3(init_pixel_blocks(d)), dim3(256), 0, s, d, hole, conf);
     return hipGetLastError();
 }
 
 hipError_t launch_import_apply(const JobDev &d, const uint8_t *rgb, int channels, const uint8_t *hole,
-                               const double *conf, uint8_t *hdist, uint32_t nonce, hipStream_t s) {
-    const int64_t n = (int64_t)d.W * d.H;
+                               const double *conf, uint32_t nonce, hipStream_t s) {
     hipLaunchKernelGGL(k_import_reset, dim3(1), dim3(1), 0, s, d.info, nonce);
-    hipLaunchKernelGGL(k_import_apply, dim3(blocks_for(n, 256)), dim3(256), 0, s, d, rgb, channels, hole, conf);
-    if (d.policy == INPAINT_SOURCE_CURRENT) {
-        // the source region is the current known region: rebuild its planes
-        hipLaunchKernelGGL(k_init_hdist, dim3(blocks_for(n, 256)), dim3(256), 0, s, d, hdist);
-        hipLaunchKernelGGL(k_init_vrad, dim3(blocks_for(n, 256)), dim3(256), 0, s, d, (const uint8_t *)hdist);
-        const int64_t np = (int64_t)d.pitch * padded_rows(d.H);
-        hipLaunchKernelGGL(k_init_padded, dim3(blocks_for(np, 256)), dim3(256), 0, s, d);
-    }
+    hipLaunchKernelGGL(k_import_apply, dim3(init_pixel_blocks(d)), dim3(256), 0, s, d, rgb, channels, hole, conf);
+    // (under the CURRENT policy the source region is the current known region)
+    if (d.policy == INPAINT_SOURCE_CURRENT) launch_planes(d, s);
     return hipGetLastError();
 }
 
 hipError_t launch_count_valid(const JobDev &d, hipStream_t s) {
-    const int64_t n = (int64_t)(d.rx1 - d.rx0) * (d.ry1 - d.ry0);
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_valid, dim3(blocks_for(n, 256)), dim3(256), 0, s, d);
+    if (d.rx1 <= d.rx0 || d.ry1 <= d.ry0) return hipSuccess;
+    hipLaunchKernelGGL(k_count_valid, dim3(std::min((unsigned)(d.ry1 - d.ry0), kInitBlocks)), dim3(256), 0, s, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_rgb(const uint32_t *img, int64_t count, uint8_t *out, hipStream_t s) {
+    hipLaunchKernelGGL(k_pack_rgb, dim3(blocks_for(count, 1024)), dim3(256), 0, s, img, count, out);
     return hipGetLastError();
 }
 

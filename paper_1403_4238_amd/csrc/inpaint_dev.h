@@ -189,8 +189,12 @@ struct MultiPlan {
 };
 
 // ---- launchers (defined in the .hip files) ----
-hipError_t launch_init(const JobDev &d, const uint8_t *stage_rgb, int channels,
-                       const uint8_t *stage_mask, uint8_t *hdist, uint32_t nonce, hipStream_t s);
+// Clears the results, slots and records and sets the loop state, then the pixel
+// pass and the search planes.
+hipError_t launch_init(const JobDev &d, const uint8_t *stage_rgb, int channels, const uint8_t *stage_mask,
+                       int64_t remaining, int nslots, uint32_t nonce, hipStream_t s);
+// Packed RGB of `count` pixels from a 16-byte aligned image word on.
+hipError_t launch_pack_rgb(const uint32_t *img, int64_t count, uint8_t *out, hipStream_t s);
 // Work-groups of the pixel pass of launch_init / launch_import_*.
 uint32_t init_pixel_blocks(const JobDev &d);
 // Writes info->seal = nonce once every earlier kernel on the stream is done.
@@ -203,7 +207,7 @@ hipError_t launch_count_valid(const JobDev &d, hipStream_t s);
 hipError_t launch_import_check(const JobDev &d, const uint8_t *hole, const double *conf, uint32_t nonce,
                                hipStream_t s);
 hipError_t launch_import_apply(const JobDev &d, const uint8_t *rgb, int channels, const uint8_t *hole,
-                               const double *conf, uint8_t *hdist, uint32_t nonce, hipStream_t s);
+                               const double *conf, uint32_t nonce, hipStream_t s);
 hipError_t launch_prio_init(const JobDev &d, hipStream_t s);
 hipError_t launch_commit(const JobDev &d, hipStream_t s);
 // SIMT search of one target; `d.isect` selects INTERSECT scoring.

@@ -33,6 +33,7 @@ thread_local std::string g_create_error;
 
 constexpr uint64_t kAlign = 256;
 constexpr int kDefaultTileRows = 8;
+constexpr uint64_t kPackBytes = 3 << 18;   // packed pixels read back at a time (2^18 of them)
 constexpr int kMaxGroups = 4096;   // work-groups of a persistent dispatch (co-resident: <= 4 per CU)
 
 uint64_t align_up(uint64_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -104,7 +105,19 @@ static MaskStats mask_stats(const uint8_t *m, int stride, int W, int H) {
         const uint8_t *row = m + (int64_t)y * stride;
         int first = -1, last = -1;
         int64_t c = 0;
-        for (int x = 0; x < W; ++x)
+        int x = 0;
+        // eight bytes at a time: most words of a mask are zero
+        for (; x + 8 <= W; x += 8) {
+            uint64_t w;
+            std::memcpy(&w, row + x, 8);
+            if (!w) continue;
+            const uint64_t low7 = 0x7f7f7f7f7f7f7f7full;
+            const uint64_t nz = (((w & low7) + low7) | w) & ~low7;   // top bit of every nonzero byte
+            if (first < 0) first = x + __builtin_ctzll(nz) / 8;
+            last = x + 7 - __builtin_clzll(nz) / 8;
+            c += __builtin_popcountll(nz);
+        }
+        for (; x < W; ++x)
             if (row[x]) {
                 if (first < 0) first = x;
                 last = x;
@@ -122,7 +135,7 @@ static MaskStats mask_stats(const uint8_t *m, int stride, int W, int H) {
 
 struct Layout {
     uint64_t img, gray, hole, hole0, vrad, conf, pcd, blk, sup, partials, tgt, qtgt, srcp, vradp, hdist, st,
-        sync, fslot, info, key, mplan, log, total;
+        sync, fslot, info, key, mplan, pack, log, total;
     int64_t log_cap;
     int max_tiles;
 };
@@ -171,6 +184,7 @@ Layout make_layout(int W, int H, const inpaint_params &p) {
     // one-job plan of the batched persistent dispatch (images whose tiles
     // outnumber the co-resident work-groups): slot, committer id, items, first
     L.mplan = take(sizeof(JobDev) + 256 + sizeof(WorkItem) * (uint64_t)L.max_tiles + 4ull * (kMaxGroups + 1));
+    L.pack = take(std::min<uint64_t>(3 * n, kPackBytes));
     L.log_cap = log_capacity(W, H, p);
     L.log = take(sizeof(StepRec) * (uint64_t)L.log_cap);
     L.total = off;
@@ -209,7 +223,7 @@ struct inpaint_ctx {
     inpaint_params p{};
     Layout L{};
     hipStream_t stream = nullptr;
-    hipStream_t cap_stream = nullptr;
+    hipStream_t cap_stream = nullptr;   // made at the first graph capture
     int device = 0;           // device current at create (the workspace's)
     uint8_t *ws = nullptr;
     int64_t hole0 = 0;
@@ -224,7 +238,7 @@ struct inpaint_ctx {
     int32_t sticky = 0;
     std::string err;
     IterState *h_state = nullptr;   // pinned mirror of the device state
-    uint64_t *h_key = nullptr;      // pinned
+    uint64_t *h_key = nullptr;      // 64 pinned bytes behind it
     hipGraphExec_t graph = nullptr;
     int graph_n = 0;
     inpaint_batch *batch = nullptr;
@@ -509,8 +523,6 @@ static int32_t create_fail(inpaint_ctx *c, int32_t st, const std::string &msg) {
     if (c) {
         if (c->stream) hipStreamSynchronize(c->stream);
         if (c->h_state) hipHostFree(c->h_state);
-        if (c->h_key) hipHostFree(c->h_key);
-        if (c->cap_stream) hipStreamDestroy(c->cap_stream);
         delete c;
     }
     return st;
@@ -544,11 +556,9 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     c->L = L;
     c->stream = (hipStream_t)hip_stream;
     c->ws = (uint8_t *)d_workspace;
-    if (hipHostMalloc((void **)&c->h_state, sizeof(IterState), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&c->h_key, 64, hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc((void **)&c->h_state, sizeof(IterState) + 64, hipHostMallocDefault) != hipSuccess)
         return create_fail(c, INPAINT_OUT_OF_MEMORY, "pinned host allocation failed");
-    if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess)
-        return create_fail(c, INPAINT_DEVICE, "stream creation failed");
+    c->h_key = (uint64_t *)(c->h_state + 1);
     if (hipGetDevice(&c->device) != hipSuccess) return create_fail(c, INPAINT_DEVICE, "no current device");
     // Device address of the allocation-free query's scratch array on this
     // device (taken once per device; a failure only disables that query).
@@ -594,36 +604,12 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     d.norm1 = 255.0;
     d.norm2 = std::sqrt(2.0) * 255.0;
 
-    // Upload: compact RGB(A) rows and the mask into the staging area (the
-    // priority-term plane, unused until the priorities are initialised).
-    const uint64_t n = (uint64_t)W * H;
-    uint8_t *stage_rgb = (uint8_t *)d.pcd;
-    uint8_t *stage_mask = stage_rgb + 4 * n;
-    uint8_t *hdist = d.hdist ? d.hdist : stage_mask + n;
-    hipStream_t s = c->stream;
-    hipError_t e = upload_rows(stage_rgb, (size_t)W * ch, img->data, img->stride_bytes, H, s);
-    if (e == hipSuccess) e = upload_rows(stage_mask, W, mask, mask_stride, H, s);
-    const uint32_t nonce = next_nonce();
-    if (e == hipSuccess) e = launch_init(d, stage_rgb, ch, stage_mask, hdist, nonce, s);
-    if (e == hipSuccess) e = launch_seal(d, nonce, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->h_key, d.info, sizeof(InitInfo), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return create_fail(c, INPAINT_DEVICE, std::string("init: ") + hipGetErrorString(e));
-    InitInfo info;
-    std::memcpy(&info, c->h_key, sizeof(info));
-    if (!sealed(info, nonce, init_pixel_blocks(d)))
-        return create_fail(c, INPAINT_DEVICE, "init kernels did not run to completion (no error was reported)");
-    if (info.hole_count != hm.count || info.bx0 != hm.x0 || info.bx1 != hm.x1 || info.by0 != hm.y0 ||
-        info.by1 != hm.y1)
-        return create_fail(c, INPAINT_DEVICE, "the initialisation read a mask other than the caller's "
-                                              "(its upload had not landed)");
-    c->hole0 = info.hole_count;
-
-    // Search rectangle.
+    // Search rectangle (the mask's box from the host's pass over it; the device
+    // must find the same, below).
     inpaint_rect R{0, 0, W, H};
     if (p->search_mode == INPAINT_SEARCH_ALPHA) {
-        alpha_axis(info.bx0, info.bx1, W, p->alpha_num, p->alpha_den, &R.x0, &R.x1);
-        alpha_axis(info.by0, info.by1, H, p->alpha_num, p->alpha_den, &R.y0, &R.y1);
+        alpha_axis(hm.x0, hm.x1, W, p->alpha_num, p->alpha_den, &R.x0, &R.x1);
+        alpha_axis(hm.y0, hm.y1, H, p->alpha_num, p->alpha_den, &R.y0, &R.y1);
     } else if (p->search_mode == INPAINT_SEARCH_RECT) {
         R.x0 = std::max(p->rect.x0, 0);
         R.y0 = std::max(p->rect.y0, 0);
@@ -644,41 +630,47 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     // Priority blocks: the hole's bbox grown by 2r+1 (how far a fill can
     // change a priority), in 8x8 blocks.
     const int reach = 2 * d.r + 1;
-    d.pbx0 = std::max(info.bx0 - reach, 0) / kBlock;
-    d.pby0 = std::max(info.by0 - reach, 0) / kBlock;
-    d.pbx1 = (std::min(info.bx1 + reach, W) + kBlock - 1) / kBlock;
-    d.pby1 = (std::min(info.by1 + reach, H) + kBlock - 1) / kBlock;
+    d.pbx0 = std::max(hm.x0 - reach, 0) / kBlock;
+    d.pby0 = std::max(hm.y0 - reach, 0) / kBlock;
+    d.pbx1 = (std::min(hm.x1 + reach, W) + kBlock - 1) / kBlock;
+    d.pby1 = (std::min(hm.y1 + reach, H) + kBlock - 1) / kBlock;
     for (d.sshift = 3;; ++d.sshift) {
         d.nsx = (d.pbx1 - d.pbx0 + (1 << d.sshift) - 1) >> d.sshift;
         d.nsy = (d.pby1 - d.pby0 + (1 << d.sshift) - 1) >> d.sshift;
         if ((int64_t)d.nsx * d.nsy <= kMaxSuper) break;
     }
 
-    const uint32_t nonce2 = next_nonce();
-    e = launch_count_valid(d, s);
-    if (e == hipSuccess) e = launch_seal(d, nonce2, s);
+    // Upload: compact RGB(A) rows and the mask into the staging area (the
+    // priority-term plane, unused until the priorities are initialised).  Then
+    // the whole initialisation, up to the first target, with one wait at its
+    // end; nothing here goes by what the device found.
+    const uint64_t n = (uint64_t)W * H;
+    uint8_t *stage_rgb = (uint8_t *)d.pcd;
+    uint8_t *stage_mask = stage_rgb + 4 * n;
+    hipStream_t s = c->stream;
+    hipError_t e = upload_rows(stage_rgb, (size_t)W * ch, img->data, img->stride_bytes, H, s);
+    if (e == hipSuccess) e = upload_rows(stage_mask, W, mask, mask_stride, H, s);
+    const uint32_t nonce = next_nonce();
+    if (e == hipSuccess) e = launch_init(d, stage_rgb, ch, stage_mask, hm.count, L.max_tiles, nonce, s);
+    if (e == hipSuccess) e = launch_count_valid(d, s);
+    if (e == hipSuccess) e = launch_prio_init(d, s);
+    if (e == hipSuccess) e = launch_commit(d, s);  // selects and stages the first target
+    if (e == hipSuccess) e = launch_seal(d, nonce, s);
     if (e == hipSuccess) e = hipMemcpyAsync(c->h_key, d.info, sizeof(InitInfo), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return create_fail(c, INPAINT_DEVICE, std::string("count: ") + hipGetErrorString(e));
+    if (e == hipSuccess) e = c->pull_state();
+    if (e != hipSuccess) return create_fail(c, INPAINT_DEVICE, std::string("init: ") + hipGetErrorString(e));
+    InitInfo info;
     std::memcpy(&info, c->h_key, sizeof(info));
-    if (info.seal != nonce2)
-        return create_fail(c, INPAINT_DEVICE, "the candidate count did not run to completion (no error was reported)");
+    if (!sealed(info, nonce, init_pixel_blocks(d)))
+        return create_fail(c, INPAINT_DEVICE, "init kernels did not run to completion (no error was reported)");
+    if (info.hole_count != hm.count || info.bx0 != hm.x0 || info.bx1 != hm.x1 || info.by0 != hm.y0 ||
+        info.by1 != hm.y1)
+        return create_fail(c, INPAINT_DEVICE, "the initialisation read a mask other than the caller's "
+                                              "(its upload had not landed)");
+    c->hole0 = info.hole_count;
     if (info.valid_count <= 0)
         return create_fail(c, INPAINT_INVALID_ARGUMENT, "no valid source centre in the search rectangle");
     c->candidates = info.valid_count;
-
-    IterState &h = *c->h_state;
-    std::memset(&h, 0, sizeof(h));
-    h.remaining = c->hole0;
-    h.iter = 0;
-    h.iter_limit = INT64_MAX;
-    e = hipMemcpyAsync(d.st, &h, sizeof(IterState), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(d.sync, 0, sizeof(FillSync), s);
-    if (e == hipSuccess) e = hipMemsetAsync(d.fslot, 0, 8 * (size_t)L.max_tiles, s);
-    if (e == hipSuccess) e = launch_prio_init(d, s);
-    if (e == hipSuccess) e = launch_commit(d, s);  // selects and stages the first target
-    if (e == hipSuccess) e = c->pull_state();
-    if (e != hipSuccess) return create_fail(c, INPAINT_DEVICE, std::string("first select: ") + hipGetErrorString(e));
     if (c->h_state->error) return create_fail(c, INPAINT_DEVICE, "device error during the first selection");
     if (!c->h_state->pending && !c->h_state->done)
         return create_fail(c, INPAINT_DEVICE, "the first selection did not run (no error was reported)");
@@ -862,7 +854,10 @@ static hipError_t ensure_graph(inpaint_ctx *ctx, int G) {
         ctx->graph = nullptr;
     }
     hipGraph_t g = nullptr;
-    hipError_t e = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal);
+    hipError_t e = hipSuccess;
+    if (!ctx->cap_stream) e = hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking);
+    if (e != hipSuccess) return e;
+    e = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal);
     for (int i = 0; i < G && e == hipSuccess; ++i) e = enqueue_iteration(ctx, ctx->cap_stream);
     hipError_t e2 = hipStreamEndCapture(ctx->cap_stream, &g);
     if (e == hipSuccess) e = e2;
@@ -959,17 +954,31 @@ int32_t inpaint_read_image(inpaint_ctx *ctx, uint8_t *rgb, int32_t stride) {
     if (ctx->sticky) return ctx->sticky;
     const int W = ctx->d.W, H = ctx->d.H;
     if (stride < 3 * W) return ctx->fail(INPAINT_INVALID_ARGUMENT, "stride smaller than a row");
-    std::vector<uint32_t> tmp((size_t)W * H);
-    HIP_OR_FAIL(ctx, hipMemcpyAsync(tmp.data(), ctx->d.img, tmp.size() * 4, hipMemcpyDeviceToHost, ctx->stream), "copy");
-    HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "sync");
-    for (int y = 0; y < H; ++y)
-        for (int x = 0; x < W; ++x) {
-            const uint32_t v = tmp[(size_t)y * W + x];
-            uint8_t *o = rgb + (size_t)y * stride + 3 * x;
-            o[0] = v & 255;
-            o[1] = (v >> 8) & 255;
-            o[2] = (v >> 16) & 255;
+    // Packed on the device, a piece at a time, straight into the caller's rows:
+    // the words' fourth byte is neither moved nor taken out on the host.
+    uint8_t *pack = ctx->ws + ctx->L.pack;
+    const int64_t n = (int64_t)W * H, piece = (int64_t)(kPackBytes / 3);
+    if (stride == 3 * W) {
+        for (int64_t i = 0; i < n; i += piece) {
+            const int64_t c = std::min(piece, n - i);
+            HIP_OR_FAIL(ctx, launch_pack_rgb(ctx->d.img + i, c, pack, ctx->stream), "pack");
+            HIP_OR_FAIL(ctx, hipMemcpyAsync(rgb + 3 * i, pack, 3 * c, hipMemcpyDeviceToHost, ctx->stream), "copy");
         }
+        HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "sync");
+        return INPAINT_OK;
+    }
+    std::vector<uint8_t> tmp((size_t)(3 * std::min(piece, n)));
+    for (int64_t i = 0; i < n; i += piece) {
+        const int64_t c = std::min(piece, n - i);
+        HIP_OR_FAIL(ctx, launch_pack_rgb(ctx->d.img + i, c, pack, ctx->stream), "pack");
+        HIP_OR_FAIL(ctx, hipMemcpyAsync(tmp.data(), pack, 3 * c, hipMemcpyDeviceToHost, ctx->stream), "copy");
+        HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "sync");
+        for (int64_t j = 0; j < c;) {   // whole rows or what this piece holds of them
+            const int64_t y = (i + j) / W, x = (i + j) % W, run = std::min<int64_t>(W - x, c - j);
+            std::memcpy(rgb + (size_t)y * stride + 3 * x, tmp.data() + 3 * j, (size_t)(3 * run));
+            j += run;
+        }
+    }
     return INPAINT_OK;
 }
 
@@ -1019,10 +1028,10 @@ int32_t inpaint_import_state(inpaint_ctx *ctx, const uint8_t *rgb, int32_t rgb_s
     const MaskStats hm = mask_stats(hole, hole_stride, W, H);
     hipStream_t s = ctx->stream;
     // Staging in the priority-term plane (16 bytes per pixel, rebuilt below):
-    // colours [0, 4n), hole [4n, 5n), row distances [5n, 6n), confidences [8n, 16n).
+    // colours [0, 4n), hole [4n, 5n), confidences [8n, 16n).
     const uint64_t n = (uint64_t)W * H;
     uint8_t *stage = (uint8_t *)d.pcd;
-    uint8_t *s_rgb = stage, *s_hole = stage + 4 * n, *s_hdist = stage + 5 * n;
+    uint8_t *s_rgb = stage, *s_hole = stage + 4 * n;
     double *s_conf = (double *)(stage + 8 * n);
     HIP_OR_FAIL(ctx, upload_rows(s_rgb, (size_t)W * channels, rgb, rgb_stride, H, s), "upload");
     HIP_OR_FAIL(ctx, upload_rows(s_hole, W, hole, hole_stride, H, s), "upload");
@@ -1044,8 +1053,7 @@ int32_t inpaint_import_state(inpaint_ctx *ctx, const uint8_t *rgb, int32_t rgb_s
                          "checkpoint hole leaves the original hole, or a filled pixel's confidence is not in [0, 1]");
     }
     const uint32_t nonce2 = next_nonce();
-    HIP_OR_FAIL(ctx, launch_import_apply(d, s_rgb, channels, s_hole, s_conf, d.hdist ? d.hdist : s_hdist, nonce2, s),
-                "import");
+    HIP_OR_FAIL(ctx, launch_import_apply(d, s_rgb, channels, s_hole, s_conf, nonce2, s), "import");
     HIP_OR_FAIL(ctx, launch_seal(d, nonce2, s), "import");
     HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_key, d.info, sizeof(InitInfo), hipMemcpyDeviceToHost, s), "import");
     HIP_OR_FAIL(ctx, hipStreamSynchronize(s), "import");
@@ -1108,7 +1116,6 @@ int32_t inpaint_destroy(inpaint_ctx *ctx) {
     for (auto ev : ctx->ev1) hipEventDestroy(ev);
     if (ctx->cap_stream) hipStreamDestroy(ctx->cap_stream);
     if (ctx->h_state) hipHostFree(ctx->h_state);
-    if (ctx->h_key) hipHostFree(ctx->h_key);
     delete ctx;
     return INPAINT_OK;
 }
