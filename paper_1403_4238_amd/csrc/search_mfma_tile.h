@@ -236,21 +236,26 @@ __device__ __forceinline__ uint64_t score_tile_rows(const JobDev &d, const FragT
             al[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a2, bl[dy >> 1], al[s], 0, 0, 0);
         }
     }
-    const uint32_t base = (uint32_t)(t2 + kk * (256 * 128 + 128));
-    uint64_t best = ~0ull;
+    // SSD = base + al - 2 acc.  The lane's candidates share a column and its
+    // bits run down the rows, so the first minimum is that of (SSD - base +
+    // kBias, bit) packed in one word: -base <= SSD - base <= 3 P^2 255^2, and
+    // both fit 28 bits with the bias at every radius.  One word per candidate
+    // in place of a 64-bit key, a compare and two selects: 6 instructions of 14.
+    constexpr int kBias = 1 << 25;
+    static_assert(P * P * (49152 + 256 * 128 + 128) < kBias && kBias + 3 * 255 * 255 * P * P < (1 << 28), "28 + 4 bits");
+    const uint32_t gone = ~vmask;
+    uint32_t low = ~0u;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (vmask & (1u << (4 * i + s))) {
-                const uint32_t ssd = base + (uint32_t)(al[s][i] - 2 * acc[s][i]);
-                const int y = ty0 + 16 * g + 4 * i + s;
-                const uint64_t key = ((uint64_t)ssd << 32) | (uint32_t)(y * W + cx);
-                best = key < best ? key : best;
-            }
+            const uint32_t j = 4 * i + s, v = (uint32_t)(al[s][i] - 2 * acc[s][i] + kBias);
+            low = min(low, v << 4 | j | (uint32_t)((int)(gone << (31 - j)) >> 31));
         }
     }
-    return best;
+    const int base = t2 + kk * (256 * 128 + 128) - kBias;
+    const uint32_t ssd = (low >> 4) + (uint32_t)base, y = (uint32_t)(ty0 + 16 * g) + (low & 15u);
+    return vmask ? (uint64_t)ssd << 32 | (y * (uint32_t)W + (uint32_t)cx) : ~0ull;
 }
 
 }  // namespace mtile
