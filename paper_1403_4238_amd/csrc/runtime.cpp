@@ -580,9 +580,9 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     d.qtgt = (TargetStage *)(ws + L.qtgt);
     // AUTO searches on the matrix cores wherever that search can run: a
     // candidate's whole window is scored (INTERSECT counts per pixel) and the
-    // caller asks for no SIMT tile height.  A search launch at 1080p takes 9
-    // (9x9) to 25 us less than the SIMT one, a persistent removal half the
-    // time, at every size from 128 x 96 up.
+    // caller asks for no SIMT tile height.  Per iteration, SIMT against MFMA:
+    // persistent 1080p 15.1 / 8.2 us (9x9) and 28.0 / 9.4 (11x11), 480x639
+    // 17x17 44.9 / 16.3; plain 640x480 30.6 / 27.6, 128x96 33 / 28.
     d.mfma = p->path == INPAINT_PATH_MFMA ||
              (p->path == INPAINT_PATH_AUTO && p->scoring == INPAINT_SCORE_WHOLE && p->tile_rows == 0);
     d.srcp = (uint32_t *)(ws + L.srcp);
