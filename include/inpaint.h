@@ -347,8 +347,9 @@ typedef struct {
     int32_t autotune;        /* 1 = time tile shapes and the persistent grid */
                              /*   of the graph form on first use, 0 = defaults */
     int32_t form;            /* 0 = PERSISTENT once the running images fit  */
-                             /*   a few tiles per search work-group (4),    */
-                             /*   else GRAPH; or                            */
+                             /*   a few tiles per search work-group (12     */
+                             /*   MFMA tiles, 16 with several radii, 4 SIMT */
+                             /*   tiles), else GRAPH; or                    */
                              /*   INPAINT_FORM_GRAPH / INPAINT_FORM_PERSISTENT */
                              /*   (a step that does not fit then fails with  */
                              /*   INVALID_ARGUMENT)                          */

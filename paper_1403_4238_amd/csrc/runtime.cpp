@@ -1424,14 +1424,32 @@ struct MultiGroupPlan {
     std::vector<int> radius;
 };
 
+// The (image, tile) items a search work-group may have, by its dispatch: MFMA
+// tiles of one radius, of several, SIMT tiles.
+struct ItemLimits {
+    int mfma, mixed, simt;
+};
+static ItemLimits same_limits(int n) { return {n, n, n}; }
+
+// AUTO steps the batched persistent form once every search work-group has at
+// most this many items.  With more, the graph form's many small search
+// work-groups hide the restaging better than the few resident ones do.
+// Limits 4, 8, 12, 16, a batch of 64 uneven images to the end, ms:
+//   MFMA 9x9     126, 104, 101, 107      3x3  580, 536, 544, 597
+//   MFMA 13x13   64, 59, 60, 63        17x17  72, 60, 56, 56
+//   radii 1-5    534, 389, 354, 320 (the graph form searches one radius
+//                after another; with 16 the batch never steps it)
+//   SIMT 9x9     160 at 4, 189 at 16
+constexpr ItemLimits kAutoItems{12, 16, 4};
+
 // Splits jobs (slot, context) into batched persistent dispatches: the
 // MFMA-form jobs of radius up to kMultiMixMaxR share one (the mixed-radius
 // kernel) when they have several radii, the others go by (search form,
 // radius).  Each dispatch has its committers first, then every remaining
-// co-resident work-group searching, each with at most max_items items.
+// co-resident work-group searching, each with at most the limit's items.
 // Returns false when a dispatch does not fit.
 static bool group_multi(inpaint_batch *b, const std::vector<std::pair<int, const inpaint_ctx *>> &jobs,
-                        int max_items, std::vector<MultiGroupPlan> *plans) {
+                        ItemLimits limits, std::vector<MultiGroupPlan> *plans) {
     std::set<int> mix_radii;
     for (const auto &j : jobs)
         if (multi_form(j.second) && j.second->d.r <= kMultiMixMaxR) mix_radii.insert(j.second->d.r);
@@ -1448,6 +1466,7 @@ static bool group_multi(inpaint_batch *b, const std::vector<std::pair<int, const
         const int cap = it != b->mcap.end() ? it->second : (b->mcap[kv.first] = multi_capacity(pl.mfma, pl.r));
         const int n_commit = (int)kv.second.size();
         pl.n_search = cap - n_commit;
+        const int max_items = !pl.mfma ? limits.simt : pl.r == kMultiMixed ? limits.mixed : limits.mfma;
         for (const auto &j : kv.second) {
             const JobDev d = multi_desc(j.second);
             const int nt = d.ntx * d.nty;
@@ -1483,21 +1502,15 @@ static std::vector<std::pair<int, const inpaint_ctx *>> running_jobs(const inpai
     return jobs;
 }
 
-// AUTO steps the batched persistent form once every search work-group has at
-// most this many (image, tile) items (a group with several restages a tile
-// per item and iteration; the graph form restages every tile every
-// iteration, so a few items per group are still the cheaper of the two).
-constexpr int kAutoPersistentItems = 4;
-
 // Plans the batched persistent dispatches of the running jobs (group_multi)
 // and uploads the slot table with each job's persistent tiling.  *fits =
 // false when a dispatch does not fit (the batch then steps in the graph
-// form).  max_items: search items per search group allowed (1: every tile
+// form).  limits: search items per search group allowed (1: every tile
 // stays in LDS for the whole dispatch).
-hipError_t plan_multi(inpaint_batch *b, int max_items, bool *fits) {
+hipError_t plan_multi(inpaint_batch *b, ItemLimits limits, bool *fits) {
     *fits = false;
     const auto jobs = running_jobs(b);
-    std::string sig = std::to_string(max_items) + "/";
+    std::string sig = std::to_string(limits.mfma) + "/";
     for (const auto &j : jobs) sig += std::to_string(j.first) + ":" + std::to_string((uintptr_t)j.second) + ",";
     if (!b->dirty && b->desc_form == INPAINT_FORM_PERSISTENT && sig == b->multi_sig) {
         *fits = true;
@@ -1505,7 +1518,7 @@ hipError_t plan_multi(inpaint_batch *b, int max_items, bool *fits) {
     }
     if (!b->dirty && sig == b->nofit_sig) return hipSuccess;
     std::vector<MultiGroupPlan> plans;
-    if (!group_multi(b, jobs, max_items, &plans)) {
+    if (!group_multi(b, jobs, limits, &plans)) {
         b->nofit_sig = sig;
         return hipSuccess;
     }
@@ -1664,14 +1677,11 @@ int32_t inpaint_batch_step(inpaint_batch *b, int32_t G, int64_t *active) {
     SharedDevice lock(g_device_mu);
     hipError_t e = hipSuccess;
     if (b->bp.form != INPAINT_FORM_GRAPH) {
-        // AUTO takes the persistent form only while every search tile of
-        // the running images can stay in LDS for the whole dispatch: with
-        // more tiles than search groups the tiles are re-staged for every
-        // target, and the graph form's many small search work-groups hide
-        // that latency better.  So a large batch starts in the graph form
-        // and its tail, when few images are left, runs persistent.
+        // AUTO takes the persistent form while a search work-group has few
+        // items (kAutoItems): a very large batch starts in the graph form,
+        // and runs persistent once enough of its images are done.
         bool fits = false;
-        e = plan_multi(b, b->bp.form == INPAINT_FORM_PERSISTENT ? kMultiMaxItems : kAutoPersistentItems, &fits);
+        e = plan_multi(b, b->bp.form == INPAINT_FORM_PERSISTENT ? same_limits(kMultiMaxItems) : kAutoItems, &fits);
         if (e != hipSuccess) return INPAINT_DEVICE;
         if (fits) {
             b->dirty = false;
@@ -1744,7 +1754,7 @@ int32_t inpaint_batch_room(inpaint_batch *b, const inpaint_ctx *ctx, int32_t til
     auto jobs = running_jobs(b);
     jobs.push_back({(int)b->slots.size(), ctx});   // (a slot index no running job uses)
     std::vector<MultiGroupPlan> plans;
-    *room = group_multi(b, jobs, tiles_per_group, &plans) ? 1 : 0;
+    *room = group_multi(b, jobs, same_limits(tiles_per_group), &plans) ? 1 : 0;
     return INPAINT_OK;
 }
 

@@ -6,6 +6,7 @@ import pytest
 import oracle
 from paper_1403_4238_amd import synth
 
+from _util import assert_logs_equal
 from test_parity_gpu import B, _built, _full_run_parity, _pair  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -82,3 +83,30 @@ def test_large_radii_several_tiles_per_group(r):
     for f in na[2].dtype.names:
         assert na[2][f].tobytes() == nb[2][f].tobytes(), f
     assert (a.read_image() == b.read_image()).all()
+
+
+@pytest.mark.parametrize("path,n,radii,first", [("auto", 32, (4,), "persistent"), ("mfma", 64, (4,), "graph"),
+                                                 ("simt", 32, (4,), "graph"), ("auto", 32, (1, 3, 5), "persistent")])
+def test_auto_batch_form_by_items_per_group(path, n, radii, first):
+    # Either side of AUTO's line between the batch forms (12 MFMA items per
+    # search work-group, 16 with several radii, 4 SIMT ones): the form of the
+    # first step, and each log's head against the image stepped alone.
+    jobs = synth.batch()[:n]
+    pid = {"auto": B.PATH_AUTO, "mfma": B.PATH_MFMA, "simt": B.PATH_SIMT}[path]
+    rs = [radii[i % len(radii)] for i in range(n)]
+    batch = B.Batch(capacity=n, graph_iters=6, autotune=False, form="auto")
+    ctxs = [B.Inpainter(j.rgb, j.mask, r, path=pid) for j, r in zip(jobs, rs)]
+    for c in ctxs:
+        batch.attach(c)
+    batch.step()
+    assert batch.last_form() == first
+    batch.step()
+    for i in range(0, n, 5):
+        alone = B.Inpainter(jobs[i].rgb, jobs[i].mask, rs[i], path=B.PATH_SIMT)
+        alone.run(max_iters=12)
+        assert_logs_equal(ctxs[i].read_log(0, 12), alone.read_log(0, 12), jobs[i].name)
+        alone.close()
+    for c in ctxs:
+        batch.detach(c)
+        c.close()
+    batch.close()
