@@ -24,6 +24,7 @@ constexpr int kMfmaMaxRadius = 8;     // int8-MFMA search: the band of 16 column
 constexpr int kMfmaPathRadius = 6;    // largest radius INPAINT_PATH_MFMA is accepted for
 constexpr int kMfmaTileRows = 16;     // MFMA search tile: 64 x 64 candidates
 constexpr int kFillTileRows = 8;      // persistent fill: candidate rows per search thread
+constexpr int kDefaultTileRows = 8;   // the SIMT search with tile_rows 0
 
 // Padding of the static search planes (srcp, vradp) around the
 // image, in pixels: every staged search window -- a tile of up to 64 x 64
@@ -259,6 +260,18 @@ hipError_t launch_fill_multi(const MultiPlan &m, bool mfma, int r, int grid, int
 
 inline int search_tile_h(int tile_rows) { return kSearchWaves * tile_rows; }
 
+// Search tiles over the candidate rect [rx0, rx1) x [ry0, ry1); mfma_r > 0
+// selects the MFMA tiling of that radius (from an aligned first column).
+struct Tiling {
+    int ntx, nty;
+    int64_t count() const { return (int64_t)ntx * nty; }
+};
+inline Tiling tiling(int rx0, int ry0, int rx1, int ry1, int tile_rows, int mfma_r = 0) {
+    if (rx1 <= rx0 || ry1 <= ry0) return {0, 0};
+    const int tx0 = mfma_r > 0 ? mfma_tile_x0(rx0, mfma_r) : rx0;
+    return {(rx1 - tx0 + kTileW - 1) / kTileW, (ry1 - ry0 + search_tile_h(tile_rows) - 1) / search_tile_h(tile_rows)};
+}
+
 // Allocation-free query (inpaint_find_exemplar_static): its target stage,
 // per-tile partial minima and result key live in one static device array of
 // kStaticScratchBytes per GPU instead of the workspace.
@@ -267,6 +280,29 @@ constexpr uint64_t kStaticStageOff = 0;
 constexpr uint64_t kStaticKeyOff = (sizeof(TargetStage) + 255) / 256 * 256;
 constexpr uint64_t kStaticPartialsOff = kStaticKeyOff + 256;
 constexpr uint64_t kStaticScratchBytes = kStaticPartialsOff + 8ull * kStaticMaxTiles;
+
+// The search of an allocation-free query of radius r on a context of path
+// `path` (mfma: it searches on the matrix cores; its tile height is
+// tile_rows).  A rect is accepted by the count of one tiling of its path: the
+// MFMA tiling for MFMA up to kMfmaPathRadius, else the SIMT one (AUTO: of the
+// default height).  The MFMA tiling may start up to 7 columns left of the
+// rect; where that takes it past the scratch on an accepted rect, the SIMT
+// search runs, so the tiles launched never outnumber the partials.
+struct StaticRoute {
+    bool ok, mfma;
+    int tile_rows;
+    Tiling t;
+};
+inline StaticRoute static_route(int path, bool mfma, int tile_rows, int r, int rx0, int ry0, int rx1, int ry1) {
+    const int rows = mfma && path == INPAINT_PATH_AUTO ? kDefaultTileRows : tile_rows;
+    const Tiling simt = tiling(rx0, ry0, rx1, ry1, rows);
+    if (!mfma) return {simt.count() <= kStaticMaxTiles, false, rows, simt};
+    const Tiling mt = tiling(rx0, ry0, rx1, ry1, kMfmaTileRows, r);
+    const bool by_mfma = path == INPAINT_PATH_MFMA && r <= kMfmaPathRadius;
+    if ((by_mfma ? mt : simt).count() > kStaticMaxTiles) return {false, false, rows, simt};
+    if (mt.count() > kStaticMaxTiles) return {true, false, rows, simt};
+    return {true, true, kMfmaTileRows, mt};
+}
 // Takes the array's device address on `device`, which must be current
 // (once per device; later calls return the first result).
 hipError_t static_scratch_setup(int device);

@@ -32,7 +32,6 @@ namespace {
 thread_local std::string g_create_error;
 
 constexpr uint64_t kAlign = 256;
-constexpr int kDefaultTileRows = 8;
 constexpr uint64_t kPackBytes = 3 << 18;   // packed pixels read back at a time (2^18 of them)
 constexpr int kMaxGroups = 4096;   // work-groups of a persistent dispatch (co-resident: <= 4 per CU)
 
@@ -510,12 +509,10 @@ static void kernel_rect(int W, int H, int r, const inpaint_rect &img_rect, int *
 // Search tiles over the kernel rect; mfma_r > 0 selects the MFMA tiling of
 // that radius (64 x 64 tiles from an aligned first column).
 static void set_tiles(JobDev &d, int tile_rows, int mfma_r = 0) {
+    const Tiling t = tiling(d.rx0, d.ry0, d.rx1, d.ry1, tile_rows, mfma_r);
     d.tile_rows = tile_rows;
-    const int rw = std::max(d.rx1 - d.rx0, 0), rh = std::max(d.ry1 - d.ry0, 0);
-    const int tx0 = mfma_r > 0 ? mfma_tile_x0(d.rx0, mfma_r) : d.rx0;
-    d.ntx = (std::max(d.rx1 - tx0, 0) + kTileW - 1) / kTileW;
-    d.nty = (rh + search_tile_h(tile_rows) - 1) / search_tile_h(tile_rows);
-    if (rw == 0 || rh == 0) d.ntx = d.nty = 0;
+    d.ntx = t.ntx;
+    d.nty = t.nty;
 }
 
 static int32_t create_fail(inpaint_ctx *c, int32_t st, const std::string &msg) {
@@ -751,20 +748,19 @@ int32_t inpaint_find_exemplar_static(inpaint_ctx *ctx, int32_t tx, int32_t ty, i
     q.ry0 = k[1];
     q.rx1 = k[2];
     q.ry1 = k[3];
-    const bool mfma = ctx->mfma && mfma_supported(r);
-    set_tiles(q, d.tile_rows, mfma ? r : 0);
-    // (AUTO's limit is that of the default SIMT tile, whichever search runs)
-    JobDev lim = q;
-    if (mfma && ctx->p.path == INPAINT_PATH_AUTO) set_tiles(lim, kDefaultTileRows);
-    if ((int64_t)lim.ntx * lim.nty > kStaticMaxTiles)
+    const StaticRoute route = static_route(ctx->p.path, ctx->mfma, d.tile_rows, r, k[0], k[1], k[2], k[3]);
+    if (!route.ok)
         return ctx->fail(INPAINT_INVALID_ARGUMENT, "search rect needs more than " + std::to_string(kStaticMaxTiles) +
                                                        " search tiles (the static scratch limit)");
+    q.tile_rows = route.tile_rows;
+    q.ntx = route.t.ntx;
+    q.nty = route.t.nty;
     q.qtgt = (TargetStage *)(base + kStaticStageOff);
     q.partials = (uint64_t *)(base + kStaticPartialsOff);
     uint64_t *dkey = (uint64_t *)(base + kStaticKeyOff);
     hipStream_t s = ctx->stream;
     HIP_OR_FAIL(ctx, launch_stage_query(q, tx, ty, r, s), "stage");
-    if (mfma)
+    if (route.mfma)
         HIP_OR_FAIL(ctx, launch_search_mfma(q, true, r, q.rx0, q.ry0, q.rx1, q.ry1, q.ntx, q.nty, s), "search");
     else if (ctx->direct)
         HIP_OR_FAIL(ctx, launch_search_direct(q, true, r, q.rx0, q.ry0, q.rx1, q.ry1, q.tile_rows, q.ntx, q.nty, s),
