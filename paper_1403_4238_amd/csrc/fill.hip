@@ -825,6 +825,9 @@ __device__ __forceinline__ void collect_slots(const uint64_t *fs, int ntiles, ui
     }
 }
 
+// A word of a StepRec, whose fields are wider.
+typedef uint32_t __attribute__((may_alias)) RecordWord;
+
 // LDS of the persistent committer: the commit's, the superblock maxima (the
 // scan of the blocks that keep their priorities reads them every iteration)
 // and the last record.
@@ -883,7 +886,7 @@ __device__ __forceinline__ void fill_commit(const JobDev &d, int ntiles, int n_i
         if (k == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the slot resets
         publish_go(sy, stop ? go_stop(epoch) : go_word(epoch, k + 1, rec_tag(v.iter)));
         if (logged && tid >= T - 64 && tid < T - 64 + (int)sizeof(StepRec) / 4 && v.iter <= d.log_cap)
-            ((uint32_t *)&d.log[v.iter - 1])[tid - (T - 64)] = ((const uint32_t *)&C.last)[tid - (T - 64)];
+            ((RecordWord *)&d.log[v.iter - 1])[tid - (T - 64)] = ((const RecordWord *)&C.last)[tid - (T - 64)];
         logged = false;
         if (stale) update_blocks<R>(tid, d, g, L, C.sup);
         stale = false;
@@ -945,11 +948,11 @@ __device__ __forceinline__ void fill_commit(const JobDev &d, int ntiles, int n_i
         v.iter += 1;
         v.remaining = remaining;
         v.pending = 0;
+        lds_barrier();   // also publishes C.last to the lanes that log it
         if (remaining == 0) {
             v.done = 1;
             continue;
         }
-        lds_barrier();
         refresh_grads<R>(tid, d, px, py, L);
         lds_barrier();
         data_terms<R>(tid, d, px, py, g, L);

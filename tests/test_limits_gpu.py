@@ -2,7 +2,9 @@
 import numpy as np
 import pytest
 
-from test_parity_gpu import B, _built  # noqa: F401
+from paper_1403_4238_amd import synth
+
+from test_parity_gpu import B, _built, _full_run_parity  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +27,20 @@ def test_static_query_of_as_many_tiles_as_the_scratch_holds():
         g.find_exemplar_static(1000, 4, r, (10, 0, W, H))
     assert e.value.status == B.INVALID_ARGUMENT
     g.close()
+
+
+# The last record of a dispatch that empties the hole follows its iteration
+# with no barrier of the next one between; here it is also the first record.
+@pytest.mark.parametrize("r", range(1, 9))
+@pytest.mark.parametrize("path", ["auto", "simt"])
+def test_record_of_an_iteration_that_empties_the_hole(r, path):
+    import torch
+    mask = np.zeros((70, 90), np.uint8)
+    mask[30:30 + min(r + 1, 6), 40] = 1   # within the patch of its every pixel
+    job = synth.Job("one", _noise(90, 70, r), mask, r)
+    for iters in (1, 64):
+        stale = torch.full((4 << 20,), 0xAB, dtype=torch.uint8, device="cuda")   # the workspace's block
+        del stale
+        log = _full_run_parity(job, "one iteration r=%d" % r, path={"auto": B.PATH_AUTO, "simt": B.PATH_SIMT}[path],
+                               form="persistent", iters_per_check=iters)
+        assert len(log) == 1
