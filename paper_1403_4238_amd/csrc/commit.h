@@ -70,7 +70,8 @@ __device__ __forceinline__ int gray_of(uint32_t w) {
 // give the same isophote).  In global memory a known pixel's gradient sits in
 // the priority terms' D, which only front pixels, never known ones, use.
 __device__ __forceinline__ uint32_t pack_grad(int gx, int gy) { return (uint32_t)(gx & 0xffff) | (uint32_t)gy << 16; }
-__device__ __forceinline__ uint32_t *grad_word(double2 *cd) { return (uint32_t *)&cd->y; }
+typedef const uint32_t __attribute__((may_alias)) GradWord;   // read there
+__device__ __forceinline__ GradWord *grad_word(const double2 *cd) { return (GradWord *)&cd->y; }
 __device__ __forceinline__ double2 off_front(uint32_t grad) {
     return make_double2(-1.0, __longlong_as_double((long long)grad));
 }
@@ -263,7 +264,8 @@ __device__ __forceinline__ Best gather(int tid, const JobDev &d, int px, int py,
                        ky0 + KR <= d.H;
     if (inner) {
         const int64_t o = (int64_t)oy * W + ox, ko = (int64_t)ky0 * W + kx0;
-        const uint32_t *pi = d.img + o, *pg = grad_word(d.pcd + o);
+        const uint32_t *pi = d.img + o;
+        GradWord *pg = grad_word(d.pcd + o);
         const double *pc = d.conf + o;
         const double2 *pk = d.pcd + ko;
 #pragma unroll
@@ -272,7 +274,7 @@ __device__ __forceinline__ Best gather(int tid, const JobDev &d, int px, int py,
             const uint32_t i = (uint32_t)(t / S::cols) * (uint32_t)W + (uint32_t)(t % S::cols);
             im[k] = *(const uint32_t *)((const char *)pi + 4 * i);
             c[k] = *(const double *)((const char *)pc + 8 * i);
-            gr[k] = *(const uint32_t *)((const char *)pg + 16 * i);
+            gr[k] = *(GradWord *)((const char *)pg + 16 * i);
         }
 #pragma unroll
         for (int k = 0; k < KIT; ++k) {
@@ -349,10 +351,11 @@ struct FillSlots {
 };
 
 // The target patch's hole pixels take the target's confidence and leave the
-// hole and the front, in device memory and LDS; their colours follow with
-// copy_colours.  keep(t): whether hole slot t is filled (INTERSECT scoring
-// fills only those whose source pixel qualifies).  L.cnt gets each wave's
-// count of filled slots.
+// hole and, in LDS, the front; their colours follow with copy_colours, their
+// terms in device memory with refresh_grads (one writer: nothing orders two
+// waves' stores to one word within an iteration).  keep(t): whether hole slot
+// t is filled (INTERSECT scoring fills only those whose source pixel
+// qualifies).  L.cnt gets each wave's count of filled slots.
 template <int R, class Keep>
 __device__ __forceinline__ FillSlots mark_filled(int tid, const JobDev &d, int px, int py, double C, const Refresh &g,
                                                  CommitLds<R> &L, Keep keep) {
@@ -372,7 +375,6 @@ __device__ __forceinline__ FillSlots mark_filled(int tid, const JobDev &d, int p
             const uint32_t dst = (uint32_t)(y * d.W + x);
             d.conf[dst] = C;
             d.hole[dst] = 0;
-            d.pcd[dst] = off_front(0);
             L.img[li] = 0;
             L.conf[li] = C;
             L.bkey[(y - 8 * g.aby0) * S::BP + (x - 8 * g.abx0)] = -1;
@@ -389,7 +391,8 @@ __device__ __forceinline__ int filled_count(const int *cnt) { return cnt[0] + cn
 // in-image 4-neighbour) go to a compact list, one atomic per wave.  Pixels
 // off the front already carry C = -1 in global memory and key -1 in LDS: a
 // hole pixel off the front has never been on it (the front only gains hole
-// pixels), a known one was set when it was filled or at initialisation.
+// pixels), a known one was set when it was filled or at initialisation (one
+// that this iteration fills gets C = -1 with its gradient).
 //
 // PATCH: the target's whole patch counts as known, so the list does not wait
 // for mark_filled, which clears those pixels at the same time.
@@ -492,7 +495,9 @@ __device__ __forceinline__ void copy_colours(int tid, const JobDev &d, int px, i
     }
 }
 
-// Gradients the copy changed: those within one pixel of the patch.
+// Gradients the copy changed: those within one pixel of the patch, which holds
+// every pixel that left the front.  An iteration that empties the hole skips
+// this: no later one reads its terms, and an import forms them all again.
 template <int R>
 __device__ __forceinline__ void refresh_grads(int tid, const JobDev &d, int px, int py, CommitLds<R> &L) {
     using S = Stage<R>;
@@ -506,7 +511,7 @@ __device__ __forceinline__ void refresh_grads(int tid, const JobDev &d, int px, 
             const uint32_t any = (L.img[li] | L.img[li + 1] | L.img[li - 1] | L.img[li + S::pitch] | L.img[li - S::pitch]) >> 24;
             const uint32_t v = any == 0 ? pack_grad((int)gp[1] - (int)gp[-1], (int)gp[G] - (int)gp[-G]) : 0u;
             L.grad[li] = v;
-            if (state_of(L.img[li]) == 0) *grad_word(d.pcd + (uint32_t)((py + dy) * d.W + (px + dx))) = v;
+            if (state_of(L.img[li]) == 0) d.pcd[(uint32_t)((py + dy) * d.W + (px + dx))] = off_front(v);
         }
     }
 }
