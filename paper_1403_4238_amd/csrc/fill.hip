@@ -400,7 +400,10 @@ __global__ __launch_bounds__(256) void k_init_planes(JobDev d, uint8_t *hdist) {
     constexpr int TH = 16, RD = 9;
     __shared__ uint8_t hd[TH + 2 * RD][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int x0 = (int)blockIdx.x * 64 - kPadL, y0 = (int)blockIdx.y * TH - kPadT, x = x0 + lane;
+    // (a grid of one dimension: images that are accepted have more rows of tiles
+    // than the 65535 that the second one is documented to take)
+    const int nx = (d.pitch + 63) / 64;
+    const int x0 = (int)(blockIdx.x % nx) * 64 - kPadL, y0 = (int)(blockIdx.x / nx) * TH - kPadT, x = x0 + lane;
     const auto bad = [&](int px, int py) { return !in_img(d, px, py) || d.hole[(int64_t)py * d.W + px] != 0; };
     for (int r = wave; r < TH + 2 * RD; r += 4) {
         const int y = y0 - RD + r;
@@ -1644,7 +1647,7 @@ uint32_t init_pixel_blocks(const JobDev &d) {
 }
 
 static void launch_planes(const JobDev &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_init_planes, dim3(blocks_for(d.pitch, 64), blocks_for(padded_rows(d.H), 16)), dim3(256), 0, s, d,
+    hipLaunchKernelGGL(k_init_planes, dim3(blocks_for(d.pitch, 64) * blocks_for(padded_rows(d.H), 16)), dim3(256), 0, s, d,
                        d.hdist);
 }
 

@@ -44,3 +44,14 @@ def test_record_of_an_iteration_that_empties_the_hole(r, path):
         log = _full_run_parity(job, "one iteration r=%d" % r, path={"auto": B.PATH_AUTO, "simt": B.PATH_SIMT}[path],
                                form="persistent", iters_per_check=iters)
         assert len(log) == 1
+
+
+# More rows of 64 x 16 tiles of the padded planes than a grid's second dimension
+# takes; the search rect keeps the oracle's search small.
+def test_very_tall_image():
+    W, H, r = 17, 1_100_000, 2
+    rgb = _noise(W, H, 3)
+    mask = np.zeros((H, W), np.uint8)
+    mask[H - 9:H - 5, 8:13] = 1
+    job = synth.Job("tall", rgb, mask, r, search_mode=synth.SEARCH_RECT, rect=(0, H - 300, W, H))
+    _full_run_parity(job, "tall", form="persistent", iters_per_check=8)
