@@ -336,7 +336,9 @@ const char *inpaint_last_error(const inpaint_ctx *ctx);
  *    radius) runs all G iterations of every image; one work-group per image
  *    commits (front, priority, copy), every other co-resident work-group
  *    searches (image, tile) items of whichever image has a staged target.
- *    Images of up to 64 tiles per search work-group.
+ *    Images of up to 64 tiles per search work-group; at most half of the
+ *    co-resident work-groups commit.  Images of path AUTO that do not fit on
+ *    the matrix cores take the SIMT search.
  *  - GRAPH: per iteration, a persistent search kernel over a static (image,
  *    tile) work list, then one commit work-group per image; G iterations are
  *    captured once into a hipGraph and replayed.  Tile shape and grid may be

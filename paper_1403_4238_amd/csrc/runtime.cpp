@@ -1401,12 +1401,17 @@ hipError_t grow(T **p, size_t *cap, size_t n) {
     return hipMalloc((void **)p, *cap * sizeof(T));
 }
 
-bool multi_form(const inpaint_ctx *c) { return c->mfma && mfma_supported(c->d.r); }
+// Whether the batched persistent dispatch searches a job on the matrix cores;
+// with auto_simt those of path AUTO go to the SIMT form.
+bool multi_form(const inpaint_ctx *c, bool auto_simt) {
+    return c->mfma && mfma_supported(c->d.r) && !(auto_simt && c->p.path == INPAINT_PATH_AUTO);
+}
 
 // A job's JobDev with the tiling of the batched persistent search.
-static JobDev multi_desc(const inpaint_ctx *c) {
+static JobDev multi_desc(const inpaint_ctx *c, bool auto_simt) {
     JobDev d = c->d;
-    set_tiles(d, multi_form(c) ? kMfmaTileRows : kFillTileRows, multi_form(c) ? c->d.r : 0);
+    const bool mfma = multi_form(c, auto_simt);
+    set_tiles(d, mfma ? kMfmaTileRows : kFillTileRows, mfma ? c->d.r : 0);
     return d;
 }
 
@@ -1445,15 +1450,15 @@ constexpr ItemLimits kAutoItems{12, 16, 4};
 // co-resident work-group searching, each with at most the limit's items.
 // Returns false when a dispatch does not fit.
 static bool group_multi(inpaint_batch *b, const std::vector<std::pair<int, const inpaint_ctx *>> &jobs,
-                        ItemLimits limits, std::vector<MultiGroupPlan> *plans) {
+                        ItemLimits limits, bool auto_simt, std::vector<MultiGroupPlan> *plans) {
     std::set<int> mix_radii;
     for (const auto &j : jobs)
-        if (multi_form(j.second) && j.second->d.r <= kMultiMixMaxR) mix_radii.insert(j.second->d.r);
+        if (multi_form(j.second, auto_simt) && j.second->d.r <= kMultiMixMaxR) mix_radii.insert(j.second->d.r);
     std::map<std::pair<int, int>, std::vector<std::pair<int, const inpaint_ctx *>>> groups;
     for (const auto &j : jobs) {
         const inpaint_ctx *c = j.second;
-        const bool mixed = mix_radii.size() > 1 && multi_form(c) && c->d.r <= kMultiMixMaxR;
-        groups[{multi_form(c) ? 1 : 0, mixed ? kMultiMixed : c->d.r}].push_back(j);
+        const bool mfma = multi_form(c, auto_simt), mixed = mix_radii.size() > 1 && mfma && c->d.r <= kMultiMixMaxR;
+        groups[{mfma ? 1 : 0, mixed ? kMultiMixed : c->d.r}].push_back(j);
     }
     plans->clear();
     for (auto &kv : groups) {
@@ -1464,7 +1469,7 @@ static bool group_multi(inpaint_batch *b, const std::vector<std::pair<int, const
         pl.n_search = cap - n_commit;
         const int max_items = !pl.mfma ? limits.simt : pl.r == kMultiMixed ? limits.mixed : limits.mfma;
         for (const auto &j : kv.second) {
-            const JobDev d = multi_desc(j.second);
+            const JobDev d = multi_desc(j.second, auto_simt);
             const int nt = d.ntx * d.nty;
             if (nt > 32 * kCommitThreads || (int64_t)d.W * d.H > (1ll << kSlotIndexBits)) return false;
             pl.jobs.push_back(j.first);
@@ -1489,6 +1494,20 @@ static bool group_multi(inpaint_batch *b, const std::vector<std::pair<int, const
     return true;
 }
 
+// group_multi with AUTO's images on the matrix cores, or, where they do not
+// fit there, on the SIMT search (*auto_simt): at radius 1 to 4 twice as many
+// of its work-groups are co-resident and so twice as many images, and each
+// radius has a dispatch of its own, where the MFMA images of radius 1 to 5
+// share one dispatch and its items per group.
+static bool group_multi_auto(inpaint_batch *b, const std::vector<std::pair<int, const inpaint_ctx *>> &jobs,
+                             ItemLimits limits, bool *auto_simt, std::vector<MultiGroupPlan> *plans) {
+    *auto_simt = false;
+    if (group_multi(b, jobs, limits, false, plans)) return true;
+    for (const auto &j : jobs)
+        if (multi_form(j.second, false) != multi_form(j.second, true)) *auto_simt = true;
+    return *auto_simt && group_multi(b, jobs, limits, true, plans);
+}
+
 // The running jobs of the batch as (slot, context).
 static std::vector<std::pair<int, const inpaint_ctx *>> running_jobs(const inpaint_batch *b) {
     const int32_t *state = (const int32_t *)(b->h_active + 1);
@@ -1498,7 +1517,7 @@ static std::vector<std::pair<int, const inpaint_ctx *>> running_jobs(const inpai
     return jobs;
 }
 
-// Plans the batched persistent dispatches of the running jobs (group_multi)
+// Plans the batched persistent dispatches of the running jobs (group_multi_auto)
 // and uploads the slot table with each job's persistent tiling.  *fits =
 // false when a dispatch does not fit (the batch then steps in the graph
 // form).  limits: search items per search group allowed (1: every tile
@@ -1514,13 +1533,14 @@ hipError_t plan_multi(inpaint_batch *b, ItemLimits limits, bool *fits) {
     }
     if (!b->dirty && sig == b->nofit_sig) return hipSuccess;
     std::vector<MultiGroupPlan> plans;
-    if (!group_multi(b, jobs, limits, &plans)) {
+    bool auto_simt = false;
+    if (!group_multi_auto(b, jobs, limits, &auto_simt, &plans)) {
         b->nofit_sig = sig;
         return hipSuccess;
     }
     std::vector<JobDev> desc(b->slots.size());
     for (size_t i = 0; i < b->slots.size(); ++i)
-        if (b->slots[i]) desc[i] = multi_desc(b->slots[i]);
+        if (b->slots[i]) desc[i] = multi_desc(b->slots[i], auto_simt);
     hipError_t e = hipSuccess;
     for (size_t i = 0; i < b->slots.size() && e == hipSuccess; ++i) {
         if (!b->slots[i]) continue;
@@ -1750,7 +1770,8 @@ int32_t inpaint_batch_room(inpaint_batch *b, const inpaint_ctx *ctx, int32_t til
     auto jobs = running_jobs(b);
     jobs.push_back({(int)b->slots.size(), ctx});   // (a slot index no running job uses)
     std::vector<MultiGroupPlan> plans;
-    *room = group_multi(b, jobs, same_limits(tiles_per_group), &plans) ? 1 : 0;
+    bool auto_simt = false;
+    *room = group_multi_auto(b, jobs, same_limits(tiles_per_group), &auto_simt, &plans) ? 1 : 0;
     return INPAINT_OK;
 }
 

@@ -55,3 +55,40 @@ def test_very_tall_image():
     mask[H - 9:H - 5, 8:13] = 1
     job = synth.Job("tall", rgb, mask, r, search_mode=synth.SEARCH_RECT, rect=(0, H - 300, W, H))
     _full_run_parity(job, "tall", form="persistent", iters_per_check=8)
+
+
+# More AUTO images than the MFMA dispatch has committers for (256 of 512
+# work-groups), of one radius and of the radii that share the mixed dispatch:
+# the persistent form takes them on the SIMT search, and goes over to the
+# matrix cores once enough are done.
+@pytest.mark.parametrize("radii", [(2,), (1, 2, 3, 4, 5)])
+def test_more_auto_images_than_mfma_committers(radii):
+    n, W, H = 300, 48, 40
+    batch = B.Batch(n, 2, form="persistent")
+    jobs = []
+    for i in range(n):
+        mask = np.zeros((H, W), np.uint8)
+        mask[12:14 + 3 * (i % 4), 15 + i % 9:22 + i % 9] = 1
+        jobs.append((_noise(W, H, i), mask, radii[i % len(radii)]))
+    ctxs = [B.Inpainter(*j) for j in jobs]
+    for i, c in enumerate(ctxs):
+        assert batch.room(c, 64), i
+        batch.attach(c)
+    left = n
+    for _ in range(100):
+        left = batch.step()
+        assert batch.last_form() == "persistent"
+        if not left:
+            break
+    assert left == 0
+    for i in range(0, n, 23):
+        alone = B.Inpainter(*jobs[i], path=B.PATH_SIMT)
+        k = alone.run(log_cap=400)[1]
+        assert ctxs[i].progress()[0] == k
+        assert ctxs[i].read_log(0, k).tobytes() == alone.read_log(0, k).tobytes(), i
+        assert (ctxs[i].read_image() == alone.read_image()).all()
+        alone.close()
+    for c in ctxs:
+        batch.detach(c)
+        c.close()
+    batch.close()
