@@ -672,8 +672,21 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     if (!c->h_state->pending && !c->h_state->done)
         return create_fail(c, INPAINT_DEVICE, "the first selection did not run (no error was reported)");
     c->run_form = p->form;
-    if (p->form == INPAINT_FORM_PERSISTENT && !persistent_fits(c) && !setup_multi(c))
-        c->run_form = INPAINT_FORM_STREAM;
+    if (p->form == INPAINT_FORM_PERSISTENT && !persistent_fits(c) && !setup_multi(c)) {
+        // the MFMA tiling may need one more column of tiles than the SIMT one
+        const bool simt = c->mfma && p->path == INPAINT_PATH_AUTO;
+        if (simt) {
+            c->mfma = d.mfma = 0;
+            set_tiles(d, kDefaultTileRows);
+        }
+        if (!simt || (!persistent_fits(c) && !setup_multi(c))) {
+            c->run_form = INPAINT_FORM_STREAM;
+            if (simt) {
+                c->mfma = d.mfma = 1;
+                set_tiles(d, kMfmaTileRows, d.r);
+            }
+        }
+    }
     *out = c;
     return INPAINT_OK;
 }

@@ -92,3 +92,18 @@ def test_more_auto_images_than_mfma_committers(radii):
         batch.detach(c)
         c.close()
     batch.close()
+
+
+# As many SIMT tiles in one row as the persistent form takes (8192); the aligned
+# MFMA tiling has one more, so AUTO keeps the form on the SIMT search.
+@pytest.mark.parametrize("x0,form", [(2, "persistent"), (1, "stream")])
+def test_auto_persistent_at_its_most_tiles(x0, form):
+    W, H, r = 64 * 8192 + 3, 9, 1
+    rgb = _noise(W, H, 5)
+    mask = np.zeros((H, W), np.uint8)
+    mask[4, 300000:300004] = 1
+    job = synth.Job("wide", rgb, mask, r, search_mode=synth.SEARCH_RECT, rect=(x0, 0, W, H))
+    g = B.Inpainter(rgb, mask, r, B.SEARCH_RECT, rect=job.rect, form="persistent", iters_per_check=8)
+    assert g.run_form() == form
+    g.close()
+    _full_run_parity(job, "wide", form="persistent", iters_per_check=8)
