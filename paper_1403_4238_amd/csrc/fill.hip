@@ -617,7 +617,6 @@ __device__ void add_filled_sources(const JobDev &d, const CommitLds<R> &L, int p
         }
         int v = dist - 1;
         v = v < 0 ? 0 : (v > kMaxRadius ? kMaxRadius : v);
-        d.vrad[(int64_t)y * W + x] = (uint8_t)v;
         d.vradp[(int64_t)(y + kPadT) * pitch + (x + kPadL)] = (uint8_t)v;
     }
 }

@@ -131,12 +131,13 @@ struct JobDev {
     uint8_t *gray;       // W*H
     uint8_t *hole;       // W*H, 1 = still to fill
     uint8_t *hole0;      // W*H, 1 = in the original hole (fixed at create)
-    uint8_t *vrad;       // W*H, largest r <= 8 with a valid patch at the centre
+    uint8_t *vrad;       // W*H, largest r <= 8 with a valid patch at the centre, for the count of valid
+                         // centres at create; scratch afterwards
     double *conf;        // W*H
     double2 *pcd;        // W*H (C, D) of front pixels; elsewhere C = -1, and in the priority range
                          // the packed gradient in the low word of D
     BlockBest *blk;      // ceil(W/8)*ceil(H/8)
-    BlockBest *sup;      // maxima of superblocks of the priority range, kMaxSuper
+    BlockBest *sup;      // maxima of superblocks of the priority range, at most kMaxSuper
     uint64_t *partials;  // one (ssd << 32 | index) per search tile
     TargetStage *tgt;    // staged target of the fill loop
     TargetStage *qtgt;   // staged target of inpaint_find_exemplar
@@ -149,7 +150,7 @@ struct JobDev {
                          // (capped at 10) to the nearest hole or out-of-image pixel of its row
     IterState *st;
     FillSync *sync;
-    uint64_t *fslot;     // one slot word per search tile
+    uint64_t *fslot;     // one slot word per search tile of the persistent forms
     StepRec *log;
     InitInfo *info;
     int32_t W, H, r, log_cap;

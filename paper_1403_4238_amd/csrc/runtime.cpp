@@ -32,7 +32,11 @@ namespace {
 thread_local std::string g_create_error;
 
 constexpr uint64_t kAlign = 256;
-constexpr uint64_t kPackBytes = 3 << 18;   // packed pixels read back at a time (2^18 of them)
+constexpr int64_t kPackPixels = 1 << 18;       // pixels packed on the device and read back at a time
+// Images of up to this many pixels are read back as words and packed on the
+// host: the device's packing takes three rounds in the room it has there
+// (400 x 300: 78 us on the host, 84 in rounds; 640 x 480: 204 and 111).
+constexpr int64_t kHostPackPixels = 1 << 17;
 constexpr int kMaxGroups = 4096;   // work-groups of a persistent dispatch (co-resident: <= 4 per CU)
 
 uint64_t align_up(uint64_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -134,9 +138,12 @@ static MaskStats mask_stats(const uint8_t *m, int stride, int W, int H) {
 
 struct Layout {
     uint64_t img, gray, hole, hole0, vrad, conf, pcd, blk, sup, partials, tgt, qtgt, srcp, vradp, hdist, st,
-        sync, fslot, info, key, mplan, pack, log, total;
+        sync, fslot, info, key, mplan, log, total;
+    uint64_t pack;    // scratch of the image read-back: what follows vrad up to conf
+    int64_t pack_px;  // pixels it holds, a multiple of 4
     int64_t log_cap;
-    int max_tiles;
+    int max_tiles;    // search tiles, of any height
+    int fill_tiles;   // of the persistent forms
 };
 
 bool tile_rows_ok(int t) { return t == 4 || t == 8 || t == 16; }
@@ -159,14 +166,21 @@ Layout make_layout(int W, int H, const inpaint_params &p) {
     L.hole = take(n);
     L.hole0 = take(n);
     L.vrad = take(n);
+    // (+7: the MFMA tiling may start up to 7 columns left of the rect)
+    const int tile_cols = (W + 7 + kTileW - 1) / kTileW;
+    L.max_tiles = tile_cols * ((H + search_tile_h(4) - 1) / search_tile_h(4));
+    L.fill_tiles = tile_cols * ((H + search_tile_h(kFillTileRows) - 1) / search_tile_h(kFillTileRows));
+    L.partials = take(8ull * L.max_tiles);
+    // the read-back packs where the radii were, which only create's count
+    // reads, and the partials, which no call leaves behind for another
+    L.pack = L.vrad;
+    L.pack_px = std::min<int64_t>((int64_t)(off - L.pack) / 3, kPackPixels) & ~3ll;
     L.conf = take(8 * n);
     L.pcd = take(16 * n);  // also the upload staging area during create (<= 6n bytes)
     const uint64_t nblk = (uint64_t)((W + kBlock - 1) / kBlock) * ((H + kBlock - 1) / kBlock);
     L.blk = take(sizeof(BlockBest) * nblk);
-    L.sup = take(sizeof(BlockBest) * kMaxSuper);
-    // (+7: the MFMA tiling may start up to 7 columns left of the rect)
-    L.max_tiles = ((W + 7 + kTileW - 1) / kTileW) * ((H + search_tile_h(4) - 1) / search_tile_h(4));
-    L.partials = take(8ull * L.max_tiles);
+    // superblocks of 8 x 8 blocks, or larger ones where those are too many
+    L.sup = take(sizeof(BlockBest) * std::min<uint64_t>((uint64_t)((W + 63) / 64) * ((H + 63) / 64), kMaxSuper));
     L.tgt = take(sizeof(TargetStage));
     L.qtgt = take(sizeof(TargetStage));
     const uint64_t np = (uint64_t)padded_pitch(W) * padded_rows(H);
@@ -177,13 +191,12 @@ Layout make_layout(int W, int H, const inpaint_params &p) {
     L.hdist = keep_hdist ? take(n) : 0;
     L.st = take(sizeof(IterState));
     L.sync = take(sizeof(FillSync));
-    L.fslot = take(8 * (uint64_t)L.max_tiles);
+    L.fslot = take(8 * (uint64_t)L.fill_tiles);
     L.info = take(sizeof(InitInfo));
     L.key = take(8);
     // one-job plan of the batched persistent dispatch (images whose tiles
     // outnumber the co-resident work-groups): slot, committer id, items, first
     L.mplan = take(sizeof(JobDev) + 256 + sizeof(WorkItem) * (uint64_t)L.max_tiles + 4ull * (kMaxGroups + 1));
-    L.pack = take(std::min<uint64_t>(3 * n, kPackBytes));
     L.log_cap = log_capacity(W, H, p);
     L.log = take(sizeof(StepRec) * (uint64_t)L.log_cap);
     L.total = off;
@@ -461,7 +474,7 @@ static bool setup_multi(inpaint_ctx *c) {
     const int ntiles = d.ntx * d.nty;
     if (c->direct || d.policy != INPAINT_SOURCE_ORIGINAL || d.isect) return false;
     if (!c->mfma && d.tile_rows != kFillTileRows) return false;
-    if (ntiles <= 0 || ntiles > 32 * kCommitThreads || ntiles > c->L.max_tiles) return false;
+    if (ntiles <= 0 || ntiles > 32 * kCommitThreads || ntiles > c->L.fill_tiles) return false;
     if ((int64_t)d.W * d.H > (1ll << kSlotIndexBits)) return false;
     const int cap = multi_capacity(c->mfma, d.r);
     const int n_search = cap - 1;
@@ -648,7 +661,7 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     hipError_t e = upload_rows(stage_rgb, (size_t)W * ch, img->data, img->stride_bytes, H, s);
     if (e == hipSuccess) e = upload_rows(stage_mask, W, mask, mask_stride, H, s);
     const uint32_t nonce = next_nonce();
-    if (e == hipSuccess) e = launch_init(d, stage_rgb, ch, stage_mask, hm.count, L.max_tiles, nonce, s);
+    if (e == hipSuccess) e = launch_init(d, stage_rgb, ch, stage_mask, hm.count, L.fill_tiles, nonce, s);
     if (e == hipSuccess) e = launch_count_valid(d, s);
     if (e == hipSuccess) e = launch_prio_init(d, s);
     if (e == hipSuccess) e = launch_commit(d, s);  // selects and stages the first target
@@ -963,10 +976,25 @@ int32_t inpaint_read_image(inpaint_ctx *ctx, uint8_t *rgb, int32_t stride) {
     if (ctx->sticky) return ctx->sticky;
     const int W = ctx->d.W, H = ctx->d.H;
     if (stride < 3 * W) return ctx->fail(INPAINT_INVALID_ARGUMENT, "stride smaller than a row");
+    const int64_t n = (int64_t)W * H;
+    if (n <= kHostPackPixels) {
+        std::vector<uint32_t> words((size_t)n);
+        HIP_OR_FAIL(ctx, hipMemcpyAsync(words.data(), ctx->d.img, 4 * n, hipMemcpyDeviceToHost, ctx->stream), "copy");
+        HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream), "sync");
+        for (int y = 0; y < H; ++y)
+            for (int x = 0; x < W; ++x) {
+                const uint32_t v = words[(size_t)y * W + x];
+                uint8_t *o = rgb + (size_t)y * stride + 3 * x;
+                o[0] = v & 255;
+                o[1] = (v >> 8) & 255;
+                o[2] = (v >> 16) & 255;
+            }
+        return INPAINT_OK;
+    }
     // Packed on the device, a piece at a time, straight into the caller's rows:
     // the words' fourth byte is neither moved nor taken out on the host.
     uint8_t *pack = ctx->ws + ctx->L.pack;
-    const int64_t n = (int64_t)W * H, piece = (int64_t)(kPackBytes / 3);
+    const int64_t piece = ctx->L.pack_px;
     if (stride == 3 * W) {
         for (int64_t i = 0; i < n; i += piece) {
             const int64_t c = std::min(piece, n - i);

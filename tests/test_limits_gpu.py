@@ -107,3 +107,46 @@ def test_auto_persistent_at_its_most_tiles(x0, form):
     assert g.run_form() == form
     g.close()
     _full_run_parity(job, "wide", form="persistent", iters_per_check=8)
+
+
+# The image read back whole: packed on the host up to 2^17 pixels, above on the
+# device in pieces that end within rows; with the caller's rows packed or padded.
+@pytest.mark.parametrize("W,H", [(40, 30), (362, 362), (363, 362), (701, 433), (1031, 777)])
+@pytest.mark.parametrize("pad", [0, 13])
+def test_read_image_rows(W, H, pad):
+    rgb = _noise(W, H, W)
+    mask = np.zeros((H, W), np.uint8)
+    mask[5:9, 7:12] = 1
+    g = B.Inpainter(rgb, mask, 2)
+    out = np.full((H, 3 * W + pad), 0x5A, np.uint8)
+    for _ in range(2):
+        assert B.lib().inpaint_read_image(g.ctx, out.ctypes.data, 3 * W + pad) == B.OK
+        want = rgb * (mask == 0)[..., None]
+        assert (out[:, :3 * W].reshape(H, W, 3) == want).all()
+        assert (out[:, 3 * W:] == 0x5A).all()
+    assert B.lib().inpaint_read_image(g.ctx, out.ctypes.data, 3 * W - 1) == B.INVALID_ARGUMENT
+    g.close()
+
+
+# The read-back works in planes that hold nothing between calls: a removal that
+# is read back part of the way goes on as one that is not.
+@pytest.mark.parametrize("kw", [dict(form="persistent"), dict(form="graph"), dict(form="stream", path=B.PATH_SIMT),
+                                dict(form="stream", source_policy=B.SOURCE_CURRENT),
+                                dict(form="stream", source_policy=B.SOURCE_CURRENT, scoring=B.SCORE_INTERSECT)])
+def test_read_image_between_runs_changes_nothing(kw):
+    job = synth.vga()
+    a, b = [B.Inpainter(job.rgb, job.mask, 4, iters_per_check=8, **kw) for _ in range(2)]
+    for _ in range(4):
+        a.run(max_iters=24)
+        a.read_image()
+        a.find_exemplar_static(300, 200)
+    b.run(max_iters=96)
+    assert a.read_log(0, 96).tobytes() == b.read_log(0, 96).tobytes()
+    assert (a.read_image() == b.read_image()).all()
+    ck = a.export_state()
+    a.import_state(*ck)
+    a.read_image()
+    assert a.run(max_iters=24)[1] == b.run(max_iters=24)[1]
+    assert a.read_log(96, 24).tobytes() == b.read_log(96, 24).tobytes()
+    for g in (a, b):
+        g.close()
