@@ -70,8 +70,9 @@ extern "C" {
  * score every target in turn, with no kernel boundary between search and
  * commit.  When the tiles outnumber the work-groups that fit on the device,
  * each search work-group takes several tiles (up to 64).  It needs the
- * default candidate domain (and the SIMT path with tile_rows 8); otherwise
- * inpaint_run uses STREAM instead -- inpaint_run_form tells which.
+ * default candidate domain and the matrix-core search or the SIMT one with
+ * tile_rows 8 (0 asks for 8); otherwise inpaint_run uses STREAM instead --
+ * inpaint_run_form tells which.
  * Persistent dispatches of one process never overlap (the library
  * serialises them; each call waits for its dispatch's end). */
 #define INPAINT_FORM_PLAIN  0    /* launch one iteration, host check, repeat  */
@@ -80,7 +81,11 @@ extern "C" {
 #define INPAINT_FORM_PERSISTENT 3 /* one dispatch of iters_per_check, check  */
 
 /* AUTO: the matrix cores for whole-window scoring with tile_rows 0, at every
- * radius, else the SIMT search.  Same results either way. */
+ * radius, else the SIMT search.  Same results either way.  AUTO takes the SIMT
+ * search also where a limit counts tiles that the matrix-core tiling exceeds
+ * (persistent forms, inpaint_find_exemplar_static), and in a batch's graph
+ * form, where images of AUTO and MFMA search with SIMT unless the autotuner
+ * finds the matrix cores faster. */
 #define INPAINT_PATH_AUTO 0
 #define INPAINT_PATH_SIMT 1      /* integer dot-product SSD on the VALU      */
 #define INPAINT_PATH_MFMA 2      /* int8 matrix-core cross term (exact), r <= 6 */
@@ -110,9 +115,10 @@ extern "C" {
  *   - The copy fills only the target's hole pixels whose source pixel
  *     qualifies; the others stay in the hole for a later iteration.
  *
- * The two fields combine freely.  Any non-default value needs the SIMT
- * search (path SIMT, SIMT_DIRECT or AUTO; MFMA gives INVALID_ARGUMENT) and
- * runs in the PLAIN, STREAM or GRAPH form (PERSISTENT runs as STREAM).
+ * The two fields combine freely.  Any non-default value needs path SIMT,
+ * SIMT_DIRECT or AUTO (MFMA gives INVALID_ARGUMENT; AUTO searches on the
+ * matrix cores with WHOLE scoring) and runs in the PLAIN, STREAM or GRAPH
+ * form (PERSISTENT runs as STREAM).
  * Such a context cannot be attached to a batch. */
 #define INPAINT_SOURCE_ORIGINAL 0
 #define INPAINT_SOURCE_CURRENT  1
@@ -215,8 +221,8 @@ int32_t inpaint_find_exemplar(inpaint_ctx *ctx, int32_t target_x, int32_t target
  * key) lives in a static device array of the library (258 KiB, one per GPU,
  * held until the process ends) instead of the context's workspace.  The
  * call allocates nothing.  A search rect that needs more
- * than 32768 search tiles (about 67 M candidate centres with the default
- * SIMT tile, 134 M with the MFMA tile) is rejected with INVALID_ARGUMENT.
+ * than 32768 search tiles (about 67 M candidate centres with path AUTO or the
+ * default SIMT tile, 134 M with path MFMA) is rejected with INVALID_ARGUMENT.
  * Every call on one GPU shares that GPU's array: calls that overlap on one
  * GPU (two threads, or two streams) race and must not be issued; it keeps
  * only the last call's contents, none of which a call reads before writing.

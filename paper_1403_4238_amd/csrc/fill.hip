@@ -75,9 +75,6 @@ __device__ __forceinline__ uint32_t lean_word(uint32_t pix, bool known, uint32_t
     return (pix & kColour) | (tag << 24) | (known ? 0x80000000u : 0u);
 }
 
-// Stages the target patch at (tx, ty) with radius r into *tg: known mask,
-// RGBX words and T2 = sum of squared known target values, in column-major
-// slot order (dx + r) * P + (dy + r).
 // Column-run bits of mask word w (of mw) of a P x P patch in column-major
 // slot order: a known slot starts a run when the slot above it in its column
 // is unknown or outside the patch, and ends one when the slot below is.
@@ -143,6 +140,9 @@ __device__ void stage_slots(int r, int tx, int ty, TargetStage *tg, Scratch &s, 
     }
 }
 
+// Stages the target patch at (tx, ty) with radius r into *tg: known mask,
+// RGBX words and T2 = sum of squared known target values, in column-major
+// slot order (dx + r) * P + (dy + r).
 __device__ void stage_target(const JobDev &d, int tx, int ty, int r, TargetStage *tg, Scratch &s) {
     const int P = 2 * r + 1;
     const GlobalView v{d};
@@ -560,11 +560,11 @@ struct CommitNote {
 
 // CURRENT source policy: the pixels this iteration filled become source
 // pixels.  Writes their words into the padded source plane and brings the
-// validity planes up to date around the patch: the horizontal distances of
-// the patch rows, then the validity radii of every centre whose radius can
-// have changed (as k_init_hdist / k_init_vrad compute them).  The hole map
-// changed only inside the patch, which the LDS neighbourhood holds; every
-// other pixel is read from device memory, unchanged since earlier launches.
+// validity plane up to date around the patch: the horizontal distances of the
+// patch rows, then the validity radii of every centre whose radius can have
+// changed (as k_init_planes computes them).  The hole map changed only inside
+// the patch, which the LDS neighbourhood holds; every other pixel is read from
+// device memory, unchanged since earlier launches.
 template <int R, bool ISECT>
 __device__ void add_filled_sources(const JobDev &d, const CommitLds<R> &L, int px, int py) {
     constexpr int P = 2 * R + 1, half = Stage<R>::half, side = Stage<R>::side, pitch_l = Stage<R>::pitch;
@@ -762,10 +762,9 @@ constexpr uint32_t kSpinLimit = 1u << 22;
 
 // Go words: the launch epoch in the high half; in the low half either stop
 // (all ones) or k + 1 (k < 2^25 - 1, the dispatch's iteration) in bits 0-24
-// with the record tag of that iteration (lean records; 0 otherwise) in bits
-// 25-31.
+// with the record tag of that iteration in bits 25-31.
 constexpr uint32_t kGoK = (1u << 25) - 1;
-__device__ __forceinline__ uint64_t go_word(uint32_t epoch, uint32_t k1, uint32_t tag = 0) {
+__device__ __forceinline__ uint64_t go_word(uint32_t epoch, uint32_t k1, uint32_t tag) {
     return ((uint64_t)epoch << 32) | (tag << 25) | k1;
 }
 __device__ __forceinline__ uint64_t go_stop(uint32_t epoch) { return ((uint64_t)epoch << 32) | 0xffffffffu; }

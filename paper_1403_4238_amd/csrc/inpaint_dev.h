@@ -20,8 +20,9 @@ constexpr int kMaxSuper = 512;
 constexpr int kTileW = 64;                             // search tile width (one wave)
 constexpr int kSearchWaves = 4;                        // waves per search work-group
 constexpr int kCommitThreads = 256;   // one work-group per image; 512 VGPRs per thread
-constexpr int kMfmaMaxRadius = 8;     // int8-MFMA search: the band of 16 columns and 2r pixels fits two MFMAs
-constexpr int kMfmaPathRadius = 6;    // largest radius INPAINT_PATH_MFMA is accepted for
+// The int8-MFMA search takes every radius (a band of 16 columns and 2r pixels
+// fits two MFMAs); INPAINT_PATH_MFMA is accepted up to this one.
+constexpr int kMfmaPathRadius = 6;
 constexpr int kMfmaTileRows = 16;     // MFMA search tile: 64 x 64 candidates
 constexpr int kFillTileRows = 8;      // persistent fill: candidate rows per search thread
 constexpr int kDefaultTileRows = 8;   // the SIMT search with tile_rows 0
@@ -221,7 +222,6 @@ hipError_t launch_search(const JobDev &d, bool query, int r, int rx0, int ry0, i
 hipError_t launch_search_direct(const JobDev &d, bool query, int r, int rx0, int ry0, int rx1, int ry1,
                                 int tile_rows, int ntx, int nty, hipStream_t s,
                                 hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-bool mfma_supported(int r);
 // int8-MFMA form of the search; same tiling as launch_search with tile_rows 16.
 hipError_t launch_search_mfma(const JobDev &d, bool query, int r, int rx0, int ry0, int rx1, int ry1, int ntx, int nty,
                               hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
@@ -249,8 +249,8 @@ int fill_grid(int ntiles);
 hipError_t launch_fill(const JobDev &d, int ntiles, int n_iters, uint32_t epoch, hipStream_t s);
 // Batched persistent fill: up to n_iters iterations of every job of the plan
 // (all of patch radius r) in one persistent dispatch of `grid` = n_commit +
-// search groups.  MFMA: r <= 6, the int8-MFMA tiling; SIMT: the SIMT tiling
-// of kFillTileRows.  MFMA with r = kMultiMixed: one dispatch for jobs of any
+// search groups.  MFMA: the int8-MFMA tiling; SIMT: the SIMT tiling of
+// kFillTileRows.  MFMA with r = kMultiMixed: one dispatch for jobs of any
 // radius up to kMultiMixMaxR, each committer and each served item taking
 // its job's radius.
 constexpr int kMultiMixed = 0;

@@ -380,7 +380,7 @@ static int32_t check_params(int32_t W, int32_t H, const inpaint_params *p, std::
 static bool persistent_fits(const inpaint_ctx *c) {
     const JobDev &d = c->d;
     const int ntiles = d.ntx * d.nty;
-    // (the committer scans at most 32 slots per thread)
+    // (the committer's three polling waves scan at most 43 slots per thread)
     if (c->direct || c->d.policy != INPAINT_SOURCE_ORIGINAL || c->d.isect) return false;
     if ((!c->mfma && d.tile_rows != kFillTileRows) || ntiles <= 0 || ntiles > 32 * kCommitThreads) return false;
     if ((int64_t)d.W * d.H > (1ll << kSlotIndexBits)) return false;   // slot word index field
@@ -730,11 +730,11 @@ int32_t inpaint_find_exemplar(inpaint_ctx *ctx, int32_t tx, int32_t ty, int32_t 
     q.ry0 = k[1];
     q.rx1 = k[2];
     q.ry1 = k[3];
-    set_tiles(q, d.tile_rows, ctx->mfma && mfma_supported(r) ? r : 0);
+    set_tiles(q, d.tile_rows, ctx->mfma ? r : 0);
     hipStream_t s = ctx->stream;
     uint64_t *dkey = (uint64_t *)(ctx->ws + ctx->L.key);
     HIP_OR_FAIL(ctx, launch_stage_query(q, tx, ty, r, s), "stage");
-    if (ctx->mfma && mfma_supported(r))
+    if (ctx->mfma)
         HIP_OR_FAIL(ctx, launch_search_mfma(q, true, r, q.rx0, q.ry0, q.rx1, q.ry1, q.ntx, q.nty, s), "search");
     else if (ctx->direct)
         HIP_OR_FAIL(ctx, launch_search_direct(q, true, r, q.rx0, q.ry0, q.rx1, q.ry1, q.tile_rows, q.ntx, q.nty, s),
@@ -751,8 +751,7 @@ int32_t inpaint_find_exemplar(inpaint_ctx *ctx, int32_t tx, int32_t ty, int32_t 
     return INPAINT_OK;
 }
 
-// inpaint_find_exemplar with its scratch (target stage, MFMA operands, tile
-// partials, key) in the static device array instead of the workspace.
+// inpaint_find_exemplar with its scratch (target stage, tile partials, key) in the static device array instead of the workspace.
 int32_t inpaint_find_exemplar_static(inpaint_ctx *ctx, int32_t tx, int32_t ty, int32_t r, inpaint_rect rect,
                                      int64_t *source_index, uint32_t *ssd) {
     SharedDevice lock(g_device_mu);
@@ -1166,7 +1165,7 @@ namespace {
 struct TuneChoice {
     int tile_rows = kDefaultTileRows;
     int grid = 0;     // 0 = one work-group per item
-    int engine = 0;   // search engine: 0 SIMT (dot4), 1 int8 MFMA (contexts with the MFMA planes)
+    int engine = 0;   // search engine: 0 SIMT (dot4), 1 int8 MFMA (contexts that search on the matrix cores)
 };
 
 struct RadiusGroup {
@@ -1277,10 +1276,11 @@ hipError_t upload_slot(inpaint_batch *b, int i) {
 }
 
 // Graph-form groups: the images of one radius searched by the same kernel,
-// keyed r, or r + kMfmaGroup for contexts that carry the MFMA planes (their
-// group may search on the matrix cores, if the autotuner finds it faster).
+// keyed r, or r + kMfmaGroup for contexts that search on the matrix cores
+// (their group starts on the SIMT search and goes over if the autotuner finds
+// the matrix cores faster).
 constexpr int kMfmaGroup = 16;
-int group_key(const inpaint_ctx *c) { return c->d.r + (c->mfma && mfma_supported(c->d.r) ? kMfmaGroup : 0); }
+int group_key(const inpaint_ctx *c) { return c->d.r + (c->mfma ? kMfmaGroup : 0); }
 bool key_mfma(int key) { return key >= kMfmaGroup; }
 int key_r(int key) { return key % kMfmaGroup; }
 
@@ -1394,7 +1394,7 @@ hipError_t autotune_group(inpaint_batch *b, int gkey, RadiusGroup &g, std::map<s
     float best_ms = 1e30f;
     TuneChoice best = g.tune;
     // (engine, tile rows): the SIMT tile shapes, and the MFMA tile (one
-    // shape, only its grid is tuned) where the contexts carry its planes
+    // shape, only its grid is tuned) for contexts that search on the matrix cores
     std::vector<std::pair<int, int>> shapes = {{0, 4}, {0, 8}, {0, 16}};
     if (key_mfma(gkey)) shapes.push_back({1, kMfmaTileRows});
     for (const auto &shape : shapes) {
@@ -1445,7 +1445,7 @@ hipError_t grow(T **p, size_t *cap, size_t n) {
 // Whether the batched persistent dispatch searches a job on the matrix cores;
 // with auto_simt those of path AUTO go to the SIMT form.
 bool multi_form(const inpaint_ctx *c, bool auto_simt) {
-    return c->mfma && mfma_supported(c->d.r) && !(auto_simt && c->p.path == INPAINT_PATH_AUTO);
+    return c->mfma && !(auto_simt && c->p.path == INPAINT_PATH_AUTO);
 }
 
 // A job's JobDev with the tiling of the batched persistent search.

@@ -152,8 +152,6 @@ hipError_t launch_mfma_t(const JobDev &d, bool query, int rx0, int ry0, int rx1,
 
 }  // namespace
 
-bool mfma_supported(int r) { return r >= 1 && r <= kMfmaMaxRadius; }
-
 hipError_t launch_search_batched_mfma(const JobDev *slots, const WorkItem *items, const int32_t *nitems, int r,
                                       int grid, hipStream_t s) {
 #define CALL(R) hipLaunchKernelGGL(k_search_batched_mfma<R>, dim3(grid), dim3(kSearchWaves * 64), 0, s, slots, items, nitems)
