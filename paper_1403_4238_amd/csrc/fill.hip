@@ -650,7 +650,14 @@ __device__ __forceinline__ void commit_body(const JobDev &d, Scratch &s, CommitL
     post_best(L, gather<R>(tid, d, px, py, g, d.sup, L));
 #pragma unroll
     for (int k = 0; k < 8; ++k) best = pv[k] < best ? pv[k] : best;   // clamped repeats are harmless
-    for (int t = threadIdx.x + 8 * T; t < ntiles; t += T) best = d.partials[t] < best ? d.partials[t] : best;
+    // (many tiles: eight in flight again; the 11750 SIMT tiles of a 24 Mpixel
+    // image at radius 1, us an iteration: 49.2 one by one, 42.1 now)
+    for (int t0 = threadIdx.x + 8 * T; t0 < ntiles; t0 += 8 * T) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pv[k] = d.partials[min(t0 + k * T, ntiles - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) best = pv[k] < best ? pv[k] : best;
+    }
     best = wave_min(best);
     if ((threadIdx.x & 63) == 0) L.smin[threadIdx.x >> 6] = best;
     lds_barrier();

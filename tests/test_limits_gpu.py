@@ -150,3 +150,17 @@ def test_read_image_between_runs_changes_nothing(kw):
     assert a.read_log(96, 24).tobytes() == b.read_log(96, 24).tobytes()
     for g in (a, b):
         g.close()
+
+
+# The stream form's commit reduces one minimum per tile, eight per thread and
+# round: counts on either side of its rounds of 2048.
+@pytest.mark.parametrize("tiles", [2047, 2048, 2049, 4097, 9000])
+def test_minima_of_many_tiles(tiles):
+    W, H, r = 64 * tiles + 2, 9, 1
+    rgb = _noise(W, H, tiles)
+    mask = np.zeros((H, W), np.uint8)
+    mask[3:6, 90:97] = 1
+    mask[3:6, W - 90:W - 81] = 1
+    log = _full_run_parity(synth.Job("wide", rgb, mask, r), "%d tiles" % tiles, path=B.PATH_SIMT, form="stream",
+                           iters_per_check=4)
+    assert len(np.unique(log["source_index"] % W // 64)) > 4
