@@ -1048,48 +1048,87 @@ struct RecWords {
     __device__ __forceinline__ bool known(int j) const { return (w[j] >> 31) != 0; }
 };
 
-// The target of a record as the SIMT search reads it: words, known mask,
-// column-run bits and T2.  Two barriers, the last of which publishes it.
-template <int R>
-__device__ __forceinline__ void build_target(const RecWords<R> &rw, tile::TargetLds *t, uint32_t *t2p) {
-    constexpr int P = 2 * R + 1, MW = (P * P + 31) / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t t2 = 0;
-#pragma unroll
-    for (int j = 0; j < RecWords<R>::J; ++j) {
-        const int sl = threadIdx.x + j * kSearchWaves * 64;
-        const bool kn = sl < P * P && rw.known(j);
-        const uint32_t w = kn ? rw.w[j] & kColour : 0u;
-        if (sl < P * P) t->tpix[sl] = w;
-        t2 = __builtin_amdgcn_udot4(w, w, t2, false);
-        const uint64_t b = __ballot(kn);
-        const int w0 = 8 * j + 2 * wave;
-        if (lane == 0 && w0 < 16) {
-            t->mbits[w0] = (uint32_t)b;
-            t->mbits[w0 + 1] = (uint32_t)(b >> 32);
+// Bit i of column_slots<P>(base, k): slot base + i of a P x P patch in
+// column-major order is the k-th of its column.
+template <int P>
+constexpr uint64_t column_slots(int base, int k) {
+    uint64_t m = 0;
+    for (int i = 0; i < 64; ++i) m |= (uint64_t)((base + i) % P == k) << i;
+    return m;
+}
+// The slots of rounds of 64 that start and end a column.
+template <int P>
+struct ColumnEnds {
+    uint64_t top[kMaxOffsets / 64 + 1], end[kMaxOffsets / 64 + 1];
+    constexpr ColumnEnds() : top(), end() {
+        for (int j = 0; j < kMaxOffsets / 64 + 1; ++j) {
+            top[j] = column_slots<P>(64 * j, 0);
+            end[j] = column_slots<P>(64 * j, P - 1);
         }
     }
-    t2 = dpp::sum_u32(t2);
-    if (lane == 0) t2p[wave] = t2;
-    __syncthreads();
-    if (threadIdx.x < MW) {
-        uint32_t sb, eb;
-        run_bits(t->mbits, threadIdx.x, MW, P, &sb, &eb);
-        t->sbits[threadIdx.x] = sb;
-        t->ebits[threadIdx.x] = eb;
+};
+
+// The target of a record as the SIMT search reads it: words, known mask,
+// column-run bits (run_bits) and T2.  Every wave reads all the words, until
+// they carry `tag`, so that each has the whole known mask in its ballots and
+// forms its share of the bits from scalars: one barrier, the caller's, which
+// publishes the target and every wave's ok[] (0 after kSpinLimit reads).
+// (Shared reads with the mask put together in LDS took three barriers a
+// target: 64 images, us an iteration, radius 3 127 -> 117, radius 6 429 -> 410.)
+template <int R>
+__device__ __forceinline__ void read_target(const FillRec *rec, uint32_t tag, tile::TargetLds *t, int32_t *ok) {
+    constexpr int P = 2 * R + 1, N = P * P, J = (N + 63) / 64;
+    constexpr ColumnEnds<P> ends;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t w[J];
+    bool fresh = false;
+    for (uint32_t spin = 0; !fresh && spin < kSpinLimit; ++spin) {
+        bool mine = true;
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            w[j] = __hip_atomic_load(&rec->tpix[min(lane + 64 * j, N - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int j = 0; j < J; ++j) mine = mine && ((w[j] >> 24) & 0x7fu) == tag;
+        fresh = __ballot(!mine) == 0;
     }
-    if (threadIdx.x == 0) t->t2 = t2p[0] + t2p[1] + t2p[2] + t2p[3];
-    __syncthreads();
+    uint64_t known[J];
+    uint32_t t2 = 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const bool kn = lane + 64 * j < N && (w[j] >> 31) != 0;
+        known[j] = __ballot(kn);
+        w[j] = kn ? w[j] & kColour : 0u;
+        t2 = __builtin_amdgcn_udot4(w[j], w[j], t2, false);
+    }
+    t2 = dpp::sum_u32(t2);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        if ((j & 3) != wave) continue;
+        if (lane + 64 * j < N) t->tpix[lane + 64 * j] = w[j];
+        const uint64_t m = known[j];
+        const uint64_t up = m << 1 | (j > 0 ? known[j > 0 ? j - 1 : 0] >> 63 : 0ull);              // slot - 1 known
+        const uint64_t dn = m >> 1 | (j + 1 < J ? known[j + 1 < J ? j + 1 : j] << 63 : 0ull);      // slot + 1 known
+        const uint64_t sb = m & (ends.top[j] | ~up), eb = m & (ends.end[j] | ~dn);
+        if (lane == 0) {
+            t->mbits[2 * j] = (uint32_t)m;
+            t->mbits[2 * j + 1] = (uint32_t)(m >> 32);
+            t->sbits[2 * j] = (uint32_t)sb;
+            t->sbits[2 * j + 1] = (uint32_t)(sb >> 32);
+            t->ebits[2 * j] = (uint32_t)eb;
+            t->ebits[2 * j + 1] = (uint32_t)(eb >> 32);
+        }
+    }
+    if (lane == 0) ok[wave] = fresh;
+    if (threadIdx.x == 0) t->t2 = t2;
 }
+__device__ __forceinline__ bool all_ok(const int32_t *ok) { return ok[0] && ok[1] && ok[2] && ok[3]; }
+static_assert(kSearchWaves == 4, "one ok word per wave");
 
 // A SIMT search group's wait for iteration k (whole group): one lane polls
-// the go word, then every thread reads its words until they are fresh.  (Up to
-// four such groups share a CU, a thousand the device: polling whole records
-// slows the committer's own loads more than the round trip it saves.)  False
-// on stop or time-out.
-template <int R>
-__device__ __forceinline__ bool wait_go(const FillRec *rec, uint32_t epoch, uint32_t k, bool words, RecWords<R> &rw,
-                                        int32_t *flag, uint32_t *tag) {
+// the go word.  (Up to four such groups share a CU, a thousand the device:
+// polling whole records slows the committer's own loads more than the round
+// trip it saves.)  False on stop or time-out.
+__device__ __forceinline__ bool wait_go(const FillRec *rec, uint32_t epoch, uint32_t k, int32_t *flag, uint32_t *tag) {
     if (threadIdx.x == 0) {
         int f = 0;
         for (uint32_t spin = 0; spin < kSpinLimit; ++spin) {
@@ -1105,14 +1144,7 @@ __device__ __forceinline__ bool wait_go(const FillRec *rec, uint32_t epoch, uint
         *flag = f;
     }
     __syncthreads();
-    if (!*flag) return false;
-    const uint32_t want = *tag;
-    bool ok = !words;
-    for (uint32_t spin = 0; !ok && spin < kSpinLimit; ++spin) {
-        rw.load(rec);
-        ok = rw.fresh(want);
-    }
-    return !words || __syncthreads_and(ok);
+    return *flag != 0;
 }
 
 // A search group's wait for iteration k (whole group): each poll reads the go
@@ -1149,7 +1181,7 @@ struct SearchLds {
     __attribute__((aligned(16))) uint32_t tile[tile::TileGeom<R, NY>::LDS_WORDS];
     tile::TargetLds tgt;
     uint64_t red[kSearchWaves];
-    uint32_t t2p[kSearchWaves];
+    int32_t ok[kSearchWaves];
     int32_t flag;
     uint32_t tag;
 };
@@ -1171,11 +1203,12 @@ __device__ __forceinline__ void fill_search(const JobDev &d, int ntiles, uint32_
     const bool anyv = __syncthreads_or(vmask != 0);
     const FillRec *rec = &d.sync->rec[t % kGoCopies];
     for (uint32_t k = 0;; ++k) {
-        RecWords<R> rw;
-        if (!wait_go<R>(rec, epoch, k, anyv, rw, &S.flag, &S.tag)) break;
+        if (!wait_go(rec, epoch, k, &S.flag, &S.tag)) break;
         uint64_t best = ~0ull;
         if (anyv) {
-            build_target<R>(rw, &S.tgt, S.t2p);
+            read_target<R>(rec, S.tag, &S.tgt, S.ok);
+            __syncthreads();
+            if (!all_ok(S.ok)) break;
             const tile::LdsTarget view{&S.tgt};
             best = tile::wave_min_u64(tile::score_tile<R, NY>(d, view, tx0, ty0, vmask, S.tile));
             if ((threadIdx.x & 63) == 0) S.red[threadIdx.x >> 6] = best;
@@ -1395,9 +1428,9 @@ __device__ __forceinline__ bool multi_serve_simt(const JobDev &d, const ServeIte
         anyv = __syncthreads_or(vmask != 0);
     }
     if (it.build && anyv) {
-        RecWords<R> rw;
-        if (!read_record<R>(&d.sync->rec[it.t % kGoCopies], it.tag, rw)) return false;
-        build_target<R>(rw, &S.tgt, S.t2p);
+        read_target<R>(&d.sync->rec[it.t % kGoCopies], it.tag, &S.tgt, S.ok);
+        __syncthreads();
+        if (!all_ok(S.ok)) return false;
     }
     uint64_t best = ~0ull;
     if (anyv) {
