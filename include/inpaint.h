@@ -80,12 +80,13 @@ extern "C" {
 #define INPAINT_FORM_GRAPH  2    /* replay a hipGraph of iters_per_check      */
 #define INPAINT_FORM_PERSISTENT 3 /* one dispatch of iters_per_check, check  */
 
-/* AUTO: the matrix cores for whole-window scoring with tile_rows 0, at every
- * radius, else the SIMT search.  Same results either way.  AUTO takes the SIMT
- * search also where a limit counts tiles that the matrix-core tiling exceeds
- * (persistent forms, inpaint_find_exemplar_static), and in a batch's graph
- * form, where images of AUTO and MFMA search with SIMT unless the autotuner
- * finds the matrix cores faster. */
+/* AUTO: the matrix cores for whole-window scoring with tile_rows 0, else the
+ * SIMT search.  Same results either way.  AUTO takes the SIMT search also
+ *   - for queries and the PLAIN, STREAM and GRAPH forms at radius 1;
+ *   - where a limit counts tiles that the matrix-core tiling exceeds
+ *     (persistent forms, inpaint_find_exemplar_static);
+ *   - in a batch's graph form, where images of AUTO and MFMA search with SIMT
+ *     unless the autotuner finds the matrix cores faster. */
 #define INPAINT_PATH_AUTO 0
 #define INPAINT_PATH_SIMT 1      /* integer dot-product SSD on the VALU      */
 #define INPAINT_PATH_MFMA 2      /* int8 matrix-core cross term (exact), r <= 6 */

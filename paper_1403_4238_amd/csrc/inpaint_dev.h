@@ -26,6 +26,14 @@ constexpr int kMfmaPathRadius = 6;
 constexpr int kMfmaTileRows = 16;     // MFMA search tile: 64 x 64 candidates
 constexpr int kFillTileRows = 8;      // persistent fill: candidate rows per search thread
 constexpr int kDefaultTileRows = 8;   // the SIMT search with tile_rows 0
+constexpr int kFillMaxTiles = 32 * kCommitThreads;   // tiles of one job in the persistent forms
+// AUTO's single searches (queries, and the plain, stream and graph forms) of a
+// smaller radius run SIMT: a 3x3 patch takes nine dot products a candidate
+// there.  Stream form, us an iteration, SIMT / MFMA: radius 1 14.0 / 14.5 at
+// 1920x1080, 24.1 / 24.9 at 3840x2160, 42.1 / 49.8 at 6000x4000; radius 2
+// 16.0 / 15.0, 29.9 / 25.6, 56.0 / 50.9.  (In the persistent forms the search
+// is hidden and MFMA has half the tiles: 33.3 / 25.1 at 3840x2160.)
+constexpr int kAutoMfmaRadius = 2;
 
 // Padding of the static search planes (srcp, vradp) around the
 // image, in pixels: every staged search window -- a tile of up to 64 x 64
@@ -161,7 +169,7 @@ struct JobDev {
     int32_t sshift, nsx, nsy;     // superblocks: 2^sshift blocks a side, nsx x nsy of them
     int32_t tile_rows;            // candidate rows per thread in the search
     int32_t ntx, nty;             // search tiles over the rect
-    int32_t mfma;                 // 1: the search runs on the matrix cores
+    int32_t mfma;                 // 1: the fill loop's search runs on the matrix cores
     int32_t pitch;                // row pitch of srcp / vradp in pixels (multiple of 4)
     int32_t policy;               // INPAINT_SOURCE_*
     int32_t isect;                // 1: INTERSECT scoring
@@ -283,10 +291,10 @@ constexpr uint64_t kStaticPartialsOff = kStaticKeyOff + 256;
 constexpr uint64_t kStaticScratchBytes = kStaticPartialsOff + 8ull * kStaticMaxTiles;
 
 // The search of an allocation-free query of radius r on a context of path
-// `path` (mfma: it searches on the matrix cores; its tile height is
-// tile_rows).  A rect is accepted by the count of one tiling of its path: the
-// MFMA tiling for MFMA up to kMfmaPathRadius, else the SIMT one (AUTO: of the
-// default height).  The MFMA tiling may start up to 7 columns left of the
+// `path` (mfma: such a query runs on the matrix cores; tile_rows: the height
+// of the SIMT tile).  A rect is accepted by the count of one tiling of its
+// path: the MFMA tiling for MFMA up to kMfmaPathRadius, else the SIMT one.
+// The MFMA tiling may start up to 7 columns left of the
 // rect; where that takes it past the scratch on an accepted rect, the SIMT
 // search runs, so the tiles launched never outnumber the partials.
 struct StaticRoute {
@@ -295,13 +303,12 @@ struct StaticRoute {
     Tiling t;
 };
 inline StaticRoute static_route(int path, bool mfma, int tile_rows, int r, int rx0, int ry0, int rx1, int ry1) {
-    const int rows = mfma && path == INPAINT_PATH_AUTO ? kDefaultTileRows : tile_rows;
-    const Tiling simt = tiling(rx0, ry0, rx1, ry1, rows);
-    if (!mfma) return {simt.count() <= kStaticMaxTiles, false, rows, simt};
+    const Tiling simt = tiling(rx0, ry0, rx1, ry1, tile_rows);
+    if (!mfma) return {simt.count() <= kStaticMaxTiles, false, tile_rows, simt};
     const Tiling mt = tiling(rx0, ry0, rx1, ry1, kMfmaTileRows, r);
     const bool by_mfma = path == INPAINT_PATH_MFMA && r <= kMfmaPathRadius;
-    if ((by_mfma ? mt : simt).count() > kStaticMaxTiles) return {false, false, rows, simt};
-    if (mt.count() > kStaticMaxTiles) return {true, false, rows, simt};
+    if ((by_mfma ? mt : simt).count() > kStaticMaxTiles) return {false, false, tile_rows, simt};
+    if (mt.count() > kStaticMaxTiles) return {true, false, tile_rows, simt};
     return {true, true, kMfmaTileRows, mt};
 }
 // Takes the array's device address on `device`, which must be current

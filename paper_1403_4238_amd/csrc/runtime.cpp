@@ -241,7 +241,7 @@ struct inpaint_ctx {
     int64_t hole0 = 0;
     int64_t candidates = 0;
     inpaint_rect rect{};      // image-clipped search rect (reported)
-    bool mfma = false;        // search on the matrix cores
+    bool mfma = false;        // may search on the matrix cores (the fill loop: d.mfma)
     bool direct = false;      // SIMT search without LDS staging
     int32_t run_form = INPAINT_FORM_PLAIN;   // form inpaint_run uses
     bool multi = false;       // persistent form through the batched dispatch (tiles > co-resident groups)
@@ -382,12 +382,12 @@ static bool persistent_fits(const inpaint_ctx *c) {
     const int ntiles = d.ntx * d.nty;
     // (the committer's three polling waves scan at most 43 slots per thread)
     if (c->direct || c->d.policy != INPAINT_SOURCE_ORIGINAL || c->d.isect) return false;
-    if ((!c->mfma && d.tile_rows != kFillTileRows) || ntiles <= 0 || ntiles > 32 * kCommitThreads) return false;
+    if ((!d.mfma && d.tile_rows != kFillTileRows) || ntiles <= 0 || ntiles > kFillMaxTiles) return false;
     if ((int64_t)d.W * d.H > (1ll << kSlotIndexBits)) return false;   // slot word index field
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return false;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-    if (fill_blocks_per_cu(d.r, c->mfma, &per_cu) != hipSuccess) return false;
+    if (fill_blocks_per_cu(d.r, d.mfma != 0, &per_cu) != hipSuccess) return false;
     return (int64_t)fill_grid(ntiles) <= (int64_t)per_cu * cus;
 }
 
@@ -473,10 +473,10 @@ static bool setup_multi(inpaint_ctx *c) {
     const JobDev &d = c->d;
     const int ntiles = d.ntx * d.nty;
     if (c->direct || d.policy != INPAINT_SOURCE_ORIGINAL || d.isect) return false;
-    if (!c->mfma && d.tile_rows != kFillTileRows) return false;
-    if (ntiles <= 0 || ntiles > 32 * kCommitThreads || ntiles > c->L.fill_tiles) return false;
+    if (!d.mfma && d.tile_rows != kFillTileRows) return false;
+    if (ntiles <= 0 || ntiles > kFillMaxTiles || ntiles > c->L.fill_tiles) return false;
     if ((int64_t)d.W * d.H > (1ll << kSlotIndexBits)) return false;
-    const int cap = multi_capacity(c->mfma, d.r);
+    const int cap = multi_capacity(d.mfma != 0, d.r);
     const int n_search = cap - 1;
     if (n_search < 1 || ntiles > (int64_t)n_search * kMultiMaxItems) return false;
     std::vector<WorkItem> all(ntiles), items;
@@ -526,6 +526,22 @@ static void set_tiles(JobDev &d, int tile_rows, int mfma_r = 0) {
     d.tile_rows = tile_rows;
     d.ntx = t.ntx;
     d.nty = t.nty;
+}
+
+// Tile height of a context's SIMT searches.
+static int simt_rows(const inpaint_params &p) {
+    return p.path == INPAINT_PATH_MFMA ? kMfmaTileRows : p.tile_rows ? p.tile_rows : kDefaultTileRows;
+}
+
+// Whether a single search of radius r runs on the matrix cores.
+static bool mfma_search(const inpaint_ctx *c, int r) {
+    return c->mfma && (c->p.path == INPAINT_PATH_MFMA || r >= kAutoMfmaRadius);
+}
+
+// The fill loop's search and its tiling.
+static void set_search(inpaint_ctx *c, bool mfma) {
+    c->d.mfma = mfma ? 1 : 0;
+    set_tiles(c->d, mfma ? kMfmaTileRows : simt_rows(c->p), mfma ? c->d.r : 0);
 }
 
 static int32_t create_fail(inpaint_ctx *c, int32_t st, const std::string &msg) {
@@ -588,13 +604,13 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     d.partials = (uint64_t *)(ws + L.partials);
     d.tgt = (TargetStage *)(ws + L.tgt);
     d.qtgt = (TargetStage *)(ws + L.qtgt);
-    // AUTO searches on the matrix cores wherever that search can run: a
+    // AUTO may search on the matrix cores wherever that search can run: a
     // candidate's whole window is scored (INTERSECT counts per pixel) and the
     // caller asks for no SIMT tile height.  Per iteration, SIMT against MFMA:
     // persistent 1080p 15.1 / 8.2 us (9x9) and 28.0 / 9.4 (11x11), 480x639
     // 17x17 44.9 / 16.3; plain 640x480 30.6 / 27.6, 128x96 33 / 28.
-    d.mfma = p->path == INPAINT_PATH_MFMA ||
-             (p->path == INPAINT_PATH_AUTO && p->scoring == INPAINT_SCORE_WHOLE && p->tile_rows == 0);
+    c->mfma = p->path == INPAINT_PATH_MFMA ||
+              (p->path == INPAINT_PATH_AUTO && p->scoring == INPAINT_SCORE_WHOLE && p->tile_rows == 0);
     d.srcp = (uint32_t *)(ws + L.srcp);
     d.vradp = ws + L.vradp;
     d.hdist = L.hdist ? ws + L.hdist : nullptr;
@@ -633,9 +649,8 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     d.ry0 = k[1];
     d.rx1 = std::max(k[2], k[0]);
     d.ry1 = std::max(k[3], k[1]);
-    c->mfma = d.mfma != 0;
     c->direct = p->path == INPAINT_PATH_SIMT_DIRECT;
-    set_tiles(d, c->mfma ? kMfmaTileRows : (p->tile_rows ? p->tile_rows : kDefaultTileRows), c->mfma ? d.r : 0);
+    set_search(c, mfma_search(c, d.r));
 
     // Priority blocks: the hole's bbox grown by 2r+1 (how far a fill can
     // change a priority), in 8x8 blocks.
@@ -685,19 +700,27 @@ int32_t inpaint_create(const inpaint_image *img, const uint8_t *mask, int32_t ma
     if (!c->h_state->pending && !c->h_state->done)
         return create_fail(c, INPAINT_DEVICE, "the first selection did not run (no error was reported)");
     c->run_form = p->form;
-    if (p->form == INPAINT_FORM_PERSISTENT && !persistent_fits(c) && !setup_multi(c)) {
-        // the MFMA tiling may need one more column of tiles than the SIMT one
-        const bool simt = c->mfma && p->path == INPAINT_PATH_AUTO;
-        if (simt) {
-            c->mfma = d.mfma = 0;
-            set_tiles(d, kDefaultTileRows);
+    if (p->form == INPAINT_FORM_PERSISTENT) {
+        const auto fits = [&](bool mfma) {
+            set_search(c, mfma);
+            return persistent_fits(c) || setup_multi(c);
+        };
+        bool ok;
+        if (c->mfma && p->path == INPAINT_PATH_AUTO) {
+            // AUTO runs this form where the SIMT tiling does.  Images that only
+            // the MFMA tiling takes have more than 8 tiles per search group, all
+            // but two staged again every iteration: 6000x4000, us an iteration,
+            // persistent / stream, radius 2 69.5 / 50.9, radius 4 78 / 60, radius
+            // 8 144 / 101 (3840x2160, 4 tiles: level).  The MFMA tiling may also
+            // need one more column of tiles than the SIMT one.
+            const Tiling simt = tiling(d.rx0, d.ry0, d.rx1, d.ry1, kFillTileRows);
+            ok = simt.count() <= kFillMaxTiles && (fits(true) || fits(false));
+        } else {
+            ok = fits(c->mfma);
         }
-        if (!simt || (!persistent_fits(c) && !setup_multi(c))) {
+        if (!ok) {
             c->run_form = INPAINT_FORM_STREAM;
-            if (simt) {
-                c->mfma = d.mfma = 1;
-                set_tiles(d, kMfmaTileRows, d.r);
-            }
+            set_search(c, mfma_search(c, d.r));
         }
     }
     *out = c;
@@ -730,11 +753,12 @@ int32_t inpaint_find_exemplar(inpaint_ctx *ctx, int32_t tx, int32_t ty, int32_t 
     q.ry0 = k[1];
     q.rx1 = k[2];
     q.ry1 = k[3];
-    set_tiles(q, d.tile_rows, ctx->mfma ? r : 0);
+    const bool mfma = mfma_search(ctx, r);
+    set_tiles(q, mfma ? kMfmaTileRows : simt_rows(ctx->p), mfma ? r : 0);
     hipStream_t s = ctx->stream;
     uint64_t *dkey = (uint64_t *)(ctx->ws + ctx->L.key);
     HIP_OR_FAIL(ctx, launch_stage_query(q, tx, ty, r, s), "stage");
-    if (ctx->mfma)
+    if (mfma)
         HIP_OR_FAIL(ctx, launch_search_mfma(q, true, r, q.rx0, q.ry0, q.rx1, q.ry1, q.ntx, q.nty, s), "search");
     else if (ctx->direct)
         HIP_OR_FAIL(ctx, launch_search_direct(q, true, r, q.rx0, q.ry0, q.rx1, q.ry1, q.tile_rows, q.ntx, q.nty, s),
@@ -773,7 +797,8 @@ int32_t inpaint_find_exemplar_static(inpaint_ctx *ctx, int32_t tx, int32_t ty, i
     q.ry0 = k[1];
     q.rx1 = k[2];
     q.ry1 = k[3];
-    const StaticRoute route = static_route(ctx->p.path, ctx->mfma, d.tile_rows, r, k[0], k[1], k[2], k[3]);
+    const StaticRoute route =
+        static_route(ctx->p.path, mfma_search(ctx, r), simt_rows(ctx->p), r, k[0], k[1], k[2], k[3]);
     if (!route.ok)
         return ctx->fail(INPAINT_INVALID_ARGUMENT, "search rect needs more than " + std::to_string(kStaticMaxTiles) +
                                                        " search tiles (the static scratch limit)");
@@ -820,7 +845,7 @@ static hipError_t enqueue_iteration(inpaint_ctx *ctx, hipStream_t s, int slot = 
     const JobDev &d = ctx->d;
     hipError_t e = hipSuccess;
     hipEvent_t e0 = slot >= 0 ? ctx->ev0[slot] : nullptr, e1 = slot >= 0 ? ctx->ev1[slot] : nullptr;
-    if (ctx->mfma)
+    if (d.mfma)
         e = launch_search_mfma(d, false, d.r, d.rx0, d.ry0, d.rx1, d.ry1, d.ntx, d.nty, s, e0, e1);
     else if (ctx->direct)
         e = launch_search_direct(d, false, d.r, d.rx0, d.ry0, d.rx1, d.ry1, d.tile_rows, d.ntx, d.nty, s, e0, e1);
@@ -924,7 +949,7 @@ int32_t inpaint_run(inpaint_ctx *ctx, int64_t max_iters, int64_t *iters_done, in
             const JobDev &d = ctx->d;
             if (ctx->prof) HIP_OR_FAIL(ctx, hipEventRecord(ctx->ev0[0], s), "event");
             if (ctx->multi)
-                HIP_OR_FAIL(ctx, launch_fill_multi(ctx->mplan, ctx->mfma, d.r, ctx->multi_grid, n, next_epoch(), s),
+                HIP_OR_FAIL(ctx, launch_fill_multi(ctx->mplan, d.mfma != 0, d.r, ctx->multi_grid, n, next_epoch(), s),
                             "persistent launch");
             else
                 HIP_OR_FAIL(ctx, launch_fill(d, d.ntx * d.nty, n, next_epoch(), s), "persistent launch");
@@ -1512,7 +1537,7 @@ static bool group_multi(inpaint_batch *b, const std::vector<std::pair<int, const
         for (const auto &j : kv.second) {
             const JobDev d = multi_desc(j.second, auto_simt);
             const int nt = d.ntx * d.nty;
-            if (nt > 32 * kCommitThreads || (int64_t)d.W * d.H > (1ll << kSlotIndexBits)) return false;
+            if (nt > kFillMaxTiles || (int64_t)d.W * d.H > (1ll << kSlotIndexBits)) return false;
             pl.jobs.push_back(j.first);
             for (int t = 0; t < nt; ++t) {
                 pl.all.push_back(WorkItem{j.first, t});

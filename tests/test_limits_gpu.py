@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+import oracle
 from paper_1403_4238_amd import synth
 
 from test_parity_gpu import B, _built, _full_run_parity  # noqa: F401
@@ -164,3 +165,40 @@ def test_minima_of_many_tiles(tiles):
     log = _full_run_parity(synth.Job("wide", rgb, mask, r), "%d tiles" % tiles, path=B.PATH_SIMT, form="stream",
                            iters_per_check=4)
     assert len(np.unique(log["source_index"] % W // 64)) > 4
+
+
+# 8200 SIMT tiles and 4100 MFMA tiles: AUTO runs the persistent form where the
+# SIMT tiling does, so it takes the stream form here; results are the same.
+@pytest.mark.parametrize("r", [1, 2])
+def test_auto_persistent_goes_by_the_simt_tiles(r):
+    W, H = 64 * 99 + 40 + 2 * r, 32 * 81 + 20 + 2 * r
+    rgb = _noise(W, H, r)
+    mask = np.zeros((H, W), np.uint8)
+    mask[700:712, 3000:3020] = 1
+    logs = []
+    for path, form in ((B.PATH_AUTO, "stream"), (B.PATH_MFMA, "persistent"), (B.PATH_SIMT, "stream")):
+        g = B.Inpainter(rgb, mask, r, path=path, form="persistent", iters_per_check=32)
+        assert g.run_form() == form
+        st, n, log = g.run(log_cap=400)
+        assert st == B.DONE
+        logs.append(log.tobytes())
+        g.close()
+    assert logs[0] == logs[1] == logs[2]
+
+
+# The MFMA tile of radius 1 at the edges of its tiles (AUTO's queries of that
+# radius run the SIMT search).
+@pytest.mark.parametrize("cw,ch", [(1, 40), (64, 64), (65, 63), (67, 130)])
+def test_mfma_tile_edges_radius_1(cw, ch):
+    W, H, r = cw + 2, ch + 2, 1
+    rgb = _noise(W, H, cw)
+    rgb[: H // 3] = np.where(rgb[: H // 3, :, :1] > 127, 255, 0)
+    mask = np.zeros((H, W), np.uint8)
+    mask[0, 0] = 1
+    o = oracle.Oracle(rgb, mask, r)
+    for path in (B.PATH_MFMA, B.PATH_AUTO):
+        g = B.Inpainter(rgb, mask, r, path=path)
+        for x, y in ((W - 1, H - 1), (0, H // 2), (W // 2, H // 2), (W // 2, 0)):
+            assert g.find_exemplar(x, y, r) == o.find_exemplar(x, y, r, (0, 0, W, H))[:2], (x, y)
+            assert g.find_exemplar_static(x, y, r) == g.find_exemplar(x, y, r)
+        g.close()

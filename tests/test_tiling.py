@@ -61,7 +61,7 @@ def test_auto_query_one_column_past_the_scratch(route):
     # 32768 SIMT tiles, accepted; the aligned MFMA tiling needs 32769
     rect = (11, 4, 2097163, 5)
     assert _simt_tiles(rect, 8) == LIMIT and _mfma_tiles(rect, 4) == LIMIT + 1
-    assert route(AUTO, True, 16, 4, rect) == (True, False, 8, LIMIT, LIMIT)
+    assert route(AUTO, True, 8, 4, rect) == (True, False, 8, LIMIT, LIMIT)
 
 
 # Widths around the limit from every residue of the first column, one tile row
@@ -74,7 +74,7 @@ def test_static_route_fits_the_scratch(route, r, rows):
         for tiles in (1, 2, LIMIT // 5, LIMIT // 3, LIMIT // 2, LIMIT - 1, LIMIT, LIMIT + 1):
             for extra in (-7, -1, 0, 1, 63):
                 rect = (r + res, r, r + res + max(64 * tiles + extra, 1), r + rows)
-                for path, mfma, tile_rows in ((AUTO, True, 16), (AUTO, False, 8), (SIMT, False, 4), (SIMT, False, 16),
+                for path, mfma, tile_rows in ((AUTO, True, 8), (AUTO, False, 8), (SIMT, False, 4), (SIMT, False, 16),
                                               (MFMA, True, 16)):
                     ok, on_mfma, used, n, room = route(path, mfma, tile_rows, r, rect)
                     if path == MFMA and r <= 6:
