@@ -1507,6 +1507,8 @@ static ItemLimits same_limits(int n) { return {n, n, n}; }
 //   radii 1-5    534, 389, 354, 320 (the graph form searches one radius
 //                after another; with 16 the batch never steps it)
 //   SIMT 9x9     160 at 4, 189 at 16
+// (12 is the best of 9x9 and near that of the others: 3x3 and 13x13 are best
+// at 8 by 1 to 2%, 17x17 level from 12.)
 constexpr ItemLimits kAutoItems{12, 16, 4};
 
 // Splits jobs (slot, context) into batched persistent dispatches: the
