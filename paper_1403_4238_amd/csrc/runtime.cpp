@@ -1287,6 +1287,7 @@ struct inpaint_batch {
     int cu_count = 256;
     // batched persistent form
     std::vector<MultiBuf> mbufs;   // one per dispatch group of running jobs (mixed MFMA radii, or form and radius)
+    size_t n_plans = 0;            // of them in use; the others keep their lists for plans of more groups
     std::string multi_sig;         // running slots the uploaded plans were built for
     std::string nofit_sig;         // running slots that did not fit one dispatch
     std::map<std::pair<int, int>, int> mcap;   // co-resident groups per (form, radius)
@@ -1618,7 +1619,8 @@ hipError_t plan_multi(inpaint_batch *b, ItemLimits limits, bool *fits) {
     if (e != hipSuccess) return e;
     b->desc_form = INPAINT_FORM_PERSISTENT;
     b->graph_sig.clear();   // the graph form rebuilds its tilings
-    b->mbufs.resize(plans.size());
+    if (b->mbufs.size() < plans.size()) b->mbufs.resize(plans.size());
+    b->n_plans = plans.size();
     for (size_t gi = 0; gi < plans.size(); ++gi) {
         const MultiGroupPlan &pl = plans[gi];
         MultiBuf &m = b->mbufs[gi];
@@ -1737,7 +1739,8 @@ extern "C" {
 // One batch step in the batched persistent form: every planned group runs G
 // iterations of its jobs in one persistent dispatch.
 static hipError_t step_multi(inpaint_batch *b, int32_t G) {
-    for (const MultiBuf &m : b->mbufs) {
+    for (size_t gi = 0; gi < b->n_plans; ++gi) {
+        const MultiBuf &m = b->mbufs[gi];
         hipError_t e = launch_fill_multi(m.plan, m.mfma, m.r, m.grid, G, next_epoch(), b->stream);
         if (e != hipSuccess) return e;
     }
